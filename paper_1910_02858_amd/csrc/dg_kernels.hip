@@ -19,11 +19,9 @@
 
 #include "dg_internal.h"
 
-// minimum waves per SIMD requested for the split-form kernel: 4 fits two 512-thread
-// workgroups per CU at N=7 (128 VGPRs), measured faster than 2-3 waves despite a small spill
-#ifndef DG_SPLIT_MINB
-#define DG_SPLIT_MINB 4
-#endif
+// waves per SIMD the split-form kernel is built for: 2 (256 registers: a line of 8 nodes holds 112
+// doubles); at N = 8 one element's LDS fills the CU and one wave per SIMD is all there is
+constexpr int split_minb(int N) { return N >= 8 ? 1 : 2; }
 // minimum waves per SIMD for the lifting kernel: 6 fits three 512-thread workgroups per CU
 #ifndef DG_LIFT_MINB
 #define DG_LIFT_MINB 6
@@ -1289,7 +1287,8 @@ struct PS {
 // VF 0: kinetic-energy preserving (Pirozzoli); 1: entropy conserving (Chandrashekar) with the
 // logarithmic means f (a+b)/(2 artanh f), f = (a-b)/(a+b), by series for f^2 < 1e-4 and by
 // logarithms otherwise; 2: mean of the two Euler fluxes.  kg = 1/(gamma-1).
-template <int VF>
+// SER: both ratios are known to lie in the series' range (no logarithms compiled in).
+template <int VF, bool SER = false>
 __device__ __forceinline__ void pair2(const PS &A, const PS &B, const double *nS, double kg, double *F) {
   const double su = A.u + B.u, sv = A.v + B.v, sw = A.w + B.w;
   if (VF == 2) {
@@ -1318,7 +1317,7 @@ __device__ __forceinline__ void pair2(const PS &A, const PS &B, const double *nS
     double rl;  // rho^ln / 2
     // beyond the series, log(a) - log(b) as one logarithm of the larger over the smaller
     // argument (the same bits from either end of the pair)
-    if (ur < 1e-4) {
+    if (SER || ur < 1e-4) {
       rl = 0.25 * sr * fma(ur, fma(ur, fma(ur, DG_LM_C3, DG_LM_C2), DG_LM_C1), 1.0);
     } else {
       rl = 0.5 * fabs(dr) / log(fmax(A.r, B.r) * frcp(fmin(A.r, B.r)));
@@ -1327,7 +1326,7 @@ __device__ __forceinline__ void pair2(const PS &A, const PS &B, const double *nS
     const double rb = frcp(sb);
     const double fb = db * rb, ub = fb * fb;
     double eb;  // 1 / (2 (gamma-1) beta^ln)
-    if (ub < 1e-4) {
+    if (SER || ub < 1e-4) {
       eb = kg * rb * fma(ub, fma(ub, fma(ub, 1.0 / 7.0, 1.0 / 5.0), 1.0 / 3.0), 1.0);
     } else {
       eb = 0.5 * kg * log(fmax(A.b, B.b) * frcp(fmin(A.b, B.b))) / fabs(db);
@@ -1396,343 +1395,411 @@ __device__ __forceinline__ void riemann_vf(const Phys &ph, const double *UL, con
   }
 }
 
-// orders this wave's LDS accesses before and after the call (LDS executes one wave's
-// instructions in order, so lanes of one wave need no workgroup barrier)
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+// LDS slots (div_slot) of the nodes of one line, without a branch on its direction: n = 8's swizzle is
+// linear over the index bits, slot = base ^ (contribution of the position's bits); else base + m stride.
+template <int n> struct LineSlots {
+  int base, s1, s2, s4;
+  __device__ __forceinline__ LineSlots(int dir, int a, int b) {
+    const int i = dir == 0 ? 0 : a, j = dir == 0 ? a : (dir == 1 ? 0 : b), k = dir == 2 ? 0 : b;
+    base = div_slot<n>(i, j, k);
+    if constexpr (n == 8) {
+      s1 = dir == 0 ? 1 : (dir == 1 ? 8 : 74);
+      s2 = dir == 0 ? 2 : (dir == 1 ? 16 : 148);
+      s4 = dir == 0 ? 4 : (dir == 1 ? 33 : 256);
+    } else {
+      s1 = dir == 0 ? 1 : (dir == 1 ? n : n * n);
+      s2 = s4 = 0;
+    }
+  }
+  __device__ __forceinline__ int operator()(int m) const {
+    if constexpr (n == 8) return base ^ ((m & 1 ? s1 : 0) ^ (m & 2 ? s2 : 0) ^ (m & 4 ? s4 : 0));
+    else return base + m * s1;
+  }
+};
 
-// LDS sizes (doubles) of one element in the split-form kernel.  Region A first holds the
-// contravariant viscous fluxes of the three directions (12 per node), then the two-point state
-// (5 per node) and the metric terms Ja^i_d (9 per node); region P first holds the six faces'
-// numerical fluxes, then the partner shares of the exchange rounds.
+// LDS sizes (doubles) of one element in the split-form kernel: the conservative state (5 per node), the
+// two-point state rho, u, v, w, beta|H (5 per node) and the metric terms Ja^i_d (9 per node); the
+// accumulated result takes the place of the metric terms once every line has read them.
 template <int N> struct SplitLds {
   static constexpr int n = N + 1, n2 = n * n, n3 = n2 * n;
-  static constexpr int A = 14 * n3;
-  static constexpr int P = (5 * n3 > 30 * n2) ? 5 * n3 : 30 * n2;
+  static constexpr int A = 19 * n3;
 };
 
-template <int N>
-__device__ __forceinline__ void split_tables(const Tab *tb, int t, int nthreads, double *sD, double *slh) {
-  constexpr int n = N + 1;
-  for (int c = t; c < n * n; c += nthreads) sD[c] = tb->D[c];
-  if (t < n) { slh[t] = tb->lhm[t]; slh[n + t] = tb->lhp[t]; }
-}
-
-// Lane layout of the split-form kernel.  With n = 7 (N = 6) the element's 343 nodes are laid out
-// on padded 8 x 8 planes, one k-plane per 64-lane wave (lane i + 8 j + 64 k, lanes with i = 7 or
-// j = 7 idle): 448 lanes instead of 384, but the lines of the first two directions then lie
-// inside one wave, like those of n = 8.  Other degrees map lane t to node t.
-#ifndef DG_SPLIT_PAD7
-#define DG_SPLIT_PAD7 1
-#endif
+// Lanes of one element in the split-form kernel: one per line of the three directions, 3 n^2 of them.
 template <int N> struct SplitSz {
-  static constexpr int n = N + 1;
-  static constexpr bool PAD = DG_SPLIT_PAD7 && n == 7;
-  static constexpr int NT = PAD ? 64 * n : Sz<N>::NT;
+  static constexpr int n = N + 1, NL = 3 * n * n;
+  static constexpr int NT = (NL + 63) / 64 * 64;
 };
 
-// exchange rounds of direction dir stay inside one 64-lane wave: lines of the first two
-// directions when n divides 64 and n^2 divides 64 (n = 2, 4, 8) or the planes are padded to
-// 8 x 8; every line when the whole element fits one wave
-template <int n> __host__ __device__ constexpr bool wave_local(int dir) {
-  return (n * n * n <= 64) || (dir < 2 && (n == 2 || n == 4 || n == 8 || SplitSz<n - 1>::PAD));
-}
+struct LineNode {  // a node of a line: its two-point state and the line direction's metric terms
+  PS s;
+  double nv[3];
+};
 
-// Split-form operator on LGL nodes (eq. semiDiscreteSplit) for element e by the NT threads t of
-// one slot: every unordered pair of nodes on a line is evaluated once; the pair's contribution
-// to the other node goes through an LDS accumulator.  Viscous part in strong form, surface
-// penalty f* s - F_int.N, -1/J, optional RK update.  Directions whose lines lie inside one wave
-// order their exchange rounds with a wave fence instead of a workgroup barrier.
-template <int N, bool NS, int VF, int MODE, int GEN, bool FVM = false>
-__device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, int e, bool valid, int lane,
-                                           const double *__restrict__ U, const double *__restrict__ G,
-                                           double *__restrict__ out, double *__restrict__ R, double ca, double cb,
-                                           double dt, double *sA, double *sP, const double *sD, const double *slh) {
+// Split-form operator on LGL nodes (eq. semiDiscreteSplit) for element e by the NT lanes of one slot.
+// A lane owns one line: it holds the line's n states and metric terms in registers, evaluates each
+// unordered pair of its nodes once and adds the pair to both nodes' sums in registers, and evaluates the
+// numerical fluxes of the two faces at the line's ends.  The three directions' sums meet in LDS in a
+// fixed order.
+// What bounds it: with one node per lane and the partner's share of each pair passed through LDS the
+// kernel issued 1686 vector instructions per node (VALU busy 71 %) and 20 LDS accesses per pair; a line
+// per lane has no exchange, no redundant half round (28 pairs for 8 nodes, not 32) and five barriers per
+// element, at 2 waves per SIMD.
+// valid = false keeps the slot's lanes in step with the workgroup barriers without touching memory.
+// mode 0 writes U_t, 1 the fused RK stage.  FVM: the sides that meet a finite-volume element take their
+// flux from Geo::fvFx.
+template <int N, bool NS, int VF, int GEN, bool FVM = false>
+__device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const Tab *tab, int e, bool valid, int lane,
+                                           const double *__restrict__ U, double *__restrict__ out,
+                                           double *__restrict__ R, double ca, double cb, double dt, int mode,
+                                           double *sm) {
   using S = Sz<N>;
   constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = SplitSz<N>::NT;
-  // t: this lane's node (lanes past the element, or on the padding, are idle)
-  int t = lane;
-  bool inb = lane < n3;
-  if constexpr (SplitSz<N>::PAD) {
-    const int i = lane & 7, j = (lane >> 3) & 7, k = lane >> 6;
-    inb = i < n && j < n && k < n;
-    t = i + n * (j + n * k);
-  }
-  const bool act = valid && inb;
+  constexpr int IT = (n3 + NT - 1) / NT;  // nodes per lane in the node loops
   const double gm1 = ph.gamma - 1.0, kg = 1.0 / gm1, gg = gm1 / ph.gamma;
   const double *Ue = U + (size_t)e * 5 * n3;
   const double *Jae = g.Ja + (size_t)e * 9 * n3;
-  double *sS = sA;           // rho, u, v, w, beta (EC) or H (KEP, central) per node
-  double *sJ = sA + 5 * n3;  // Ja^i_d at (i*3+d)*n3 + node
-  // Navier-Stokes: the lifting kernel has formed the viscous divergence (Geo::Gd) and the face
-  // traces of the viscous fluxes (Geo::Gf)
-  const double *Gfe = NS ? g.Gf + (size_t)e * 24 * n2 : nullptr;
-  // the node's own state is loaded before the face phase, so that its latency overlaps with it
-  double Uo[5];
-  if (act) {
+  double *sU = sm, *sS = sm + 5 * n3, *sJ = sm + 10 * n3;  // node slots: div_slot
+  double *sAcc = sJ;
+  // the 1D tables through the scalar cache
+  const __attribute__((address_space(4))) double *D = (const __attribute__((address_space(4))) double *)tab->D;
+  const double lh0 = tab->lhm[0], lhN = tab->lhp[N];
+  // this lane's line: direction, and its position (a, b) among the direction's lines, which is also the
+  // face point of its two ends
+  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(lane / n2) : lane / n2;
+  const int ab = lane - dir * n2, a = ab % n, b = ab / n;
+  const bool act = valid && lane < 3 * n2;
+  // the two end faces' neighbours first (loads return in order: behind the others, the neighbours' traces
+  // would wait for all of them), then the state and metric terms for LDS and the faces' other sides
+  int nb2[2] = {0, 0};
+  NbFace f2[2];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) Uo[v] = Ue[v * n3 + t];
+  for (int sd = 0; sd < 2; ++sd)
+    if (act) {
+      nb2[sd] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
+      f2[sd] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
+    }
+  double Uq[IT][5];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Uq[it][v] = Ue[v * n3 + t];
+    }
   }
-  // numerical surface flux on the six faces, stored outward for this element
-  for (int q = valid ? lane : 6 * n2; q < 6 * n2; q += NT) {
-    const int s = q / n2, ab = q - s * n2, a = ab % n, b = ab / n, dn = s >> 1;
-    const bool plus = s & 1;
-    const int nb = g.nbr[(size_t)e * 6 + s];
-    const NbFace f = nbr_face<n, (GEN > 0)>(g, e, s, a, b);
+  double Jq[IT][9];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) Jq[it][c] = Jae[c * n3 + t];
+    }
+  }
+  double Ux[2][5], Vo[2][4], Vn[2][4];  // the end faces: the other side's state, both sides' viscous fluxes
+  int kind[2];                // -1 inner face, else the boundary kind; -2 a face whose flux is given (Ux)
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd) {
+    kind[sd] = -1;
+    if (!act) continue;
+    const int s = 2 * dir + sd;
+    const bool plus = sd;
+    const int nb = nb2[sd];
+    const NbFace f = f2[sd];
     const bool bnd = GEN && f.bnd;
     if (GEN == 2 && bnd && f.kind == FACE_MORTAR) {
       // non-conforming face: the outward flux from the mortar face array
       const double *mf = g.mflux + (size_t)g.mslot[(size_t)e * 6 + s] * 5 * n2 + ab;
+      kind[sd] = -2;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) sP[(s * 5 + v) * n2 + ab] = mf[v * n2];
+      for (int v = 0; v < 5; ++v) Ux[sd][v] = mf[v * n2];
       continue;
     }
     if (FVM && g.fvflag[nb]) {
       // face shared with a finite-volume element: the outward flux at the face nodes
       const double *fx = g.fvFx + ((size_t)e * 6 + s) * 5 * n2 + ab;
+      kind[sd] = -2;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) sP[(s * 5 + v) * n2 + ab] = fx[v * n2];
+      for (int v = 0; v < 5; ++v) Ux[sd][v] = fx[v * n2];
       continue;
     }
-    const double *Un = U + (size_t)(bnd ? e : nb) * 5 * n3;
-    const int qo = line_node<n>(dn, a, b, plus ? N : 0);
-    const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dn, a, b, plus ? 0 : N);
-    // this side's trace of Fv^dn at the face point (component c at fo[c * n2]) and the
-    // neighbour's trace of Fv^{f.dn} on its side of the face (fnb[c * n2])
-    const double *fo = NS ? Gfe + s * 4 * n2 + ab : nullptr;
-    const double *fnb = NS ? g.Gf + ((size_t)(bnd ? e : nb) * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b
-                           : nullptr;
-    double Uw[5], Ux[5];
+    if (bnd) kind[sd] = f.kind;
+    if (!bnd) {
+      const double *Un = U + (size_t)nb * 5 * n3;
+      const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dir, a, b, plus ? 0 : N);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) { Uw[v] = Ue[v * n3 + qo]; Ux[v] = bnd ? Uw[v] : Un[v * n3 + qn]; }
-    // normal along +xi_dn scaled by s-hat: Ja^dn at the face node, the master's on the master
-    // side and (up to rounding, the metric terms being continuous across the face) on the slave
-    const double sg = plus ? 1.0 : -1.0;
-    const double nt[3] = {Jae[(dn * 3) * n3 + qo], Jae[(dn * 3 + 1) * n3 + qo], Jae[(dn * 3 + 2) * n3 + qo]};
-    const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
-    const double ish = 1.0 / sh;
-    const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
-    const bool given = bnd && (f.kind == DG_BC_STATE || f.kind == DG_BC_OUTFLOW);
-    const bool iso = bnd && f.kind == DG_BC_WALL_ISOTHERMAL;
-    const bool wall = bnd && (f.kind == DG_BC_WALL || iso);
-    if (given && f.kind == DG_BC_OUTFLOW) {
-      // pressure outflow: the own trace's density and velocity with p_out
-      Ux[4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
-    } else if (given) {
-#pragma unroll
-      for (int v = 0; v < 5; ++v) Ux[v] = ph.ub[v];  // given outer state
-    } else if (wall) {
-      Ux[1] = -Uw[1]; Ux[2] = -Uw[2]; Ux[3] = -Uw[3];  // no-slip wall: velocity reversed
-    } else if (bnd) {
-      mirror3(Ux + 1, nh);  // symmetry plane: mirror image of the inner state
+      for (int v = 0; v < 5; ++v) Ux[sd][v] = Un[v * n3 + qn];
     }
-    const double *UM = plus ? Uw : Ux, *US = plus ? Ux : Uw;
-    double F[5];
-    riemann_vf<VF>(ph, UM, US, nh, F);
-#pragma unroll
-    for (int v = 0; v < 5; ++v) F[v] *= sh;
     if (NS) {
-      // BR1 mean of the viscous fluxes along this side's +xi_dn normal Ja^dn: on both sides the
-      // contravariant flux of the face's direction (the normal metric of a conforming face is
-      // continuous: the neighbour's Ja of its face direction is +-Ja^dn, + where one side is a
-      // +xi side and the other a -xi side)
-      if (given) {
-        // given outer state: the outer viscous flux equals the inner one
+      // both sides' contravariant viscous flux of the face's direction from the lifting (a boundary side:
+      // the own trace); only loaded here, so that both faces' loads are in flight at once
+      const double *fo = g.Gf + ((size_t)e * 6 + s) * 4 * n2 + ab;
+      const double *fnb = bnd ? fo : g.Gf + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) F[1 + c] -= fo[c * n2];
-      } else if (wall) {
-        // no-slip wall: the outer momentum flux equals the inner one, the outer energy flux is
-        // its negative (reversed velocity, mirrored heat flux), so the mean keeps the momentum;
-        // at an isothermal wall the outer gradient is the inner one, so the mean energy flux is
-        // the inner heat flux: the inner energy flux minus the work (tau Ja^dn) . u
-        double g3[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          g3[c] = fo[c * n2];
-          F[1 + c] -= g3[c];
-        }
-        if (iso) {
-          const double ir = 1.0 / Uw[0];
-          F[4] -= fo[3 * n2] - (g3[0] * Uw[1] + g3[1] * Uw[2] + g3[2] * Uw[3]) * ir;
-        }
-      } else if (bnd) {
-        // symmetry plane: the mirrored outer flux cancels the inner shear and heat flux, the
-        // mean keeps the normal part of the momentum flux
-        const double gm = fo[0] * nh[0] + fo[n2] * nh[1] + fo[2 * n2] * nh[2];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) F[1 + c] -= gm * nh[c];
-      } else if (GEN) {
-        const double sn = (f.plus != plus) ? 1.0 : -1.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) F[1 + c] -= 0.5 * (fo[c * n2] + sn * fnb[c * n2]);
-      } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) F[1 + c] -= 0.5 * (fo[c * n2] + fnb[c * n2]);
-      }
+      for (int c = 0; c < 4; ++c) { Vo[sd][c] = fo[c * n2]; Vn[sd][c] = fnb[c * n2]; }
     }
+  }
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sP[(s * 5 + v) * n2 + ab] = sg * F[v];
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+      const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+      const Pr5 P = to_prim(Uq[it], gm1);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sU[v * n3 + q] = Uq[it][v];
+      sS[q] = P.rho; sS[n3 + q] = P.u; sS[2 * n3 + q] = P.v; sS[3 * n3 + q] = P.w;
+      // beta = rho / (2 p) for EC, the total enthalpy otherwise
+      sS[4 * n3 + q] = (VF == 1) ? 0.5 * P.rho / P.p : (Uq[it][4] + P.p) / P.rho;
+#pragma unroll
+      for (int c = 0; c < 9; ++c) sJ[c * n3 + q] = Jq[it][c];
+    }
   }
   __syncthreads();
-  PS o;
-  double p = 0.0;
+  double acc[n][5];
   if (act) {
-    const Pr5 P = to_prim(Uo, gm1);
-    p = P.p;
-    o.r = P.rho; o.u = P.u; o.v = P.v; o.w = P.w;
-    if (VF == 1) {
-      o.b = 0.5 * P.rho / P.p;
-      o.q = P.u * P.u + P.v * P.v + P.w * P.w;
-    } else {
-      o.b = P.p;
-      o.q = (Uo[4] + P.p) / P.rho;
-    }
-  }
-  double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  const int id3[3] = {t % n, (t / n) % n, t / n2};
-  if (act) {
-    // surface integral, numerical-flux part: lhat(+-1) f* s on the faces through this node
-#pragma unroll
-    for (int dir = 0; dir < 3; ++dir) {
-      const int id = id3[dir];
-      if (id != 0 && id != N) continue;
-      const int sd = (id == N) ? 1 : 0;
-      const int s = 2 * dir + sd;
-      const double lh = slh[(sd ? n : 0) + id];
-      const int a = dir == 0 ? id3[1] : id3[0], b = dir == 2 ? id3[1] : id3[2];
-      const int ab = a + n * b;
-#pragma unroll
-      for (int v = 0; v < 5; ++v) acc[v] += lh * sP[(s * 5 + v) * n2 + ab];
-    }
-  }
-  double ja[9];
-  if (act) {
-#pragma unroll
-    for (int c = 0; c < 9; ++c) ja[c] = Jae[c * n3 + t];
-  }
-  if (act) {
-    sS[t] = o.r; sS[n3 + t] = o.u; sS[2 * n3 + t] = o.v; sS[3 * n3 + t] = o.w;
-    sS[4 * n3 + t] = (VF == 1) ? o.b : o.q;
-#pragma unroll
-    for (int c = 0; c < 9; ++c) sJ[c * n3 + t] = ja[c];
-  }
-  // the first direction's barrier also separates the face-flux reads above from the partner
-  // shares and publishes the staged state of every node
-  double Rq[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, sjq = 0.0;
-#pragma unroll
-  for (int dir = 0; dir < 3; ++dir) {
-    if (dir == 2 && act) {
-      // the epilogue's loads are issued before the last direction's rounds
-      sjq = g.sJ[(size_t)e * n3 + t];
-      if (MODE == 1 && ca != 0.0) {
-        const double *Re = R + (size_t)e * 5 * n3;
-#pragma unroll
-        for (int v = 0; v < 5; ++v) Rq[v] = Re[v * n3 + t];
-      }
-    }
-    const bool wl = wave_local<n>(dir);
-    if (dir > 0 && wl) wave_sync(); else __syncthreads();
+    const LineSlots<n> slot(dir, a, b);
     const double *sJd = sJ + 3 * dir * n3;
-    double nvo[3] = {0.0, 0.0, 0.0};
-    if (act) { nvo[0] = sJd[t]; nvo[1] = sJd[n3 + t]; nvo[2] = sJd[2 * n3 + t]; }
-    const int id = act ? id3[dir] : 0;
-    const int str = dir == 0 ? 1 : (dir == 1 ? n : n2);
-    const int base = t - id * str;
-    // pairs (id, id+s mod n), s = 1 .. (n-1)/2: each unordered pair once, both nodes updated
-#pragma unroll 1
-    for (int sft = 1; sft <= (n - 1) / 2; ++sft) {
-      // barriers stay in uniform control flow: only the work is guarded
-      if (act) {
-        int jp = id + sft;
-        if (jp >= n) jp -= n;
-        const int qp = base + jp * str;
-        const PS bq = load_ps<VF>(sS, n3, qp, gg);
-        const double nS[3] = {nvo[0] + sJd[qp], nvo[1] + sJd[n3 + qp], nvo[2] + sJd[2 * n3 + qp]};
-        double F[5];
-        pair2<VF>(o, bq, nS, kg, F);
-        const double Dij = sD[id * n + jp], Dji = sD[jp * n + id];
+    // numerical surface fluxes at the line's ends, lifted (outward times lhat), and the interior
+    // convective part: 2 D_ii F(U_i) (D_ii is non-zero only at the ends of LGL lines) -+ lhat F_int
+    double fe[2][5];
 #pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          acc[v] = fma(Dij, F[v], acc[v]);
-          sP[v * n3 + qp] = Dji * F[v];
+    for (int sd = 0; sd < 2; ++sd) {
+      const bool plus = sd;
+      const int qo = slot(plus ? N : 0);
+      const double sg = plus ? 1.0 : -1.0, lh = plus ? lhN : lh0;
+      double Uw[5], Fo[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Uw[v] = sU[v * n3 + qo];
+      // normal along +xi scaled by s-hat: Ja^dir at the face node, the master's on the master side and
+      // (up to rounding, the metric terms being continuous across the face) on the slave
+      const double nt[3] = {sJd[qo], sJd[n3 + qo], sJd[2 * n3 + qo]};
+      const Pr5 Pw = {Uw[0], sS[n3 + qo], sS[2 * n3 + qo], sS[3 * n3 + qo],
+                      gm1 * (Uw[4] - 0.5 * (Uw[1] * sS[n3 + qo] + Uw[2] * sS[2 * n3 + qo] + Uw[3] * sS[3 * n3 + qo]))};
+      flux_c(Uw, Pw, nt, Fo);
+      const double cd = 2.0 * D[plus ? N * n + N : 0] - sg * lh;
+      double F[5];
+      if ((GEN == 2 || FVM) && kind[sd] == -2) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) F[v] = sg * Ux[sd][v];
+      } else {
+        const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
+        const double ish = 1.0 / sh;
+        const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
+        const bool bnd = GEN && kind[sd] >= 0;
+        const bool outflow = bnd && kind[sd] == DG_BC_OUTFLOW;
+        const bool given = bnd && (kind[sd] == DG_BC_STATE || outflow);
+        const bool iso = bnd && kind[sd] == DG_BC_WALL_ISOTHERMAL;
+        const bool wall = bnd && (kind[sd] == DG_BC_WALL || iso);
+        if (bnd) {
+#pragma unroll
+          for (int v = 0; v < 5; ++v) Ux[sd][v] = Uw[v];
+          if (outflow) {
+            // pressure outflow: the own trace's density and velocity with p_out
+            Ux[sd][4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
+          } else if (given) {
+#pragma unroll
+            for (int v = 0; v < 5; ++v) Ux[sd][v] = ph.ub[v];  // given outer state
+          } else if (wall) {
+            Ux[sd][1] = -Uw[1]; Ux[sd][2] = -Uw[2]; Ux[sd][3] = -Uw[3];  // no-slip wall: velocity reversed
+          } else {
+            mirror3(Ux[sd] + 1, nh);  // symmetry plane: mirror image of the inner state
+          }
+        }
+        riemann_vf<VF>(ph, plus ? Uw : Ux[sd], plus ? Ux[sd] : Uw, nh, F);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) F[v] *= sh;
+        if (NS) {
+          // BR1 mean of the viscous fluxes along this side's +xi normal Ja^dir (the normal metric of a
+          // conforming face is continuous: the neighbour's Ja of its face direction is +-Ja^dir, + where
+          // one side is a +xi side and the other a -xi side)
+          double V[4];
+          const double sn = (GEN && f2[sd].plus == plus) ? -1.0 : 1.0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[sd][c] : 0.5 * (Vo[sd][c] + sn * Vn[sd][c]);
+          if (!bnd || given) {
+            // given outer state: the outer viscous flux equals the inner one
+#pragma unroll
+            for (int c = 0; c < 4; ++c) F[1 + c] -= V[c];
+          } else if (wall) {
+            // no-slip wall: the outer momentum flux equals the inner one, the outer energy flux is its
+            // negative (reversed velocity, mirrored heat flux), so the mean keeps the momentum; at an
+            // isothermal wall the outer gradient is the inner one, so the mean energy flux is the inner
+            // heat flux: the inner energy flux minus the work (tau Ja^dir) . u
+#pragma unroll
+            for (int c = 0; c < 3; ++c) F[1 + c] -= V[c];
+            if (iso) F[4] -= V[3] - (V[0] * Uw[1] + V[1] * Uw[2] + V[2] * Uw[3]) * (1.0 / Uw[0]);
+          } else {
+            // symmetry plane: the mirrored outer flux cancels the inner shear and heat flux, the mean
+            // keeps the normal part of the momentum flux
+            const double gm = V[0] * nh[0] + V[1] * nh[1] + V[2] * nh[2];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) F[1 + c] -= gm * nh[c];
+          }
         }
       }
-      // every node receives exactly one partner share per round: collect it in a fixed order
-      if (wl) wave_sync(); else __syncthreads();
-      if (act) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) acc[v] += sP[v * n3 + t];
+      for (int v = 0; v < 5; ++v) fe[sd][v] = fma(cd, Fo[v], (sg * lh) * F[v]);
+    }
+#pragma unroll
+    for (int m = 0; m < n; ++m)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) acc[m][v] = m == 0 ? fe[0][v] : (m == N ? fe[1][v] : 0.0);
+    // EC: where every pair of every line of this wave lies in the series' range (the largest ratio of a
+    // line is that of its largest and smallest value) the unrolled loop below needs no logarithm
+    bool series = true;
+    if constexpr (VF == 1) {
+      double r0 = sS[slot(0)], r1 = r0, b0 = sS[4 * n3 + slot(0)], b1 = b0;
+#pragma unroll
+      for (int m = 1; m < n; ++m) {
+        const double r = sS[slot(m)], bt = sS[4 * n3 + slot(m)];
+        r0 = fmin(r0, r); r1 = fmax(r1, r);
+        b0 = fmin(b0, bt); b1 = fmax(b1, bt);
       }
-      if (wl) wave_sync(); else __syncthreads();
+      const double dr = r1 - r0, sr = r1 + r0, db = b1 - b0, sb = b1 + b0;
+      series = dr * dr < 0.99e-4 * (sr * sr) && db * db < 0.99e-4 * (sb * sb);
+      series = __all(series);
     }
-    if (act && (n & 1) == 0) {
-      // s = n/2 pairs each other twice: each side takes only its own share
-      int jp = id + n / 2;
-      if (jp >= n) jp -= n;
-      const int qp = base + jp * str;
-      const PS bq = load_ps<VF>(sS, n3, qp, gg);
-      const double nS[3] = {nvo[0] + sJd[qp], nvo[1] + sJd[n3 + qp], nvo[2] + sJd[2 * n3 + qp]};
-      double F[5];
-      pair2<VF>(o, bq, nS, kg, F);
-      const double Dij = sD[id * n + jp];
+    if (VF != 1 || series) {
+      // node i in registers, its partners read from LDS one pair ahead of their use (a whole line in
+      // registers spills 500 bytes at n = 8); the first partner is the next row's node
+      auto node = [&](int m) -> LineNode {
+        LineNode x;
+        const int q = slot(m);
+        x.s = load_ps<VF>(sS, n3, q, gg);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) acc[v] = fma(Dij, F[v], acc[v]);
-    }
-    if (act && (id == 0 || id == N)) {
-      // end nodes of the line: diagonal F#(U,U) = F(U).Ja (D_ii is non-zero only there on LGL
-      // lines) and the interior convective part - F_int . N_out lhat(+-1) of the surface integral
-      const Pr5 P = {o.r, o.u, o.v, o.w, p};
-      double Fc[5];
-      flux_c(Uo, P, nvo, Fc);
-      const double Dii = sD[id * n + id];
-      const bool plus = id == N;
-      const double lh = slh[(plus ? n : 0) + id];
-      const double cd = 2.0 * Dii + (plus ? -lh : lh);
+        for (int d = 0; d < 3; ++d) x.nv[d] = sJd[d * n3 + q];
+        return x;
+      };
+      LineNode A = node(0), B = node(1), An = B, Bn = B;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) acc[v] += cd * Fc[v];
+      for (int i = 0; i + 1 < n; ++i) {
+#pragma unroll
+        for (int j = i + 1; j < n; ++j) {
+          if (j == i + 1) An = B;
+          if (j + 1 < n) Bn = node(j + 1);
+          else if (i + 2 < n) Bn = node(i + 2);
+          const double nS[3] = {A.nv[0] + B.nv[0], A.nv[1] + B.nv[1], A.nv[2] + B.nv[2]};
+          double F[5];
+          pair2<VF, true>(A.s, B.s, nS, kg, F);
+          const double Dij = D[i * n + j], Dji = D[j * n + i];
+#pragma unroll
+          for (int v = 0; v < 5; ++v) {
+            acc[i][v] = fma(Dij, F[v], acc[i][v]);
+            acc[j][v] = fma(Dji, F[v], acc[j][v]);
+          }
+          B = Bn;
+          // at most two pairs in flight: more spill (n <= 6 fits as scheduled)
+          if (n > 6 && (j - i) % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+        }
+        A = An;
+        asm volatile("" ::: "memory");  // the next row's partners are read again, not kept
+      }
+    } else {
+      // the same pairs (i, i + s mod n) with logarithms, the states read from LDS as they are met; a
+      // rolled loop over i whose sums move down one place per turn, so that node i's is always the first
+#pragma unroll 1
+      for (int i = 0; i < n; ++i) {
+        const int qi = slot(i);
+        const PS A = load_ps<VF>(sS, n3, qi, gg);
+        const double na[3] = {sJd[qi], sJd[n3 + qi], sJd[2 * n3 + qi]};
+#pragma unroll
+        for (int sft = 1; sft <= n / 2; ++sft) {
+          if (2 * sft == n && 2 * i >= n) continue;  // met from the other end
+          const int j = i + sft < n ? i + sft : i + sft - n;
+          const int qj = slot(j);
+          const PS B = load_ps<VF>(sS, n3, qj, gg);
+          const double nS[3] = {na[0] + sJd[qj], na[1] + sJd[n3 + qj], na[2] + sJd[2 * n3 + qj]};
+          double F[5];
+          pair2<VF>(A, B, nS, kg, F);
+          const double Dij = D[i * n + j], Dji = D[j * n + i];
+#pragma unroll
+          for (int v = 0; v < 5; ++v) {
+            acc[0][v] = fma(Dij, F[v], acc[0][v]);
+            acc[sft][v] = fma(Dji, F[v], acc[sft][v]);
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          const double x = acc[0][v];
+#pragma unroll
+          for (int m = 0; m + 1 < n; ++m) acc[m][v] = acc[m + 1][v];
+          acc[N][v] = x;
+        }
+      }
     }
   }
-  if (act) {
-    if (NS) {
-      // viscous part in strong form, formed by the lifting kernel (loaded here: held through the
-      // rounds, these four values push the operator past its register budget)
+  // the epilogue's loads are issued before the directions' sums meet
+  double Rq[IT][5], gd[IT][4], sjq[IT];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[1 + c] -= g.Gd[((size_t)e * 4 + c) * n3 + t];
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+      sjq[it] = g.sJ[(size_t)e * n3 + t];
+      if (NS) {
+        // viscous part in strong form, formed by the lifting kernel
+#pragma unroll
+        for (int c = 0; c < 4; ++c) gd[it][c] = g.Gd[((size_t)e * 4 + c) * n3 + t];
+      }
+      if (mode == 1 && ca != 0.0) {
+        const double *Re = R + (size_t)e * 5 * n3;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Rq[it][v] = Re[v * n3 + t];
+      }
     }
-    const double sj = sjq;
-    double *Oe = out + (size_t)e * 5 * n3;
-    if (MODE == 0) {
+  }
+  // the three directions' sums, in order
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Oe[v * n3 + t] = -acc[v] * sj;
+  for (int d = 0; d < 3; ++d) {
+    __syncthreads();
+    if (act && dir == d) {
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        const int q = d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m));
+#pragma unroll
+        for (int v = 0; v < 5; ++v) sAcc[v * n3 + q] = d == 0 ? acc[m][v] : sAcc[v * n3 + q] + acc[m][v];
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (!(valid && t < n3)) continue;
+    const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+    double r[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) r[v] = sAcc[v * n3 + q];
+    if (NS) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) r[1 + c] -= gd[it][c];
+    }
+    double *Oe = out + (size_t)e * 5 * n3;
+    if (mode == 0) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Oe[v * n3 + t] = -r[v] * sjq[it];
     } else {
       double *Re = R + (size_t)e * 5 * n3;
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         // a = 0 (first stage) does not read R, so R may hold anything on entry
-        const double r = (ca != 0.0 ? ca * Rq[v] : 0.0) + dt * (-acc[v] * sj);
-        Re[v * n3 + t] = r;
-        Oe[v * n3 + t] = Uo[v] + cb * r;
+        const double x = (ca != 0.0 ? ca * Rq[it][v] : 0.0) + dt * (-r[v] * sjq[it]);
+        Re[v * n3 + t] = x;
+        Oe[v * n3 + t] = sU[v * n3 + q] + cb * x;
       }
     }
   }
 }
 
-template <int N, bool NS, int VF, int MODE, int GEN, bool FVM = false>
-__global__ void __launch_bounds__(SplitSz<N>::NT, DG_SPLIT_MINB) k_split(Geo g, Phys ph, const double *__restrict__ U,
-                                                     const double *__restrict__ G, double *__restrict__ out,
-                                                     double *__restrict__ R, double ca, double cb, double dt) {
-  using L = SplitLds<N>;
-  constexpr int n = L::n;
-  __shared__ double sA[L::A], sP[L::P];
-  __shared__ double sD[n * n], slh[2 * n];
-  split_tables<N>(g.tab, threadIdx.x, SplitSz<N>::NT, sD, slh);
+template <int N, bool NS, int VF, int GEN, bool FVM = false>
+__global__ void __launch_bounds__(SplitSz<N>::NT, split_minb(N)) k_split(Geo g, Phys ph, const double *__restrict__ U,
+                                                     double *__restrict__ out, double *__restrict__ R, double ca,
+                                                     double cb, double dt, int mode) {
+  __shared__ double sm[SplitLds<N>::A];
   const int e = xcd_element(blockIdx.x, g.K);
   if (e >= g.K) return;
   if (FVM && g.fvflag[e]) return;  // a finite-volume element
-  split_body<N, NS, VF, MODE, GEN, FVM>(g, ph, e, true, threadIdx.x, U, G, out, R, ca, cb, dt, sA, sP, sD, slh);
+  split_body<N, NS, VF, GEN, FVM>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
 }
 
 // ----------------------------------------------------------------------------- ensemble batch
@@ -1771,12 +1838,10 @@ __global__ void __launch_bounds__(Sz<N>::NT * EPB, DG_LIFT_MINB) k_lift_b(BatchV
 }
 
 template <int N, bool NS, int VF, int EPB, bool GEN>
-__global__ void __launch_bounds__(SplitSz<N>::NT * EPB, DG_SPLIT_MINB) k_split_b(BatchView bv) {
+__global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N)) k_split_b(BatchView bv) {
   using L = SplitLds<N>;
-  constexpr int n = L::n, NT = SplitSz<N>::NT;
-  __shared__ double sA[EPB * L::A], sP[EPB * L::P];
-  __shared__ double sD[n * n], slh[2 * n];
-  split_tables<N>(bv.tab, threadIdx.x, NT * EPB, sD, slh);
+  constexpr int NT = SplitSz<N>::NT;
+  __shared__ double sm[EPB * L::A];
   const int nblk = (bv.total + EPB - 1) / EPB;
   const int blk = xcd_element(blockIdx.x, nblk);
   if (blk >= nblk) return;
@@ -1786,8 +1851,8 @@ __global__ void __launch_bounds__(SplitSz<N>::NT * EPB, DG_SPLIT_MINB) k_split_b
   const bool valid = item < bv.total;
   const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
   const Member &M = bv.m[mi];
-  split_body<N, NS, VF, 1, GEN>(M.g, M.ph, valid ? item - bv.first[mi] : 0, valid, t, M.U, M.G, M.out, M.R, M.a, M.b,
-                           M.dt, sA + slot * L::A, sP + slot * L::P, sD, slh);
+  split_body<N, NS, VF, GEN>(M.g, M.ph, bv.tab, valid ? item - bv.first[mi] : 0, valid, t, M.U, M.out, M.R, M.a, M.b,
+                             M.dt, 1, sm + slot * L::A);
 }
 
 // ----------------------------------------------------------------------------- reductions
@@ -2623,28 +2688,20 @@ static int launch_main_t(const Geo &g, const Phys &ph, const double *U, const do
 }
 
 template <int N, bool NS, int VF>
-static int launch_split_t(const Geo &g, const Phys &ph, const double *U, const double *G, double *out, double *R,
-                          double a, double b, double dt, int mode, hipStream_t st) {
+static int launch_split_t(const Geo &g, const Phys &ph, const double *U, double *out, double *R, double a, double b,
+                          double dt, int mode, hipStream_t st) {
   dim3 grid(xcd_grid(g.K)), block(SplitSz<N>::NT);
-  const bool gen = g.fc != nullptr;
   if constexpr (!NS) {
     if (g.fvflag) {
-      if (mode == 0)
-        hipLaunchKernelGGL((k_split<N, NS, VF, 0, 1, true>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt);
-      else
-        hipLaunchKernelGGL((k_split<N, NS, VF, 1, 1, true>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt);
+      hipLaunchKernelGGL((k_split<N, NS, VF, 1, true>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode);
       DG_CHECK_LAUNCH();
       return DG_OK;
     }
   }
   // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
-  const int lev = !gen ? 0 : (g.mslot ? 2 : 1);
-#define DG_KS(M_, G_) hipLaunchKernelGGL((k_split<N, NS, VF, M_, G_>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt)
-  if (mode == 0) {
-    if (lev == 0) DG_KS(0, 0); else if (lev == 1) DG_KS(0, 1); else DG_KS(0, 2);
-  } else {
-    if (lev == 0) DG_KS(1, 0); else if (lev == 1) DG_KS(1, 1); else DG_KS(1, 2);
-  }
+  const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
+#define DG_KS(G_) hipLaunchKernelGGL((k_split<N, NS, VF, G_>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode)
+  if (lev == 0) DG_KS(0); else if (lev == 1) DG_KS(1); else DG_KS(2);
 #undef DG_KS
   DG_CHECK_LAUNCH();
   return DG_OK;
@@ -2657,9 +2714,9 @@ static int launch_form(const Geo &g, const Phys &ph, int form, const double *U, 
   if (form == DG_FORM_STRONG) return launch_main_t<N, LGL, NS, 2>(g, ph, U, G, out, R, a, b, dt, mode, st);
   if (!LGL) return DG_ERR_UNSUPPORTED;
   if (form == DG_FORM_SPLIT) {
-    if (ph.vf == DG_VF_EC) return launch_split_t<N, NS, 1>(g, ph, U, G, out, R, a, b, dt, mode, st);
-    if (ph.vf == DG_VF_KEP) return launch_split_t<N, NS, 0>(g, ph, U, G, out, R, a, b, dt, mode, st);
-    return launch_split_t<N, NS, 2>(g, ph, U, G, out, R, a, b, dt, mode, st);
+    if (ph.vf == DG_VF_EC) return launch_split_t<N, NS, 1>(g, ph, U, out, R, a, b, dt, mode, st);
+    if (ph.vf == DG_VF_KEP) return launch_split_t<N, NS, 0>(g, ph, U, out, R, a, b, dt, mode, st);
+    return launch_split_t<N, NS, 2>(g, ph, U, out, R, a, b, dt, mode, st);
   }
   return DG_ERR_UNSUPPORTED;
 }
@@ -2945,9 +3002,10 @@ int launch_axpby(double *y, const double *x, double alpha, double beta, size_t n
 // workgroup of 512 lanes holds fused_epb elements of its group's degree in slots of the degree's
 // own lane count, and the static LDS is the largest degree's, carved per slot.  Lanes past the
 // last slot run the per-element code as invalid slots (no memory access, every barrier).
+constexpr int FUSED_SPLIT_LDS = 2 * SplitLds<7>::A;  // 152 KB: one workgroup per CU
 template <int N> constexpr int fused_epb_split() {
   constexpr int by_lanes = 512 / SplitSz<N>::NT;
-  constexpr int by_lds = (SplitLds<7>::A + SplitLds<7>::P) / (SplitLds<N>::A + SplitLds<N>::P);
+  constexpr int by_lds = FUSED_SPLIT_LDS / SplitLds<N>::A;
   return by_lanes < by_lds ? by_lanes : by_lds;
 }
 template <int N> constexpr int fused_epb_lift() {
@@ -2964,10 +3022,9 @@ __device__ __forceinline__ int fused_group(const FusedView &fv, int b) {
 }
 
 template <int N, bool NS, int VF>
-__device__ __forceinline__ void fused_split_group(const BatchView &bv, int blk, double *smem, double *sD, double *slh) {
+__device__ __forceinline__ void fused_split_group(const BatchView &bv, int blk, double *smem) {
   using L = SplitLds<N>;
   constexpr int NT = SplitSz<N>::NT, EPB = fused_epb_split<N>();
-  split_tables<N>(bv.tab, threadIdx.x, 512, sD, slh);
   const int raw = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int slot = raw < EPB ? raw : EPB - 1;
   const int t = threadIdx.x - raw * NT;
@@ -2975,27 +3032,26 @@ __device__ __forceinline__ void fused_split_group(const BatchView &bv, int blk, 
   const bool valid = raw < EPB && item < bv.total;
   const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
   const Member &M = bv.m[mi];
-  split_body<N, NS, VF, 1, false>(M.g, M.ph, valid ? item - bv.first[mi] : 0, valid, t, M.U, M.G, M.out, M.R, M.a,
-                                  M.b, M.dt, smem + slot * L::A, smem + EPB * L::A + slot * L::P, sD, slh);
+  split_body<N, NS, VF, 0>(M.g, M.ph, bv.tab, valid ? item - bv.first[mi] : 0, valid, t, M.U, M.out, M.R, M.a, M.b,
+                           M.dt, 1, smem + slot * L::A);
 }
 
 template <bool NS, int VF>
-__global__ void __launch_bounds__(512, DG_SPLIT_MINB) k_split_f(FusedView fv) {
-  __shared__ double smem[SplitLds<7>::A + SplitLds<7>::P];
-  __shared__ double sD[64], slh[16];
+__global__ void __launch_bounds__(512, 2) k_split_f(FusedView fv) {
+  __shared__ double smem[FUSED_SPLIT_LDS];
   const int nb = fv.start[fv.ng];
   const int b = xcd_element(blockIdx.x, nb);
   if (b >= nb) return;
   const int gi = fused_group(fv, b);
   const int lb = b - fv.start[gi];
   switch (fv.N[gi]) {
-    case 1: fused_split_group<1, NS, VF>(fv.v[gi], lb, smem, sD, slh); break;
-    case 2: fused_split_group<2, NS, VF>(fv.v[gi], lb, smem, sD, slh); break;
-    case 3: fused_split_group<3, NS, VF>(fv.v[gi], lb, smem, sD, slh); break;
-    case 4: fused_split_group<4, NS, VF>(fv.v[gi], lb, smem, sD, slh); break;
-    case 5: fused_split_group<5, NS, VF>(fv.v[gi], lb, smem, sD, slh); break;
-    case 6: fused_split_group<6, NS, VF>(fv.v[gi], lb, smem, sD, slh); break;
-    default: fused_split_group<7, NS, VF>(fv.v[gi], lb, smem, sD, slh); break;
+    case 1: fused_split_group<1, NS, VF>(fv.v[gi], lb, smem); break;
+    case 2: fused_split_group<2, NS, VF>(fv.v[gi], lb, smem); break;
+    case 3: fused_split_group<3, NS, VF>(fv.v[gi], lb, smem); break;
+    case 4: fused_split_group<4, NS, VF>(fv.v[gi], lb, smem); break;
+    case 5: fused_split_group<5, NS, VF>(fv.v[gi], lb, smem); break;
+    case 6: fused_split_group<6, NS, VF>(fv.v[gi], lb, smem); break;
+    default: fused_split_group<7, NS, VF>(fv.v[gi], lb, smem); break;
   }
 }
 
