@@ -110,8 +110,12 @@ dg::BatchView view(const dg_batch *b, const Group &g, const dg::Member *table) {
   v.total = g.total;
   v.tab = b->mem[g.idx[0]]->d_tab;
   v.general = 0;
-  for (int i : g.idx)
+  int affine = 0;
+  for (int i : g.idx) {
     if (b->mem[i]->d_fc) v.general = 1;
+    if (b->mem[i]->d_Jc) ++affine;
+  }
+  v.affine = affine == 0 ? dg::AFF_NONE : (affine == v.count ? dg::AFF_ALL : dg::AFF_MIXED);
   return v;
 }
 
@@ -127,6 +131,7 @@ std::vector<dg::Member> describe(const dg_batch *b, const double *const *U_in, d
       dg::Member d;
       std::memset(&d, 0, sizeof(d));
       d.g.Ja = h->d_Ja; d.g.sJ = h->d_sJ; d.g.fn = h->d_fn; d.g.nbr = h->d_nbr; d.g.fc = h->d_fc; d.g.tab = h->d_tab; d.g.K = h->K;
+      d.g.Jc = h->d_Jc;
       d.g.Gd = h->d_Gd; d.g.Gf = h->d_Gf;
       d.ph.gamma = h->ph.gamma; d.ph.R = h->ph.R; d.ph.mu = h->ph.mu; d.ph.Pr = h->ph.Pr;
       d.ph.kappa = h->ph.kappa; d.ph.vf = h->ph.vf; d.ph.rs = h->ph.rs;
@@ -199,7 +204,9 @@ int launch_stage_fused(dg_batch *b, const dg::Member *table, hipStream_t st) {
     const Group &g = b->groups[gi];
     fl.v[gi] = fs.v[gi] = view(b, g, table);
     fl.N[gi] = fs.N[gi] = g.N;
-    const int el = dg::fused_epb(g.N, true), es = dg::fused_epb(g.N, false);
+    // (a group with affine and other members: one element per workgroup)
+    const bool mixed = fl.v[gi].affine == dg::AFF_MIXED;
+    const int el = mixed ? 1 : dg::fused_epb(g.N, true), es = mixed ? 1 : dg::fused_epb(g.N, false);
     fl.start[gi + 1] = fl.start[gi] + (g.total + el - 1) / el;
     fs.start[gi + 1] = fs.start[gi] + (g.total + es - 1) / es;
   }

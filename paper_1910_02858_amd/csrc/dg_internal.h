@@ -41,6 +41,10 @@ struct MortarDesc {
   int es[4], ss[4], o[4], sl[4];   // small sides by position: element, side, orientation code, slot
 };
 
+// Constant metric terms of an affine element: Ja^i_d at i*3+d, 1/J at 9, and the outward scaled normal of
+// every side (the master's, negated on slaves) at 10 + 3*side + d.
+constexpr int AFFINE_DOUBLES = 28;
+
 // Device-resident geometry of one mesh.
 struct Geo {
   const double *Ja;   // [K][9][n3]: Ja^i_d at (i*3+d)
@@ -54,6 +58,9 @@ struct Geo {
   const uint8_t *fc;
   const Tab *tab;
   int K;
+  // [K][AFFINE_DOUBLES] where every element of the mesh is affine (its nodes lie on an affine map of the
+  // reference cube to the rounding of the coordinates), else NULL
+  const double *Jc;
   // non-conforming faces (NULL without): slot of every side [K][6] (-1 for conforming sides), and
   // per slot the side's outward numerical flux times the surface element minus the BR1 viscous
   // mean, mflux[slot][5][n^2], its lifting surface term W* s n_d, mlift[slot][d*4+c][n^2], and the
@@ -164,7 +171,9 @@ struct BatchView {
   int count, total;
   const Tab *tab;
   int general;  // some member's mesh has face codes (Geo::fc): launch the kernels that read them
+  int affine;   // AFF_NONE, AFF_ALL or AFF_MIXED: no, every or some member's elements are affine (Geo::Jc)
 };
+enum { AFF_NONE = 0, AFF_ALL = 1, AFF_MIXED = 2 };
 
 // elements per workgroup the batched kernels are built for (1, 2, 4 up to this bound)
 __host__ __device__ constexpr int batch_max_epb(int N) { return N <= 3 ? 4 : (N <= 5 ? 2 : 1); }
@@ -255,6 +264,7 @@ struct dg_handle {
   hipStream_t stream = nullptr;
   // device memory owned by the handle
   double *d_Ja = nullptr, *d_sJ = nullptr, *d_fn = nullptr;
+  double *d_Jc = nullptr;       // affine elements' constants [K][AFFINE_DOUBLES], NULL if some element is not affine
   int32_t *d_nbr = nullptr;
   uint8_t *d_fc = nullptr;      // face codes [K][6], only on meshes that are not structured
   int nm = 0;                   // non-conforming faces (mortars)
@@ -296,6 +306,7 @@ struct dg_handle {
   dg::Geo geo() const {
     dg::Geo g;
     g.Ja = d_Ja; g.sJ = d_sJ; g.fn = d_fn; g.nbr = d_nbr; g.fc = d_fc; g.tab = d_tab; g.K = K;
+    g.Jc = d_Jc;
     g.mslot = d_mslot; g.mflux = d_mflux; g.mlift = d_mlift; g.mg = d_mg;
     g.fvflag = fv_on ? d_fvflag : nullptr; g.fvFx = fv_on ? d_fvFx : nullptr;
     g.Gd = d_Gd; g.Gf = d_Gf;

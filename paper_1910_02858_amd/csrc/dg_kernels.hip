@@ -364,8 +364,17 @@ template <int n> __device__ __forceinline__ int div_slot(int i, int j, int k) {
   else return i + n * (j + n * k);
 }
 
+// Constant metric terms of an affine element (Geo::Jc) through the scalar cache.
+typedef const __attribute__((address_space(4))) double *AffineConst;
+__device__ __forceinline__ AffineConst affine_const(const Geo &g, int e) {
+  return (AffineConst)(g.Jc + (size_t)__builtin_amdgcn_readfirstlane(e) * AFFINE_DOUBLES);
+}
+
 // sm: the slot's LiftLds<N> regions, contiguous (W, JA, WS).
-template <int N, bool LGL, int OUT, int GEN>
+// AFF: every element is affine; the metric terms are the element's constants (Geo::Jc).  The gradient is
+// then Ja^dir_d times the reference derivative: 4 LDS reads and 4 fused multiply-adds per line node instead
+// of 7 and 15, and 10 of the 20 doubles read per node (Ja, 1/J) stay out of memory traffic.
+template <int N, bool LGL, int OUT, int GEN, bool AFF>
 __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, bool valid, int t,
                                           const double *__restrict__ U, double *__restrict__ G,
                                           double *__restrict__ Fv, double *sm, const double *sDh,
@@ -381,7 +390,10 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
   // node's 1/J are loaded one phase ahead
   constexpr int JPT = (3 * n3 + NT - 1) / NT;
   double jn[JPT], sjn = 0.0;
-  {
+  AffineConst jc = nullptr;
+  if constexpr (AFF) {
+    jc = affine_const(g, e);
+  } else {
     const double *Jd = g.Ja + (size_t)e * 9 * n3;
 #pragma unroll
     for (int r = 0; r < JPT; ++r) jn[r] = (valid && t + r * NT < 3 * n3) ? Jd[t + r * NT] : 0.0;
@@ -501,6 +513,50 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
   const int i = t % n, j = (t / n) % n, k = t / n2;
   double jo[9];  // this node's metric terms, kept for the viscous fluxes
   double gd[4] = {0.0, 0.0, 0.0, 0.0};  // the viscous divergence (LIFT_DIV, LIFT_DIVK)
+  if constexpr (AFF) {
+    __syncthreads();  // W and the face means are complete
+    if (valid && t < n3) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) jo[c] = jc[c];
+#pragma unroll
+      for (int dir = 0; dir < 3; ++dir) {
+        const int id = dir == 0 ? i : (dir == 1 ? j : k);
+        const int str = dir == 0 ? 1 : (dir == 1 ? n : n2);
+        const int base = t - id * str;
+        const int a = dir == 0 ? j : i, b = dir == 2 ? j : k, ab = a + n * b;
+        double dw[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int m = 0; m < n; ++m) {
+          const int qm = base + m * str;
+          const double Dh = sDh[id * n + m];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) dw[v] = fma(Dh, sW[v * n3 + qm], dw[v]);
+        }
+        // surface: +-lhat(+-1) W*, the normal times s-hat being +-Ja^dir on both faces of the direction
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+          const int s = 2 * dir + sd;
+          if (LGL && id != (sd ? N : 0)) continue;
+          const double lh = slh[(sd ? n : 0) + id];
+          if (GEN == 2 && is_mortar(g, e, s)) {
+            // non-conforming face: W* s n_d (outward) from the mortar face array
+            const double *ml = g.mlift + (size_t)g.mslot[(size_t)e * 6 + s] * 12 * n2 + ab;
+#pragma unroll
+            for (int c = 0; c < 12; ++c) acc[c] += lh * ml[c * n2];
+          } else {
+            const double sl_ = sd ? lh : -lh;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dw[v] = fma(sl_, sWs[(s * 4 + v) * n2 + ab], dw[v]);
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[d * 4 + v] = fma(jo[dir * 3 + d], dw[v], acc[d * 4 + v]);
+      }
+    }
+    sjn = jc[9];
+  } else {
 #pragma unroll
   for (int dir = 0; dir < 3; ++dir) {
     __syncthreads();
@@ -559,7 +615,8 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
       }
     }
   }
-  if (!LGL && valid && t < n3) {
+  }
+  if (!LGL && !AFF && valid && t < n3) {
     // surface: lhat(+-1) [W* nt_d] on each side
     for (int s = 0; s < 6; ++s) {
       const int dn = s >> 1;
@@ -686,8 +743,9 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
 #pragma unroll
         for (int c = 0; c < 5; ++c) Uq[c] = ut[c * n2];
       }
-      const double *fnp = g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
-      const double nt[3] = {fnp[0], fnp[n2], fnp[2 * n2]};
+      const double *fnp = AFF ? g.Jc + (size_t)e * AFFINE_DOUBLES + 10 + 3 * s : g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
+      const int fst = AFF ? 1 : n2;
+      const double nt[3] = {fnp[0], fnp[fst], fnp[2 * fst]};
       double Fo[5];
       flux_v(to_prim(Uq, gm1), gq, ph, nt, Fo);
       const NbFace f = nbr_face<n, (GEN > 0)>(g, e, s, a, b);
@@ -879,7 +937,7 @@ template <bool LGL, int OUT, int GEN> constexpr int lift_minb() {
   return (LGL || GEN == 0) ? DG_LIFT_MINB : 2;
 }
 
-template <int N, bool LGL, int OUT, int GEN>
+template <int N, bool LGL, int OUT, int GEN, bool AFF>
 __global__ void __launch_bounds__(Sz<N>::NT, (lift_minb<LGL, OUT, GEN>()))
     k_lift(Geo g, Phys ph, const double *__restrict__ U, double *__restrict__ G, double *__restrict__ Fv) {
   using L = LiftLds<N>;
@@ -889,7 +947,7 @@ __global__ void __launch_bounds__(Sz<N>::NT, (lift_minb<LGL, OUT, GEN>()))
   lift_tables<N>(g.tab, threadIdx.x, Sz<N>::NT, sDh, sl, slh);
   const int e = xcd_element(blockIdx.x, g.K);
   if (e >= g.K) return;
-  lift_body<N, LGL, OUT, GEN>(g, ph, e, true, threadIdx.x, U, G, Fv, sm, sDh, sl, slh);
+  lift_body<N, LGL, OUT, GEN, AFF>(g, ph, e, true, threadIdx.x, U, G, Fv, sm, sDh, sl, slh);
 }
 
 // ----------------------------------------------------------------------------- operator
@@ -909,10 +967,10 @@ template <int N, bool LGL, bool NS, int FORM, int GEN> constexpr int main_minb()
 // FORM: 0 weak, 1 split, 2 strong.  MODE: 0 write U_t, 1 fused RK stage.  GEN: face codes.
 // FVM: hybrid DG/FV mesh (Euler): finite-volume elements are left to k_fv_volume, and the sides
 // that meet one take their flux from Geo::fvFx.
-template <int N, bool LGL, bool NS, int FORM, int MODE, int GEN, bool FVM = false>
+template <int N, bool LGL, bool NS, int FORM, int GEN, bool FVM, bool AFF>
 __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()))
     k_main(Geo g, Phys ph, const double *__restrict__ U, const double *__restrict__ G, double *__restrict__ out,
-           double *__restrict__ R, double ca, double cb, double dt) {
+           double *__restrict__ R, double ca, double cb, double dt, int mode) {
   using S = Sz<N>;
   constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = S::NT;
   constexpr int NX = (FORM == 1) ? 8 : 5;
@@ -933,9 +991,12 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
   __shared__ double sX[NX * n3];
   __shared__ double sF[6 * 5 * n2];
   __shared__ double sD[n * n], sl[2 * n], slh[2 * n];
-  const int e = blockIdx.x;
+  const int e = xcd_element(blockIdx.x, g.K);
   const int t = threadIdx.x;
+  if (e >= g.K) return;
   if (FVM && g.fvflag[e]) return;  // a finite-volume element
+  AffineConst jc = nullptr;
+  if constexpr (AFF) jc = affine_const(g, e);
   const double gm1 = ph.gamma - 1.0;
   const Tab *tb = g.tab;
   // strong form on LG nodes: the derivative matrix carries the interior flux's interpolation
@@ -1023,8 +1084,8 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
           }
         }
       } else {
-        // a rolled loop: unrolled, the early loads of all n nodes' values spill
-#pragma unroll 1
+        // two nodes' loads in flight: all n nodes' early loads spill
+#pragma unroll 2
         for (int m = 0; m < n; ++m) {
           const int q = line_node<n>(dn, a, b, m), qn = GEN ? line_node<n>(f.dn, f.a, f.b, m) : q;
 #pragma unroll
@@ -1038,10 +1099,11 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
     }
     // the master's normal and state go first (fn holds the outward normal, the master's
     // negated on the slave side)
-    const double *fnp = g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
+    const double *fnp = AFF ? g.Jc + (size_t)e * AFFINE_DOUBLES + 10 + 3 * s : g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
+    const int fst = AFF ? 1 : n2;
     const bool mst = GEN ? f.master : plus;
     const double sg = mst ? 1.0 : -1.0;
-    const double nt[3] = {sg * fnp[0], sg * fnp[n2], sg * fnp[2 * n2]};
+    const double nt[3] = {sg * fnp[0], sg * fnp[fst], sg * fnp[2 * fst]};
     const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
     const double ish = 1.0 / sh;
     const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
@@ -1168,8 +1230,12 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
     double Fint[5], nv[3];
     __syncthreads();
     if (t < n3) {
-      const double *Jd = g.Ja + ((size_t)e * 9 + dir * 3) * n3 + t;
-      nv[0] = Jd[0]; nv[1] = Jd[n3]; nv[2] = Jd[2 * n3];
+      if constexpr (AFF) {
+        nv[0] = jc[3 * dir]; nv[1] = jc[3 * dir + 1]; nv[2] = jc[3 * dir + 2];
+      } else {
+        const double *Jd = g.Ja + ((size_t)e * 9 + dir * 3) * n3 + t;
+        nv[0] = Jd[0]; nv[1] = Jd[n3]; nv[2] = Jd[2 * n3];
+      }
       double Fc[5], Fv[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
       double Un[5];
 #pragma unroll
@@ -1241,8 +1307,8 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[1 + c] -= g.Gd[((size_t)e * 4 + c) * n3 + t];
     }
-    const double sj = g.sJ[(size_t)e * n3 + t];
-    if (MODE == 0) {
+    const double sj = AFF ? jc[9] : g.sJ[(size_t)e * n3 + t];
+    if (mode == 0) {
       double *Oe = out + (size_t)e * 5 * n3;
 #pragma unroll
       for (int v = 0; v < 5; ++v) Oe[v * n3 + t] = -acc[v] * sj;
@@ -1418,11 +1484,12 @@ template <int n> struct LineSlots {
 };
 
 // LDS sizes (doubles) of one element in the split-form kernel: the conservative state (5 per node), the
-// two-point state rho, u, v, w, beta|H (5 per node) and the metric terms Ja^i_d (9 per node); the
-// accumulated result takes the place of the metric terms once every line has read them.
+// two-point state rho, u, v, w, beta|H (5 per node) and the metric terms Ja^i_d (9 per node; none on
+// affine elements); the accumulated result takes the place of the metric terms (affine: of the two-point
+// state) once every line has read them.
 template <int N> struct SplitLds {
   static constexpr int n = N + 1, n2 = n * n, n3 = n2 * n;
-  static constexpr int A = 19 * n3;
+  static constexpr int A = 19 * n3, AFFINE = 10 * n3;
 };
 
 // Lanes of one element in the split-form kernel: one per line of the three directions, 3 n^2 of them.
@@ -1446,9 +1513,11 @@ struct LineNode {  // a node of a line: its two-point state and the line directi
 // per lane has no exchange, no redundant half round (28 pairs for 8 nodes, not 32) and five barriers per
 // element, at 2 waves per SIMD.
 // valid = false keeps the slot's lanes in step with the workgroup barriers without touching memory.
+// AFF: every element is affine, its metric terms and 1/J are the element's constants (Geo::Jc): 10 of the
+// 43 doubles per node are not read, and 41 KB of LDS at N = 7 instead of 78 fit three workgroups per CU.
 // mode 0 writes U_t, 1 the fused RK stage.  FVM: the sides that meet a finite-volume element take their
 // flux from Geo::fvFx.
-template <int N, bool NS, int VF, int GEN, bool FVM = false>
+template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
 __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const Tab *tab, int e, bool valid, int lane,
                                            const double *__restrict__ U, double *__restrict__ out,
                                            double *__restrict__ R, double ca, double cb, double dt, int mode,
@@ -1460,7 +1529,9 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
   const double *Ue = U + (size_t)e * 5 * n3;
   const double *Jae = g.Ja + (size_t)e * 9 * n3;
   double *sU = sm, *sS = sm + 5 * n3, *sJ = sm + 10 * n3;  // node slots: div_slot
-  double *sAcc = sJ;
+  double *sAcc = AFF ? sS : sJ;
+  AffineConst jc = nullptr;
+  if constexpr (AFF) jc = affine_const(g, e);
   // the 1D tables through the scalar cache
   const __attribute__((address_space(4))) double *D = (const __attribute__((address_space(4))) double *)tab->D;
   const double lh0 = tab->lhm[0], lhN = tab->lhp[N];
@@ -1492,7 +1563,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int t = lane + it * NT;
-    if (valid && t < n3) {
+    if (!AFF && valid && t < n3) {
 #pragma unroll
       for (int c = 0; c < 9; ++c) Jq[it][c] = Jae[c * n3 + t];
     }
@@ -1552,14 +1623,24 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       // beta = rho / (2 p) for EC, the total enthalpy otherwise
       sS[4 * n3 + q] = (VF == 1) ? 0.5 * P.rho / P.p : (Uq[it][4] + P.p) / P.rho;
 #pragma unroll
-      for (int c = 0; c < 9; ++c) sJ[c * n3 + q] = Jq[it][c];
+      for (int c = 0; c < 9 && !AFF; ++c) sJ[c * n3 + q] = Jq[it][c];
     }
   }
   __syncthreads();
   double acc[n][5];
   if (act) {
     const LineSlots<n> slot(dir, a, b);
+    // the line direction's metric terms at a node
     const double *sJd = sJ + 3 * dir * n3;
+    double jl[3] = {0.0, 0.0, 0.0};
+    if constexpr (AFF) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) jl[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
+    }
+    auto metric = [&](int d, int q) -> double {
+      if constexpr (AFF) return jl[d];
+      else return sJd[d * n3 + q];
+    };
     // numerical surface fluxes at the line's ends, lifted (outward times lhat), and the interior
     // convective part: 2 D_ii F(U_i) (D_ii is non-zero only at the ends of LGL lines) -+ lhat F_int
     double fe[2][5];
@@ -1573,7 +1654,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       for (int v = 0; v < 5; ++v) Uw[v] = sU[v * n3 + qo];
       // normal along +xi scaled by s-hat: Ja^dir at the face node, the master's on the master side and
       // (up to rounding, the metric terms being continuous across the face) on the slave
-      const double nt[3] = {sJd[qo], sJd[n3 + qo], sJd[2 * n3 + qo]};
+      const double nt[3] = {metric(0, qo), metric(1, qo), metric(2, qo)};
       const Pr5 Pw = {Uw[0], sS[n3 + qo], sS[2 * n3 + qo], sS[3 * n3 + qo],
                       gm1 * (Uw[4] - 0.5 * (Uw[1] * sS[n3 + qo] + Uw[2] * sS[2 * n3 + qo] + Uw[3] * sS[3 * n3 + qo]))};
       flux_c(Uw, Pw, nt, Fo);
@@ -1668,7 +1749,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
         const int q = slot(m);
         x.s = load_ps<VF>(sS, n3, q, gg);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) x.nv[d] = sJd[d * n3 + q];
+        for (int d = 0; d < 3; ++d) x.nv[d] = metric(d, q);
         return x;
       };
       LineNode A = node(0), B = node(1), An = B, Bn = B;
@@ -1702,14 +1783,14 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       for (int i = 0; i < n; ++i) {
         const int qi = slot(i);
         const PS A = load_ps<VF>(sS, n3, qi, gg);
-        const double na[3] = {sJd[qi], sJd[n3 + qi], sJd[2 * n3 + qi]};
+        const double na[3] = {metric(0, qi), metric(1, qi), metric(2, qi)};
 #pragma unroll
         for (int sft = 1; sft <= n / 2; ++sft) {
           if (2 * sft == n && 2 * i >= n) continue;  // met from the other end
           const int j = i + sft < n ? i + sft : i + sft - n;
           const int qj = slot(j);
           const PS B = load_ps<VF>(sS, n3, qj, gg);
-          const double nS[3] = {na[0] + sJd[qj], na[1] + sJd[n3 + qj], na[2] + sJd[2 * n3 + qj]};
+          const double nS[3] = {na[0] + metric(0, qj), na[1] + metric(1, qj), na[2] + metric(2, qj)};
           double F[5];
           pair2<VF>(A, B, nS, kg, F);
           const double Dij = D[i * n + j], Dji = D[j * n + i];
@@ -1735,7 +1816,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
   for (int it = 0; it < IT; ++it) {
     const int t = lane + it * NT;
     if (valid && t < n3) {
-      sjq[it] = g.sJ[(size_t)e * n3 + t];
+      sjq[it] = AFF ? jc[9] : g.sJ[(size_t)e * n3 + t];
       if (NS) {
         // viscous part in strong form, formed by the lifting kernel
 #pragma unroll
@@ -1791,15 +1872,15 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
   }
 }
 
-template <int N, bool NS, int VF, int GEN, bool FVM = false>
+template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
 __global__ void __launch_bounds__(SplitSz<N>::NT, split_minb(N)) k_split(Geo g, Phys ph, const double *__restrict__ U,
                                                      double *__restrict__ out, double *__restrict__ R, double ca,
                                                      double cb, double dt, int mode) {
-  __shared__ double sm[SplitLds<N>::A];
+  __shared__ double sm[AFF ? SplitLds<N>::AFFINE : SplitLds<N>::A];
   const int e = xcd_element(blockIdx.x, g.K);
   if (e >= g.K) return;
   if (FVM && g.fvflag[e]) return;  // a finite-volume element
-  split_body<N, NS, VF, GEN, FVM>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
+  split_body<N, NS, VF, GEN, FVM, AFF>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
 }
 
 // ----------------------------------------------------------------------------- ensemble batch
@@ -1807,6 +1888,8 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, split_minb(N)) k_split(Geo g, 
 // degree; EPB elements share a workgroup (one slot of Sz<N>::NT threads each, SplitSz<N>::NT in
 // the split-form kernel, wave aligned).
 // Each slot finds its member by bisection of the element prefix sums.
+// AFF: AFF_NONE, AFF_ALL (every member's elements are affine) or AFF_MIXED, which takes each member's own
+// path, so that a member's result has the bits of its one-mesh launch whatever its neighbours in the batch.
 __device__ __forceinline__ int member_of(const int *first, int count, int item) {
   int lo = 0, hi = count - 1;
   while (lo < hi) {
@@ -1817,7 +1900,7 @@ __device__ __forceinline__ int member_of(const int *first, int count, int item) 
   return lo;
 }
 
-template <int N, int EPB, bool GEN>
+template <int N, int EPB, bool GEN, int AFF>
 __global__ void __launch_bounds__(Sz<N>::NT * EPB, DG_LIFT_MINB) k_lift_b(BatchView bv) {
   using L = LiftLds<N>;
   constexpr int n = L::n, NT = Sz<N>::NT, SM = L::W + L::JA + L::WS;
@@ -1833,15 +1916,17 @@ __global__ void __launch_bounds__(Sz<N>::NT * EPB, DG_LIFT_MINB) k_lift_b(BatchV
   const bool valid = item < bv.total;
   const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
   const Member &M = bv.m[mi];
-  lift_body<N, true, LIFT_DIV, GEN>(M.g, M.ph, valid ? item - bv.first[mi] : 0, valid, t, M.U, nullptr, nullptr,
-                                    sm + slot * SM, sDh, sl, slh);
+  const int e = valid ? item - bv.first[mi] : 0;
+  if (AFF == AFF_ALL || (AFF == AFF_MIXED && M.g.Jc))
+    lift_body<N, true, LIFT_DIV, GEN, true>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm + slot * SM, sDh, sl, slh);
+  else
+    lift_body<N, true, LIFT_DIV, GEN, false>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm + slot * SM, sDh, sl, slh);
 }
 
-template <int N, bool NS, int VF, int EPB, bool GEN>
+template <int N, bool NS, int VF, int EPB, bool GEN, int AFF>
 __global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N)) k_split_b(BatchView bv) {
-  using L = SplitLds<N>;
-  constexpr int NT = SplitSz<N>::NT;
-  __shared__ double sm[EPB * L::A];
+  constexpr int NT = SplitSz<N>::NT, L = AFF == AFF_ALL ? SplitLds<N>::AFFINE : SplitLds<N>::A;
+  __shared__ double sm[EPB * L];
   const int nblk = (bv.total + EPB - 1) / EPB;
   const int blk = xcd_element(blockIdx.x, nblk);
   if (blk >= nblk) return;
@@ -1851,8 +1936,11 @@ __global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N)) k_split_b
   const bool valid = item < bv.total;
   const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
   const Member &M = bv.m[mi];
-  split_body<N, NS, VF, GEN>(M.g, M.ph, bv.tab, valid ? item - bv.first[mi] : 0, valid, t, M.U, M.out, M.R, M.a, M.b,
-                             M.dt, 1, sm + slot * L::A);
+  const int e = valid ? item - bv.first[mi] : 0;
+  if (AFF == AFF_ALL || (AFF == AFF_MIXED && M.g.Jc))
+    split_body<N, NS, VF, GEN, false, true>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
+  else
+    split_body<N, NS, VF, GEN, false, false>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
 }
 
 // ----------------------------------------------------------------------------- reductions
@@ -2659,29 +2747,27 @@ __global__ void __launch_bounds__(Sz<N>::NT) k_fv_switch(Geo g, Phys ph, FvGeo f
     if (_e != hipSuccess) return DG_ERR_HIP;                \
   } while (0)
 
+// The kernels that take an element's metric terms as constants (AFF) run on meshes whose every element is
+// affine (Geo::Jc is set up by dg_init exactly there); any other mesh reads them per node.
 template <int N, bool LGL, bool NS, int FORM>
 static int launch_main_t(const Geo &g, const Phys &ph, const double *U, const double *G, double *out, double *R,
                          double a, double b, double dt, int mode, hipStream_t st) {
-  dim3 grid(g.K), block(Sz<N>::NT);
-  const bool gen = g.fc != nullptr;
+  dim3 grid(xcd_grid(g.K)), block(Sz<N>::NT);
+#define DG_KM(G_, F_) \
+  do { \
+    if (g.Jc) hipLaunchKernelGGL((k_main<N, LGL, NS, FORM, G_, F_, true>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt, mode); \
+    else hipLaunchKernelGGL((k_main<N, LGL, NS, FORM, G_, F_, false>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt, mode); \
+  } while (0)
   if constexpr (!NS) {
     if (g.fvflag) {
-      if (mode == 0)
-        hipLaunchKernelGGL((k_main<N, LGL, NS, FORM, 0, 1, true>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt);
-      else
-        hipLaunchKernelGGL((k_main<N, LGL, NS, FORM, 1, 1, true>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt);
+      DG_KM(1, true);
       DG_CHECK_LAUNCH();
       return DG_OK;
     }
   }
   // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
-  const int lev = !gen ? 0 : (g.mslot ? 2 : 1);
-#define DG_KM(M_, G_) hipLaunchKernelGGL((k_main<N, LGL, NS, FORM, M_, G_>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt)
-  if (mode == 0) {
-    if (lev == 0) DG_KM(0, 0); else if (lev == 1) DG_KM(0, 1); else DG_KM(0, 2);
-  } else {
-    if (lev == 0) DG_KM(1, 0); else if (lev == 1) DG_KM(1, 1); else DG_KM(1, 2);
-  }
+  const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
+  if (lev == 0) DG_KM(0, false); else if (lev == 1) DG_KM(1, false); else DG_KM(2, false);
 #undef DG_KM
   DG_CHECK_LAUNCH();
   return DG_OK;
@@ -2691,17 +2777,21 @@ template <int N, bool NS, int VF>
 static int launch_split_t(const Geo &g, const Phys &ph, const double *U, double *out, double *R, double a, double b,
                           double dt, int mode, hipStream_t st) {
   dim3 grid(xcd_grid(g.K)), block(SplitSz<N>::NT);
+#define DG_KS(G_, F_) \
+  do { \
+    if (g.Jc) hipLaunchKernelGGL((k_split<N, NS, VF, G_, F_, true>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode); \
+    else hipLaunchKernelGGL((k_split<N, NS, VF, G_, F_, false>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode); \
+  } while (0)
   if constexpr (!NS) {
     if (g.fvflag) {
-      hipLaunchKernelGGL((k_split<N, NS, VF, 1, true>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode);
+      DG_KS(1, true);
       DG_CHECK_LAUNCH();
       return DG_OK;
     }
   }
   // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
   const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
-#define DG_KS(G_) hipLaunchKernelGGL((k_split<N, NS, VF, G_>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode)
-  if (lev == 0) DG_KS(0); else if (lev == 1) DG_KS(1); else DG_KS(2);
+  if (lev == 0) DG_KS(0, false); else if (lev == 1) DG_KS(1, false); else DG_KS(2, false);
 #undef DG_KS
   DG_CHECK_LAUNCH();
   return DG_OK;
@@ -2734,26 +2824,28 @@ int launch_lift(const Geo &g, const Phys &ph, bool lgl, int out, const double *U
   dim3 grid(xcd_grid(g.K)), block(Sz<N>::NT);
   // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
   const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
+#define DG_KLG(L_, O_, G_) \
+  do { \
+    if (g.Jc) hipLaunchKernelGGL((k_lift<N, L_, O_, G_, true>), grid, block, 0, st, g, ph, U, G, Fv); \
+    else hipLaunchKernelGGL((k_lift<N, L_, O_, G_, false>), grid, block, 0, st, g, ph, U, G, Fv); \
+  } while (0)
 #define DG_KL(L_, O_) \
   do { \
-    if (lev == 0) hipLaunchKernelGGL((k_lift<N, L_, O_, 0>), grid, block, 0, st, g, ph, U, G, Fv); \
-    else if (lev == 1) hipLaunchKernelGGL((k_lift<N, L_, O_, 1>), grid, block, 0, st, g, ph, U, G, Fv); \
-    else hipLaunchKernelGGL((k_lift<N, L_, O_, 2>), grid, block, 0, st, g, ph, U, G, Fv); \
+    if (lev == 0) DG_KLG(L_, O_, 0); \
+    else if (lev == 1) DG_KLG(L_, O_, 1); \
+    else DG_KLG(L_, O_, 2); \
   } while (0)
   if (out == LIFT_SV) {
     // the strong-form operator of conforming meshes on LG nodes
     if (lev == 2 || lgl) return DG_ERR_UNSUPPORTED;
-    if (lev == 0) hipLaunchKernelGGL((k_lift<N, false, LIFT_SV, 0>), grid, block, 0, st, g, ph, U, G, Fv);
-    else hipLaunchKernelGGL((k_lift<N, false, LIFT_SV, 1>), grid, block, 0, st, g, ph, U, G, Fv);
+    if (lev == 0) DG_KLG(false, LIFT_SV, 0); else DG_KLG(false, LIFT_SV, 1);
   } else if (out == LIFT_WV) {
     // the weak-form operator of conforming meshes
     if (lev == 2) return DG_ERR_UNSUPPORTED;
     if (lgl) {
-      if (lev == 0) hipLaunchKernelGGL((k_lift<N, true, LIFT_WV, 0>), grid, block, 0, st, g, ph, U, G, Fv);
-      else hipLaunchKernelGGL((k_lift<N, true, LIFT_WV, 1>), grid, block, 0, st, g, ph, U, G, Fv);
+      if (lev == 0) DG_KLG(true, LIFT_WV, 0); else DG_KLG(true, LIFT_WV, 1);
     } else {
-      if (lev == 0) hipLaunchKernelGGL((k_lift<N, false, LIFT_WV, 0>), grid, block, 0, st, g, ph, U, G, Fv);
-      else hipLaunchKernelGGL((k_lift<N, false, LIFT_WV, 1>), grid, block, 0, st, g, ph, U, G, Fv);
+      if (lev == 0) DG_KLG(false, LIFT_WV, 0); else DG_KLG(false, LIFT_WV, 1);
     }
   } else if (!lgl) {
     if (out == LIFT_G) DG_KL(false, LIFT_G);
@@ -2770,6 +2862,7 @@ int launch_lift(const Geo &g, const Phys &ph, bool lgl, int out, const double *U
   } else {
     return DG_ERR_UNSUPPORTED;
   }
+#undef DG_KLG
 #undef DG_KL
   DG_CHECK_LAUNCH();
   return DG_OK;
@@ -2787,45 +2880,52 @@ int launch_main(const Geo &g, const Phys &ph, bool lgl, int eqn, int form, const
   return launch_form<N, false, false>(g, ph, form, U, G, out, R, a, b, dt, mode, st);
 }
 
-template <int N, int EPB>
+template <int N, int EPB, int AFF>
 static int launch_batch_lift_t(const BatchView &bv, hipStream_t st) {
-  const int nblk = (bv.total + EPB - 1) / EPB;
-  if (bv.general)
-    hipLaunchKernelGGL((k_lift_b<N, EPB, true>), dim3(xcd_grid(nblk)), dim3(Sz<N>::NT * EPB), 0, st, bv);
-  else
-    hipLaunchKernelGGL((k_lift_b<N, EPB, false>), dim3(xcd_grid(nblk)), dim3(Sz<N>::NT * EPB), 0, st, bv);
+  const dim3 grid(xcd_grid((bv.total + EPB - 1) / EPB)), block(Sz<N>::NT * EPB);
+  if (bv.general) hipLaunchKernelGGL((k_lift_b<N, EPB, true, AFF>), grid, block, 0, st, bv);
+  else hipLaunchKernelGGL((k_lift_b<N, EPB, false, AFF>), grid, block, 0, st, bv);
   DG_CHECK_LAUNCH();
   return DG_OK;
 }
 
-template <int N, bool NS, int VF, int EPB>
+// a group with affine and other members runs one element per workgroup, whatever the tile choice: the two
+// paths pass different numbers of workgroup barriers, so the slots of one workgroup may not differ
+template <int N, int EPB> static int launch_batch_lift_a(const BatchView &bv, hipStream_t st) {
+  if (bv.affine == AFF_MIXED) return launch_batch_lift_t<N, 1, AFF_MIXED>(bv, st);
+  return bv.affine == AFF_ALL ? launch_batch_lift_t<N, EPB, AFF_ALL>(bv, st) : launch_batch_lift_t<N, EPB, AFF_NONE>(bv, st);
+}
+
+template <int N, bool NS, int VF, int EPB, int AFF>
 static int launch_batch_split_t(const BatchView &bv, hipStream_t st) {
-  const int nblk = (bv.total + EPB - 1) / EPB;
-  if (bv.general)
-    hipLaunchKernelGGL((k_split_b<N, NS, VF, EPB, true>), dim3(xcd_grid(nblk)), dim3(SplitSz<N>::NT * EPB), 0, st,
-                       bv);
-  else
-    hipLaunchKernelGGL((k_split_b<N, NS, VF, EPB, false>), dim3(xcd_grid(nblk)), dim3(SplitSz<N>::NT * EPB), 0, st,
-                       bv);
+  const dim3 grid(xcd_grid((bv.total + EPB - 1) / EPB)), block(SplitSz<N>::NT * EPB);
+  if (bv.general) hipLaunchKernelGGL((k_split_b<N, NS, VF, EPB, true, AFF>), grid, block, 0, st, bv);
+  else hipLaunchKernelGGL((k_split_b<N, NS, VF, EPB, false, AFF>), grid, block, 0, st, bv);
   DG_CHECK_LAUNCH();
   return DG_OK;
+}
+
+template <int N, bool NS, int VF, int EPB> static int launch_batch_split_a(const BatchView &bv, hipStream_t st) {
+  if (bv.affine == AFF_MIXED) return launch_batch_split_t<N, NS, VF, 1, AFF_MIXED>(bv, st);
+  return bv.affine == AFF_ALL ? launch_batch_split_t<N, NS, VF, EPB, AFF_ALL>(bv, st)
+                              : launch_batch_split_t<N, NS, VF, EPB, AFF_NONE>(bv, st);
 }
 
 template <int N, bool NS, int EPB>
 static int launch_batch_split_vf(const BatchView &bv, int vf, hipStream_t st) {
-  if (vf == DG_VF_EC) return launch_batch_split_t<N, NS, 1, EPB>(bv, st);
-  if (vf == DG_VF_KEP) return launch_batch_split_t<N, NS, 0, EPB>(bv, st);
-  return launch_batch_split_t<N, NS, 2, EPB>(bv, st);
+  if (vf == DG_VF_EC) return launch_batch_split_a<N, NS, 1, EPB>(bv, st);
+  if (vf == DG_VF_KEP) return launch_batch_split_a<N, NS, 0, EPB>(bv, st);
+  return launch_batch_split_a<N, NS, 2, EPB>(bv, st);
 }
 
 template <int N>
 int launch_batch_lift(const BatchView &bv, int epb, hipStream_t st) {
   if (bv.total <= 0) return DG_OK;
-  if (epb == 1) return launch_batch_lift_t<N, 1>(bv, st);
+  if (epb == 1) return launch_batch_lift_a<N, 1>(bv, st);
   if constexpr (batch_max_epb(N) >= 2)
-    if (epb == 2) return launch_batch_lift_t<N, 2>(bv, st);
+    if (epb == 2) return launch_batch_lift_a<N, 2>(bv, st);
   if constexpr (batch_max_epb(N) >= 4)
-    if (epb == 4) return launch_batch_lift_t<N, 4>(bv, st);
+    if (epb == 4) return launch_batch_lift_a<N, 4>(bv, st);
   return DG_ERR_UNSUPPORTED;
 }
 
@@ -3021,19 +3121,32 @@ __device__ __forceinline__ int fused_group(const FusedView &fv, int b) {
   return gi;
 }
 
+// elements of group bv per workgroup: one where affine and other members mix (the two paths pass different
+// numbers of workgroup barriers, so every slot of a workgroup takes the path of its first element's member)
+__device__ __forceinline__ int fused_slots(const BatchView &bv, int epb) { return bv.affine == AFF_MIXED ? 1 : epb; }
+__device__ __forceinline__ bool fused_affine(const BatchView &bv, int first_item) {
+  if (bv.affine != AFF_MIXED) return bv.affine == AFF_ALL;
+  return bv.m[member_of(bv.first, bv.count, first_item)].g.Jc != nullptr;
+}
+
 template <int N, bool NS, int VF>
 __device__ __forceinline__ void fused_split_group(const BatchView &bv, int blk, double *smem) {
   using L = SplitLds<N>;
   constexpr int NT = SplitSz<N>::NT, EPB = fused_epb_split<N>();
+  const int epb = fused_slots(bv, EPB);
   const int raw = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int slot = raw < EPB ? raw : EPB - 1;
   const int t = threadIdx.x - raw * NT;
-  const int item = blk * EPB + slot;
-  const bool valid = raw < EPB && item < bv.total;
+  const int item = blk * epb + slot;
+  const bool valid = raw < epb && item < bv.total;
   const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
   const Member &M = bv.m[mi];
-  split_body<N, NS, VF, 0>(M.g, M.ph, bv.tab, valid ? item - bv.first[mi] : 0, valid, t, M.U, M.out, M.R, M.a, M.b,
-                           M.dt, 1, smem + slot * L::A);
+  const int e = valid ? item - bv.first[mi] : 0;
+  double *sm = smem + slot * L::A;
+  if (fused_affine(bv, blk * epb))
+    split_body<N, NS, VF, 0, false, true>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
+  else
+    split_body<N, NS, VF, 0, false, false>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
 }
 
 template <bool NS, int VF>
@@ -3061,15 +3174,20 @@ __device__ __forceinline__ void fused_lift_group(const BatchView &bv, int blk, d
   using L = LiftLds<N>;
   constexpr int NT = Sz<N>::NT, EPB = fused_epb_lift<N>();
   lift_tables<N>(bv.tab, threadIdx.x, 512, sDh, sl, slh);
+  const int epb = fused_slots(bv, EPB);
   const int raw = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int slot = raw < EPB ? raw : EPB - 1;
   const int t = threadIdx.x - raw * NT;
-  const int item = blk * EPB + slot;
-  const bool valid = raw < EPB && item < bv.total;
+  const int item = blk * epb + slot;
+  const bool valid = raw < epb && item < bv.total;
   const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
   const Member &M = bv.m[mi];
-  lift_body<N, true, LIFT_DIV, false>(M.g, M.ph, valid ? item - bv.first[mi] : 0, valid, t, M.U, nullptr, nullptr,
-                                      smem + slot * (L::W + L::JA + L::WS), sDh, sl, slh);
+  const int e = valid ? item - bv.first[mi] : 0;
+  double *sm = smem + slot * (L::W + L::JA + L::WS);
+  if (fused_affine(bv, blk * epb))
+    lift_body<N, true, LIFT_DIV, 0, true>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm, sDh, sl, slh);
+  else
+    lift_body<N, true, LIFT_DIV, 0, false>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm, sDh, sl, slh);
 }
 
 __global__ void __launch_bounds__(512, DG_LIFT_MINB) k_lift_f(FusedView fv) {
