@@ -2090,77 +2090,136 @@ template <int n> __device__ __forceinline__ void sub_point(int o, int a, int b, 
   b2 = (o & 2) ? n - 1 - q : q;
 }
 
-// interpolation (proj = false) or projection (proj = true) matrices of sub-face p of a mortar of
-// type t along the big side's two face directions, from sM = [IL | IU | PL | PU]; nullptr where
-// the face is not cut in that direction
-template <int n>
-__device__ __forceinline__ void sub_ops(const double *sM, int t, int p, bool proj, const double *&M1,
-                                        const double *&M2) {
-  const int p1 = t == 1 ? p : (t == 3 ? (p & 1) : -1);
-  const int p2 = t == 2 ? p : (t == 3 ? (p >> 1) : -1);
-  const double *base = sM + (proj ? 2 * n * n : 0);
-  M1 = p1 < 0 ? nullptr : base + p1 * n * n;
-  M2 = p2 < 0 ? nullptr : base + p2 * n * n;
-}
-__device__ __forceinline__ double mcoef(const double *M, int n, int r, int c) {
-  return M ? M[r * n + c] : (r == c ? 1.0 : 0.0);
-}
+// Lanes of one mortar's workgroup: one per point of up to four small sides.
+template <int N> struct MortarSz {
+  static constexpr int n2 = (N + 1) * (N + 1), NT = (4 * n2 + 63) / 64 * 64;
+};
 
-// sum over the big side's points (m, l) of M1[r1][m] M2[r2][l] X[v][m + n l], v < NV
+// A mortar's big side is cut into na parts along its first face direction and nb along its second; small
+// side pos = p1 + na p2.  Interpolation to the small sides and projection back are applied one face
+// direction at a time (n products a value instead of n^2), all components of all points spread over the
+// lanes: a mesh has few such faces, so the chain of one workgroup's steps is what the kernels wait on.  One
+// rolled n^2 sum per point and lane (64 lanes for the projection) took 72 us (fluxes) and 64 us (lifting) a
+// launch for 128 faces at N = 7; now 11 and 10 us.
+// sM = [IL | IU | PL | PU].
+
+// first direction of the interpolation: T[(p1 NV + v) n^2 + i + n l] = sum_m I_p1[i][m] X[v][m + n l]
 template <int n, int NV>
-__device__ __forceinline__ void sub_apply(const double *M1, const double *M2, int r1, int r2, const double *X,
-                                          double *out) {
+__device__ __forceinline__ void mortar_interp_a(const double *sM, int type, int na, const double *X, double *T, int t,
+                                                int nth) {
   constexpr int n2 = n * n;
+  for (int q = t; q < na * NV * n2; q += nth) {
+    const int p1 = q / (NV * n2), r = q - p1 * NV * n2, pt = r % n2, i = pt % n, l = pt / n;
+    if (type & 1) {
+      const double *M = sM + p1 * n2 + i * n, *x = X + (r - pt) + n * l;
+      double s = 0.0;
+#pragma unroll
+      for (int m = 0; m < n; ++m) s += M[m] * x[m];
+      T[q] = s;
+    } else {
+      T[q] = X[r];
+    }
+  }
+}
+// second direction, at the sub-face point (a2, b2) of small side pos: out[v], v < NV
+template <int n, int NV>
+__device__ __forceinline__ void mortar_interp_b(const double *sM, int type, int na, int pos, int a2, int b2,
+                                                const double *T, double *out) {
+  constexpr int n2 = n * n;
+  const int p1 = pos % na, p2 = pos / na;
+  const double *x = T + p1 * NV * n2 + a2, *M = sM + p2 * n2 + b2 * n;
 #pragma unroll
   for (int v = 0; v < NV; ++v) out[v] = 0.0;
-#pragma unroll 1
-  for (int l = 0; l < n; ++l) {
-    const double c2 = mcoef(M2, n, r2, l);
-    if (c2 == 0.0) continue;
-#pragma unroll 1
-    for (int m = 0; m < n; ++m) {
-      const double c1 = mcoef(M1, n, r1, m);
-      if (c1 == 0.0) continue;
+  if (type & 2) {
+#pragma unroll 4
+    for (int l = 0; l < n; ++l) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) out[v] += c1 * (c2 * X[v * n2 + m + n * l]);
+      for (int v = 0; v < NV; ++v) out[v] += M[l] * x[v * n2 + n * l];
     }
+  } else {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[v] = x[v * n2 + n * b2];
+  }
+}
+// projection of the small sides' NC values X[(pos NC + c) n^2 + a2 + n b2] onto the big side, negated
+// (outward of the big element), into out[c n^2 + i + n j]; Y: 2 NC n^2 doubles of scratch
+template <int n, int NC>
+__device__ __forceinline__ void mortar_project(const double *sM, int type, int na, int nb, const double *X, double *Y,
+                                               double *__restrict__ out, int t, int nth) {
+  constexpr int n2 = n * n;
+  for (int q = t; q < nb * NC * n2; q += nth) {
+    const int p2 = q / (NC * n2), r = q - p2 * NC * n2, pt = r % n2, i = pt % n, l = pt / n;
+    double s = 0.0;
+    if (type & 1) {
+#pragma unroll
+      for (int p1 = 0; p1 < 2; ++p1) {
+        const double *M = sM + (2 + p1) * n2 + i * n, *x = X + (p1 + 2 * p2) * NC * n2 + (r - pt) + n * l;
+#pragma unroll
+        for (int m = 0; m < n; ++m) s += M[m] * x[m];
+      }
+    } else {
+      s = X[p2 * NC * n2 + r];
+    }
+    Y[q] = s;
+  }
+  __syncthreads();
+  for (int q = t; q < NC * n2; q += nth) {
+    const int pt = q % n2, i = pt % n, j = pt / n;
+    double s = 0.0;
+    if (type & 2) {
+#pragma unroll
+      for (int p2 = 0; p2 < 2; ++p2) {
+        const double *M = sM + (2 + p2) * n2 + j * n, *y = Y + p2 * NC * n2 + (q - pt) + i;
+#pragma unroll
+        for (int l = 0; l < n; ++l) s += M[l] * y[n * l];
+      }
+    } else {
+      s = Y[q];
+    }
+    out[q] = -s;
   }
 }
 
 template <int N, bool LGL>
-__global__ void __launch_bounds__(256) k_mortar_lift(Geo g, Phys ph, const MortarDesc *__restrict__ md,
-                                                     const double *__restrict__ U) {
-  constexpr int n = N + 1, n2 = n * n;
-  __shared__ double sM[4 * n * n];    // IL, IU, PL, PU
+__global__ void __launch_bounds__(MortarSz<N>::NT) k_mortar_lift(Geo g, Phys ph, const MortarDesc *__restrict__ md,
+                                                                 const double *__restrict__ U) {
+  constexpr int n = N + 1, n2 = n * n, NT = MortarSz<N>::NT;
+  __shared__ double sM[4 * n2];       // IL, IU, PL, PU
   __shared__ double sWB[4 * n2];      // W = (u, v, w, T) of the big side's trace
+  __shared__ double sTa[2 * 12 * n2]; // interpolated along the first direction; then the projection's scratch
   __shared__ double sT[4 * 12 * n2];  // the small sides' surface terms at their sub-face points
-  const int t = threadIdx.x, nth = blockDim.x;
+  const int t = threadIdx.x;
   const Tab *tb = g.tab;
-  for (int c = t; c < n * n; c += nth) {
-    sM[c] = tb->IL[c]; sM[n * n + c] = tb->IU[c]; sM[2 * n * n + c] = tb->PL[c]; sM[3 * n * n + c] = tb->PU[c];
-  }
   const MortarDesc &m = md[blockIdx.x];  // read in place: its arrays are indexed by sub-face
+  const int type = m.type, na = (type & 1) ? 2 : 1, nb = (type & 2) ? 2 : 1, cnt = na * nb;
   const double gm1 = ph.gamma - 1.0;
-  for (int p = t; p < n2; p += nth) {
-    double W[4];
-    face_trace_W<n, LGL>(U, m.eb, m.sb, p % n, p / n, tb->lm, tb->lp, gm1, ph.R, W);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sWB[v * n2 + p] = W[v];
-  }
-  __syncthreads();
-  const int cnt = m.type == 3 ? 4 : 2;
-  for (int q = t; q < cnt * n2; q += nth) {
-    const int pos = q / n2, ab = q - pos * n2, a = ab % n, b = ab / n;
-    const int es = m.es[pos], ss = m.ss[pos];
-    int a2, b2;
-    sub_point<n>(m.o[pos], a, b, a2, b2);
-    const double *A1, *A2;
-    sub_ops<n>(sM, m.type, pos, false, A1, A2);
-    double WB[4], Ws[4];
-    sub_apply<n, 4>(A1, A2, a2, b2, sWB, WB);
+  // this lane's point of a small side: its trace and normal are loaded before the first barrier
+  const bool act = t < cnt * n2;
+  const int pos = act ? t / n2 : 0, ab = t - pos * n2, a = ab % n, b = ab / n;
+  const int es = m.es[pos], ss = m.ss[pos];
+  double Ws[4], nt[3];
+  if (act) {
     face_trace_W<n, LGL>(U, es, ss, a, b, tb->lm, tb->lp, gm1, ph.R, Ws);
     const double *fnp = g.fn + ((size_t)es * 6 + ss) * 3 * n2 + ab;
-    const double nt[3] = {fnp[0], fnp[n2], fnp[2 * n2]};
+    nt[0] = fnp[0]; nt[1] = fnp[n2]; nt[2] = fnp[2 * n2];
+  }
+  for (int c = t; c < n2; c += NT) {
+    sM[c] = tb->IL[c]; sM[n2 + c] = tb->IU[c]; sM[2 * n2 + c] = tb->PL[c]; sM[3 * n2 + c] = tb->PU[c];
+  }
+  if (t < n2) {
+    double W[4];
+    face_trace_W<n, LGL>(U, m.eb, m.sb, t % n, t / n, tb->lm, tb->lp, gm1, ph.R, W);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sWB[v * n2 + t] = W[v];
+  }
+  __syncthreads();
+  mortar_interp_a<n, 4>(sM, type, na, sWB, sTa, t, NT);
+  __syncthreads();
+  if (act) {
+    int a2, b2;
+    sub_point<n>(m.o[pos], a, b, a2, b2);
+    double WB[4];
+    mortar_interp_b<n, 4>(sM, type, na, pos, a2, b2, sTa, WB);
     double *ml = g.mlift + (size_t)m.sl[pos] * 12 * n2 + ab;
 #pragma unroll
     for (int d = 0; d < 3; ++d)
@@ -2172,104 +2231,84 @@ __global__ void __launch_bounds__(256) k_mortar_lift(Geo g, Phys ph, const Morta
       }
   }
   __syncthreads();
-  for (int q = t; q < n2; q += nth) {
-    const int i = q % n, j = q / n;
-    double acc[12];
-#pragma unroll
-    for (int c = 0; c < 12; ++c) acc[c] = 0.0;
-    for (int pos = 0; pos < cnt; ++pos) {
-      const double *B1, *B2;
-      sub_ops<n>(sM, m.type, pos, true, B1, B2);
-#pragma unroll 1
-      for (int b2 = 0; b2 < n; ++b2) {
-        const double c2 = mcoef(B2, n, j, b2);
-        if (c2 == 0.0) continue;
-#pragma unroll 1
-        for (int a2 = 0; a2 < n; ++a2) {
-          const double c = mcoef(B1, n, i, a2) * c2;
-          if (c == 0.0) continue;
-#pragma unroll
-          for (int k = 0; k < 12; ++k) acc[k] -= c * sT[(pos * 12 + k) * n2 + a2 + n * b2];
-        }
-      }
-    }
-    double *ml = g.mlift + (size_t)m.slot * 12 * n2 + q;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) ml[c * n2] = acc[c];
-  }
+  mortar_project<n, 12>(sM, type, na, nb, sT, sTa, g.mlift + (size_t)m.slot * 12 * n2, t, NT);
 }
 
 // G: the lifted gradients [K][12][n^3] (read on LG nodes); on LGL nodes the gradients at the
 // mortar sides' points come from Geo::mg, written by the lifting kernel
 template <int N, bool LGL, bool NS>
-__global__ void __launch_bounds__(256) k_mortar_flux(Geo g, Phys ph, const MortarDesc *__restrict__ md,
-                                                     const double *__restrict__ U, const double *__restrict__ G) {
-  constexpr int n = N + 1, n2 = n * n;
-  __shared__ double sM[4 * n * n];
-  __shared__ double sUB[5 * n2];
-  __shared__ double sGB[NS ? 12 * n2 : 1];
-  __shared__ double sF[4 * 5 * n2];  // the small sides' fluxes at their sub-face points
-  const int t = threadIdx.x, nth = blockDim.x;
+__global__ void __launch_bounds__(MortarSz<N>::NT) k_mortar_flux(Geo g, Phys ph, const MortarDesc *__restrict__ md,
+                                                                 const double *__restrict__ U,
+                                                                 const double *__restrict__ G) {
+  constexpr int n = N + 1, n2 = n * n, NT = MortarSz<N>::NT, NV = NS ? 17 : 5;
+  __shared__ double sM[4 * n2];
+  __shared__ double sB[NV * n2];       // the big side's trace: U (5), for Navier-Stokes the gradients (12)
+  __shared__ double sTa[2 * NV * n2];  // interpolated along the first direction; then the projection's scratch
+  __shared__ double sF[4 * 5 * n2];    // the small sides' fluxes at their sub-face points
+  const int t = threadIdx.x;
   const Tab *tb = g.tab;
-  for (int c = t; c < n * n; c += nth) {
-    sM[c] = tb->IL[c]; sM[n * n + c] = tb->IU[c]; sM[2 * n * n + c] = tb->PL[c]; sM[3 * n * n + c] = tb->PU[c];
-  }
   const MortarDesc &m = md[blockIdx.x];  // read in place: its arrays are indexed by sub-face
+  const int type = m.type, na = (type & 1) ? 2 : 1, nb = (type & 2) ? 2 : 1, cnt = na * nb;
   const double gm1 = ph.gamma - 1.0;
-  for (int p = t; p < n2; p += nth) {
-    double Uq[5];
-    face_trace<n, LGL, 5>(U, m.eb, m.sb, p % n, p / n, tb->lm, tb->lp, Uq);
+  // this lane's point of a small side, the master of its part of the face: its own trace and normal are
+  // loaded before the first barrier
+  const bool act = t < cnt * n2;
+  const int pos = act ? t / n2 : 0, ab = t - pos * n2, a = ab % n, b = ab / n;
+  const int es = m.es[pos], ss = m.ss[pos];
+  double UM[5], gM[12], nt[3];
+  if (act) {
+    face_trace<n, LGL, 5>(U, es, ss, a, b, tb->lm, tb->lp, UM);
+    if (NS && LGL) {
+      const double *mg = g.mg + (size_t)m.sl[pos] * 12 * n2 + ab;
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sUB[v * n2 + p] = Uq[v];
+      for (int c = 0; c < 12; ++c) gM[c] = mg[c * n2];
+    } else if (NS) {
+      face_trace<n, false, 12>(G, es, ss, a, b, tb->lm, tb->lp, gM);
+    }
+    const double *fnp = g.fn + ((size_t)es * 6 + ss) * 3 * n2 + ab;
+    nt[0] = fnp[0]; nt[1] = fnp[n2]; nt[2] = fnp[2 * n2];
+  }
+  for (int c = t; c < n2; c += NT) {
+    sM[c] = tb->IL[c]; sM[n2 + c] = tb->IU[c]; sM[2 * n2 + c] = tb->PL[c]; sM[3 * n2 + c] = tb->PU[c];
+  }
+  if (t < n2) {
+    double Uq[5];
+    face_trace<n, LGL, 5>(U, m.eb, m.sb, t % n, t / n, tb->lm, tb->lp, Uq);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) sB[v * n2 + t] = Uq[v];
     if (NS) {
       double gq[12];
       if (LGL) {
-        const double *mg = g.mg + (size_t)m.slot * 12 * n2 + p;
+        const double *mg = g.mg + (size_t)m.slot * 12 * n2 + t;
 #pragma unroll
         for (int c = 0; c < 12; ++c) gq[c] = mg[c * n2];
       } else {
-        face_trace<n, false, 12>(G, m.eb, m.sb, p % n, p / n, tb->lm, tb->lp, gq);
+        face_trace<n, false, 12>(G, m.eb, m.sb, t % n, t / n, tb->lm, tb->lp, gq);
       }
 #pragma unroll
-      for (int c = 0; c < 12; ++c) sGB[c * n2 + p] = gq[c];
+      for (int c = 0; c < 12; ++c) sB[(5 + c) * n2 + t] = gq[c];
     }
   }
   __syncthreads();
-  const int cnt = m.type == 3 ? 4 : 2;
-  for (int q = t; q < cnt * n2; q += nth) {
-    const int pos = q / n2, ab = q - pos * n2, a = ab % n, b = ab / n;
-    const int es = m.es[pos], ss = m.ss[pos];
+  mortar_interp_a<n, NV>(sM, type, na, sB, sTa, t, NT);
+  __syncthreads();
+  if (act) {
     int a2, b2;
     sub_point<n>(m.o[pos], a, b, a2, b2);
-    const double *A1, *A2;
-    sub_ops<n>(sM, m.type, pos, false, A1, A2);
-    // the small side is the master of its part of the face: its own normal, its state first
-    double UM[5], US[5];
-    face_trace<n, LGL, 5>(U, es, ss, a, b, tb->lm, tb->lp, UM);
-    sub_apply<n, 5>(A1, A2, a2, b2, sUB, US);
-    const double *fnp = g.fn + ((size_t)es * 6 + ss) * 3 * n2 + ab;
-    const double nt[3] = {fnp[0], fnp[n2], fnp[2 * n2]};
+    double XS[NV];  // the big side's state (and gradients) at this point
+    mortar_interp_b<n, NV>(sM, type, na, pos, a2, b2, sTa, XS);
     const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
     const double ish = 1.0 / sh;
     const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
     double F[5];
-    riemann(ph, UM, US, nh, F);
+    riemann(ph, UM, XS, nh, F);
 #pragma unroll
     for (int v = 0; v < 5; ++v) F[v] *= sh;
-    if (NS) {
+    if constexpr (NS) {
       // BR1: mean of the two sides' viscous fluxes, the big side's state and gradients interpolated
-      double gM[12], gS[12], FvM[5], FvS[5];
-      if (LGL) {
-        const double *mg = g.mg + (size_t)m.sl[pos] * 12 * n2 + ab;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) gM[c] = mg[c * n2];
-      } else {
-        face_trace<n, false, 12>(G, es, ss, a, b, tb->lm, tb->lp, gM);
-      }
-      sub_apply<n, 12>(A1, A2, a2, b2, sGB, gS);
-      const Pr5 PM = to_prim(UM, gm1), PS = to_prim(US, gm1);
-      flux_v(PM, gM, ph, nt, FvM);
-      flux_v(PS, gS, ph, nt, FvS);
+      double FvM[5], FvS[5];
+      flux_v(to_prim(UM, gm1), gM, ph, nt, FvM);
+      flux_v(to_prim(XS, gm1), XS + 5, ph, nt, FvS);
 #pragma unroll
       for (int v = 0; v < 5; ++v) F[v] -= 0.5 * (FvM[v] + FvS[v]);
     }
@@ -2281,29 +2320,7 @@ __global__ void __launch_bounds__(256) k_mortar_flux(Geo g, Phys ph, const Morta
     }
   }
   __syncthreads();
-  for (int q = t; q < n2; q += nth) {
-    const int i = q % n, j = q / n;
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int pos = 0; pos < cnt; ++pos) {
-      const double *B1, *B2;
-      sub_ops<n>(sM, m.type, pos, true, B1, B2);
-#pragma unroll 1
-      for (int b2 = 0; b2 < n; ++b2) {
-        const double c2 = mcoef(B2, n, j, b2);
-        if (c2 == 0.0) continue;
-#pragma unroll 1
-        for (int a2 = 0; a2 < n; ++a2) {
-          const double c = mcoef(B1, n, i, a2) * c2;
-          if (c == 0.0) continue;
-#pragma unroll
-          for (int v = 0; v < 5; ++v) acc[v] -= c * sF[(pos * 5 + v) * n2 + a2 + n * b2];
-        }
-      }
-    }
-    double *mf = g.mflux + (size_t)m.slot * 5 * n2 + q;
-#pragma unroll
-    for (int v = 0; v < 5; ++v) mf[v * n2] = acc[v];
-  }
+  mortar_project<n, 5>(sM, type, na, nb, sF, sTa, g.mflux + (size_t)m.slot * 5 * n2, t, NT);
 }
 
 // ----------------------------------------------------------------------------- FV subcells
@@ -2990,8 +3007,8 @@ template <int N>
 int launch_mortar_lift(const Geo &g, const Phys &ph, bool lgl, const MortarDesc *md, int nm, const double *U,
                        hipStream_t st) {
   if (nm <= 0) return DG_OK;
-  if (lgl) hipLaunchKernelGGL((k_mortar_lift<N, true>), dim3(nm), dim3(256), 0, st, g, ph, md, U);
-  else hipLaunchKernelGGL((k_mortar_lift<N, false>), dim3(nm), dim3(256), 0, st, g, ph, md, U);
+  if (lgl) hipLaunchKernelGGL((k_mortar_lift<N, true>), dim3(nm), dim3(MortarSz<N>::NT), 0, st, g, ph, md, U);
+  else hipLaunchKernelGGL((k_mortar_lift<N, false>), dim3(nm), dim3(MortarSz<N>::NT), 0, st, g, ph, md, U);
   DG_CHECK_LAUNCH();
   return DG_OK;
 }
@@ -3001,10 +3018,10 @@ int launch_mortar_flux(const Geo &g, const Phys &ph, bool lgl, int eqn, const Mo
                        const double *U, const double *G, hipStream_t st) {
   if (nm <= 0) return DG_OK;
   const bool ns = eqn == DG_NAVIER_STOKES;
-  if (lgl && ns) hipLaunchKernelGGL((k_mortar_flux<N, true, true>), dim3(nm), dim3(256), 0, st, g, ph, md, U, G);
-  else if (lgl) hipLaunchKernelGGL((k_mortar_flux<N, true, false>), dim3(nm), dim3(256), 0, st, g, ph, md, U, G);
-  else if (ns) hipLaunchKernelGGL((k_mortar_flux<N, false, true>), dim3(nm), dim3(256), 0, st, g, ph, md, U, G);
-  else hipLaunchKernelGGL((k_mortar_flux<N, false, false>), dim3(nm), dim3(256), 0, st, g, ph, md, U, G);
+  if (lgl && ns) hipLaunchKernelGGL((k_mortar_flux<N, true, true>), dim3(nm), dim3(MortarSz<N>::NT), 0, st, g, ph, md, U, G);
+  else if (lgl) hipLaunchKernelGGL((k_mortar_flux<N, true, false>), dim3(nm), dim3(MortarSz<N>::NT), 0, st, g, ph, md, U, G);
+  else if (ns) hipLaunchKernelGGL((k_mortar_flux<N, false, true>), dim3(nm), dim3(MortarSz<N>::NT), 0, st, g, ph, md, U, G);
+  else hipLaunchKernelGGL((k_mortar_flux<N, false, false>), dim3(nm), dim3(MortarSz<N>::NT), 0, st, g, ph, md, U, G);
   DG_CHECK_LAUNCH();
   return DG_OK;
 }
