@@ -777,19 +777,19 @@ int reduce_dispatch(dg_handle *h, int what, const double *U) {
   int rc;
   switch (h->N) {
 #define DG_CASE(NN) \
-  case NN: rc = dg::launch_reduce<NN>(g, h->ph, what, U, 0.0, h->d_partial, h->stream); break;
+  case NN: rc = dg::launch_reduce<NN>(g, h->ph, what, U, h->d_partial, h->stream); break;
     DG_CASE(1) DG_CASE(2) DG_CASE(3) DG_CASE(4) DG_CASE(5) DG_CASE(6) DG_CASE(7) DG_CASE(8)
 #undef DG_CASE
     default: return DG_ERR_UNSUPPORTED;
   }
   if (rc) return rc;
-  return dg::launch_final_reduce(what, h->d_partial, h->K, h->d_red, h->stream);
+  return dg::launch_final_reduce(what, h->d_partial, dg::reduce_rows(h->K, h->n3), h->h_red, h->stream);
 }
 
+// the last kernel has written the result to pinned host memory: no copy, only the wait
 int fetch_red(dg_handle *h, double *out8) {
-  if (hipMemcpyAsync(out8, h->d_red, 8 * sizeof(double), hipMemcpyDeviceToHost, h->stream) != hipSuccess)
-    return fail(h, DG_ERR_HIP, "copy of a reduction result failed");
   if (hipStreamSynchronize(h->stream) != hipSuccess) return fail(h, DG_ERR_HIP, "stream synchronisation failed");
+  std::memcpy(out8, h->h_red, 8 * sizeof(double));
   return DG_OK;
 }
 
@@ -946,7 +946,11 @@ int dg_init(const dg_mesh *mesh, int N, int node_type, const dg_scheme *sc, void
     if (!rc) rc = dev_alloc(&h->d_Gtr, (size_t)K * 72 * n2);
   }
   if (!rc) rc = dev_alloc(&h->d_partial, (size_t)K * 8);
-  if (!rc) rc = dev_alloc(&h->d_red, 8);
+  if (!rc && hipHostMalloc((void **)&h->h_red, 8 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+    h->h_red = nullptr;
+    (void)hipGetLastError();
+    rc = DG_ERR_OOM;
+  }
   if (!rc && h->nm) {
     int slots = 0;
     for (const dg::MortarDesc &d : md) slots += 1 + (d.type == 3 ? 4 : 2);
@@ -1494,7 +1498,8 @@ void dg_destroy(dg_handle *h) {
   (void)hipFree(h->d_Ja); (void)hipFree(h->d_sJ); (void)hipFree(h->d_fn); (void)hipFree(h->d_nbr);
   (void)hipFree(h->d_fc); (void)hipFree(h->d_tab); (void)hipFree(h->d_Jc);
   (void)hipFree(h->d_G); (void)hipFree(h->d_Gd); (void)hipFree(h->d_Gf); (void)hipFree(h->d_Utr);
-  (void)hipFree(h->d_Wtr); (void)hipFree(h->d_Gtr); (void)hipFree(h->d_Pf); (void)hipFree(h->d_partial); (void)hipFree(h->d_red);
+  (void)hipFree(h->d_Wtr); (void)hipFree(h->d_Gtr); (void)hipFree(h->d_Pf); (void)hipFree(h->d_partial);
+  if (h->h_red) (void)hipHostFree(h->h_red);
   (void)hipFree(h->d_md); (void)hipFree(h->d_mslot); (void)hipFree(h->d_mflux); (void)hipFree(h->d_mlift);
   (void)hipFree(h->d_mg);
   (void)hipFree(h->d_fvtab); (void)hipFree(h->d_fvJbar); (void)hipFree(h->d_fvNf); (void)hipFree(h->d_fvFx);

@@ -130,8 +130,7 @@ int launch_vjp(const Geo &g, const Phys &ph, int eqn, int form, bool lgl, const 
                const double *Ubar_t, double *Ubar, double scale, int accumulate, double *Rb, double ra, double rb,
                hipStream_t st);
 template <int N>
-int launch_reduce(const Geo &g, const Phys &ph, int what, const double *U, double cfl_unused, double *partial,
-                  hipStream_t st);
+int launch_reduce(const Geo &g, const Phys &ph, int what, const double *U, double *partial, hipStream_t st);
 // hybrid DG/FV (Euler): face fluxes of faces touching FV elements, the FV elements' operator with
 // the optional fused RK stage (mode as launch_main), and the indicator with switching in place
 template <int N>
@@ -246,7 +245,13 @@ int launch_batch_split(const BatchView &bv, bool ns, int vf, int epb, hipStream_
 // what codes for launch_reduce
 enum { RED_TIMESTEP = 0, RED_INTEGRALS = 1, RED_FINITE = 2 };
 
-int launch_final_reduce(int what, const double *partial, int K, double *out, hipStream_t st);
+// rows of partial results (at most 8 doubles each) that launch_reduce leaves for a mesh of K elements of n3
+// nodes: eight workgroups of 256 lanes per CU, never more than one per element (callers' scratch holds 8 K)
+inline int reduce_rows(int K, int n3) {
+  const long long full = ((long long)K * n3 + 255) / 256;
+  return (int)(full < K ? (full < 2048 ? full : 2048) : (K < 2048 ? K : 2048));
+}
+int launch_final_reduce(int what, const double *partial, int rows, double *out, hipStream_t st);
 // Static scratch of the entry points that allocate nothing (dg_static.hip): doubles per GPU, and
 // the once-per-device lookup of its device address, called by dg_init with that device current.
 #define DG_NOALLOC_SCRATCH_DOUBLES (1 << 20)
@@ -291,8 +296,8 @@ struct dg_handle {
   dg::Tab *d_tab = nullptr;
   double *d_G = nullptr;        // lifted gradients [K][12][n3] (Navier-Stokes)
   double *d_Pf = nullptr;       // face terms of the transposed lifting [K][6][4][n^2] (first VJP)
-  double *d_partial = nullptr;  // [K][8] per-element partial reductions
-  double *d_red = nullptr;      // [8] reduction result
+  double *d_partial = nullptr;  // [K][8] partial reductions
+  double *h_red = nullptr;      // [8] reduction result, in pinned host memory the kernels write to
   dg::Tab tab{};
   // optional per-kernel timing with HIP events (dg_profile)
   bool prof = false;

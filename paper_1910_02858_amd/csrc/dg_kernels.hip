@@ -6,8 +6,8 @@
 //               flux differencing eq. semiDiscreteSplit), numerical surface flux (Riemann + BR1
 //               viscous mean), surface integral, -1/J scaling, and optionally the 2N-storage
 //               Runge-Kutta update of Sec. 4.4 fused into the epilogue.
-//   k_reduce .. per-element partial sums for the time step (eqs. CFLCondition, DFLCondition),
-//               quadrature integrals and the finiteness check, then one final pass.
+//   k_reduce .. partial results for the time step (eqs. CFLCondition, DFLCondition), quadrature
+//               integrals and the finiteness check, then one final pass.
 //
 // Layout: U[e][v][k][j][i] (i fastest), Ja[e][i*3+d][node], 1/J[e][node],
 // outward normals fn[e][side][d][a + n*b].  Each workgroup stages its element's state in
@@ -1944,77 +1944,96 @@ __global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N)) k_split_b
 }
 
 // ----------------------------------------------------------------------------- reductions
-// partial[e][0..7]: timestep -> {max sum lambda_c, max sum lambda_v};
-// integrals -> {rho, m1, m2, m3, E, KE, entropy, min J}; finite -> {count of non-finite}
-template <int N>
-__global__ void __launch_bounds__(Sz<N>::NT) k_reduce(Geo g, Phys ph, int what, const double *__restrict__ U,
-                                                      double *__restrict__ partial) {
-  using S = Sz<N>;
-  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = S::NT;
-  __shared__ double red[8][NT];
-  const int e = blockIdx.x, t = threadIdx.x;
-  const double gm1 = ph.gamma - 1.0;
-  double val[8];
-  const bool isMin[8] = {false, false, false, false, false, false, false, true};
+// WHAT RED_TIMESTEP -> {max sum lambda_c, max sum lambda_v}; RED_INTEGRALS -> {rho, m1, m2, m3, E, KE,
+// entropy, min J}; RED_FINITE -> {count of non-finite}
+template <int WHAT> struct Red {
+  static constexpr int NC = WHAT == RED_TIMESTEP ? 2 : (WHAT == RED_INTEGRALS ? 8 : 1);
+  static __device__ __forceinline__ double init(int c) { return WHAT == RED_INTEGRALS && c == 7 ? 1e300 : 0.0; }
+  static __device__ __forceinline__ double join(int c, double x, double y) {
+    if (WHAT == RED_TIMESTEP) return fmax(x, y);
+    if (WHAT == RED_INTEGRALS && c == 7) return fmin(x, y);
+    return x + y;
+  }
+  // every lane's val joined over the workgroup of NT lanes (a fixed butterfly per wave, then the waves in
+  // order); the result in lane 0.  sm: NC NT / 64 doubles.
+  template <int NT> static __device__ __forceinline__ void workgroup(double *val, double *sm) {
 #pragma unroll
-  for (int c = 0; c < 8; ++c) val[c] = 0.0;
-  if (what == RED_INTEGRALS) val[7] = 1e300;
-  if (t < n3) {
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) val[c] = join(c, val[c], __shfl_xor(val[c], off, 64));
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) sm[w * NC + c] = val[c];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int v = 1; v < NT / 64; ++v)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) val[c] = join(c, val[c], sm[v * NC + c]);
+    }
+  }
+};
+
+// A fixed number of workgroups walk the nodes of the whole mesh and leave one row of partial results each.
+// One workgroup per element, its eight components folded through LDS, took 17 us for 885 k nodes (N = 5,
+// 42 MB of state) and left 4096 rows to the last kernel, 12 us more; now 6 (finiteness), 16 (integrals) and 19
+// (time step, which reads the metric terms), and 3 to 8 for the last kernel.
+template <int N, int WHAT>
+__global__ void __launch_bounds__(256) k_reduce(Geo g, Phys ph, const double *__restrict__ U,
+                                                double *__restrict__ partial) {
+  constexpr int n = N + 1, n2 = n * n, n3 = n2 * n, NC = Red<WHAT>::NC;
+  __shared__ double sm[4 * NC];
+  const double gm1 = ph.gamma - 1.0;
+  double val[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) val[c] = Red<WHAT>::init(c);
+  const unsigned total = (unsigned)g.K * n3, step = gridDim.x * 256u;  // fewer than 2^31 nodes
+  for (unsigned q = blockIdx.x * 256u + threadIdx.x; q < total; q += step) {
+    const int e = q / n3, t = q - e * n3;
     double Uq[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Uq[v] = U[((size_t)e * 5 + v) * n3 + t];
-    if (what == RED_FINITE) {
+    if constexpr (WHAT == RED_FINITE) {
       double bad = 0.0;
 #pragma unroll
       for (int v = 0; v < 5; ++v) bad += isfinite(Uq[v]) ? 0.0 : 1.0;
-      val[0] = bad;
-    } else {
+      val[0] += bad;
+    } else if constexpr (WHAT == RED_TIMESTEP) {
+      // the metric terms per node, or the element's constants
+      const double *Jd = g.Jc ? g.Jc + (size_t)e * AFFINE_DOUBLES : g.Ja + (size_t)e * 9 * n3 + t;
+      const int js = g.Jc ? 1 : n3;
+      const double sj = g.Jc ? Jd[9] : g.sJ[(size_t)e * n3 + t];
       const Pr5 P = to_prim(Uq, gm1);
+      const double c = sqrt(ph.gamma * P.p / P.rho);
+      double sc = 0.0, sv = 0.0;
+#pragma unroll
+      for (int dir = 0; dir < 3; ++dir) {
+        const double a0 = Jd[(3 * dir) * js], a1 = Jd[(3 * dir + 1) * js], a2 = Jd[(3 * dir + 2) * js];
+        const double nn = a0 * a0 + a1 * a1 + a2 * a2;
+        sc += (fabs(P.u * a0 + P.v * a1 + P.w * a2) + c * sqrt(nn)) * sj;
+        sv += fmax(4.0 / 3.0, ph.gamma / ph.Pr) * (ph.mu / P.rho) * nn * sj * sj;
+      }
+      val[0] = fmax(val[0], sc);
+      val[1] = fmax(val[1], sv);
+    } else {
       const double sj = g.sJ[(size_t)e * n3 + t];
-      if (what == RED_TIMESTEP) {
-        const double c = sqrt(ph.gamma * P.p / P.rho);
-        double sc = 0.0, sv = 0.0;
-        for (int dir = 0; dir < 3; ++dir) {
-          const double *Jd = g.Ja + ((size_t)e * 9 + dir * 3) * n3 + t;
-          const double a0 = Jd[0], a1 = Jd[n3], a2 = Jd[2 * n3];
-          const double nn = a0 * a0 + a1 * a1 + a2 * a2;
-          sc += (fabs(P.u * a0 + P.v * a1 + P.w * a2) + c * sqrt(nn)) * sj;
-          sv += fmax(4.0 / 3.0, ph.gamma / ph.Pr) * (ph.mu / P.rho) * nn * sj * sj;
-        }
-        val[0] = sc; val[1] = sv;
-      } else {
-        const int i = t % n, j = (t / n) % n, k = t / n2;
-        const double wq = g.tab->w[i] * g.tab->w[j] * g.tab->w[k] / sj;
+      const Pr5 P = to_prim(Uq, gm1);
+      const int i = t % n, j = (t / n) % n, k = t / n2;
+      const double wq = g.tab->w[i] * g.tab->w[j] * g.tab->w[k] / sj;
 #pragma unroll
-        for (int v = 0; v < 5; ++v) val[v] = wq * Uq[v];
-        val[5] = wq * 0.5 * (Uq[1] * P.u + Uq[2] * P.v + Uq[3] * P.w);
-        const double s = log(P.p) - ph.gamma * log(P.rho);
-        val[6] = wq * (-P.rho * s / gm1);
-        val[7] = 1.0 / sj;
-      }
+      for (int v = 0; v < 5; ++v) val[v] += wq * Uq[v];
+      val[5] += wq * 0.5 * (Uq[1] * P.u + Uq[2] * P.v + Uq[3] * P.w);
+      const double s = log(P.p) - ph.gamma * log(P.rho);
+      val[6] += wq * (-P.rho * s / gm1);
+      val[7] = fmin(val[7], 1.0 / sj);
     }
   }
+  Red<WHAT>::template workgroup<256>(val, sm);
+  if (threadIdx.x == 0) {
 #pragma unroll
-  for (int c = 0; c < 8; ++c) red[c][t] = val[c];
-  __syncthreads();
-  // fold the block onto its largest power-of-two prefix, then halve
-  constexpr int P = (NT & (NT - 1)) == 0 ? NT : (NT >= 512 ? 512 : 256);
-  for (int off = P; off > 0; off >>= 1) {
-    const int lim = (off == P) ? NT - P : off;
-    if (off < P || P < NT) {
-      if (t < lim) {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          const double x = red[c][t], y = red[c][t + off];
-          if (what == RED_TIMESTEP) red[c][t] = fmax(x, y);
-          else if (what == RED_INTEGRALS && isMin[c]) red[c][t] = fmin(x, y);
-          else red[c][t] = x + y;
-        }
-      }
-    }
-    __syncthreads();
+    for (int c = 0; c < NC; ++c) partial[(size_t)blockIdx.x * NC + c] = val[c];
   }
-  if (t < 8) partial[(size_t)e * 8 + t] = red[t][0];
 }
 
 // ----------------------------------------------------------------------------- mortars
@@ -3027,46 +3046,34 @@ int launch_mortar_flux(const Geo &g, const Phys &ph, bool lgl, int eqn, const Mo
 }
 
 template <int N>
-int launch_reduce(const Geo &g, const Phys &ph, int what, const double *U, double, double *partial, hipStream_t st) {
-  hipLaunchKernelGGL((k_reduce<N>), dim3(g.K), dim3(Sz<N>::NT), 0, st, g, ph, what, U, partial);
+int launch_reduce(const Geo &g, const Phys &ph, int what, const double *U, double *partial, hipStream_t st) {
+  const dim3 grid(reduce_rows(g.K, (N + 1) * (N + 1) * (N + 1))), block(256);
+  if (what == RED_TIMESTEP) hipLaunchKernelGGL((k_reduce<N, RED_TIMESTEP>), grid, block, 0, st, g, ph, U, partial);
+  else if (what == RED_INTEGRALS) hipLaunchKernelGGL((k_reduce<N, RED_INTEGRALS>), grid, block, 0, st, g, ph, U, partial);
+  else hipLaunchKernelGGL((k_reduce<N, RED_FINITE>), grid, block, 0, st, g, ph, U, partial);
   DG_CHECK_LAUNCH();
   return DG_OK;
 }
 
 #if !defined(DG_ONLY_N) && !defined(DG_FUSED_BATCH)
-// one workgroup folds the per-element partials in a fixed order
-__global__ void __launch_bounds__(256) k_final_reduce(int what, const double *__restrict__ partial, int K,
-                                                      double *__restrict__ out) {
-  __shared__ double red[8][256];
-  const int t = threadIdx.x;
-  double val[8];
+// one workgroup folds the rows of partial results in a fixed order; the components beyond WHAT's are zero
+template <int WHAT>
+__global__ void __launch_bounds__(1024) k_final_reduce(const double *__restrict__ partial, int rows,
+                                                       double *__restrict__ out) {
+  constexpr int NC = Red<WHAT>::NC;
+  __shared__ double sm[16 * NC];
+  double val[NC];
 #pragma unroll
-  for (int c = 0; c < 8; ++c) val[c] = (what == RED_INTEGRALS && c == 7) ? 1e300 : 0.0;
-  for (int e = t; e < K; e += 256) {
+  for (int c = 0; c < NC; ++c) val[c] = Red<WHAT>::init(c);
+  for (int r = threadIdx.x; r < rows; r += 1024) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const double x = partial[(size_t)e * 8 + c];
-      if (what == RED_TIMESTEP) val[c] = fmax(val[c], x);
-      else if (what == RED_INTEGRALS && c == 7) val[c] = fmin(val[c], x);
-      else val[c] += x;
-    }
+    for (int c = 0; c < NC; ++c) val[c] = Red<WHAT>::join(c, val[c], partial[(size_t)r * NC + c]);
   }
+  Red<WHAT>::template workgroup<1024>(val, sm);
+  if (threadIdx.x == 0) {
 #pragma unroll
-  for (int c = 0; c < 8; ++c) red[c][t] = val[c];
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (t < off) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const double x = red[c][t], y = red[c][t + off];
-        if (what == RED_TIMESTEP) red[c][t] = fmax(x, y);
-        else if (what == RED_INTEGRALS && c == 7) red[c][t] = fmin(x, y);
-        else red[c][t] = x + y;
-      }
-    }
-    __syncthreads();
+    for (int c = 0; c < 8; ++c) out[c] = c < NC ? val[c < NC ? c : 0] : 0.0;
   }
-  if (t < 8) out[t] = red[t][0];
 }
 
 // quadrature weight of every node: J w_i w_j w_k
@@ -3089,8 +3096,11 @@ __global__ void k_axpby(double *y, const double *x, double alpha, double beta, s
   for (; i < n; i += stride) y[i] = alpha * y[i] + beta * x[i];
 }
 
-int launch_final_reduce(int what, const double *partial, int K, double *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_final_reduce, dim3(1), dim3(256), 0, st, what, partial, K, out);
+int launch_final_reduce(int what, const double *partial, int rows, double *out, hipStream_t st) {
+  const dim3 one(1), block(1024);
+  if (what == RED_TIMESTEP) hipLaunchKernelGGL(k_final_reduce<RED_TIMESTEP>, one, block, 0, st, partial, rows, out);
+  else if (what == RED_INTEGRALS) hipLaunchKernelGGL(k_final_reduce<RED_INTEGRALS>, one, block, 0, st, partial, rows, out);
+  else hipLaunchKernelGGL(k_final_reduce<RED_FINITE>, one, block, 0, st, partial, rows, out);
   DG_CHECK_LAUNCH();
   return DG_OK;
 }
@@ -3266,7 +3276,7 @@ template int launch_lift<DG_ONLY_N>(const Geo &, const Phys &, bool, int, const 
                                     hipStream_t);
 template int launch_main<DG_ONLY_N>(const Geo &, const Phys &, bool, int, int, const double *, const double *,
                                     double *, double *, double, double, double, int, hipStream_t);
-template int launch_reduce<DG_ONLY_N>(const Geo &, const Phys &, int, const double *, double, double *, hipStream_t);
+template int launch_reduce<DG_ONLY_N>(const Geo &, const Phys &, int, const double *, double *, hipStream_t);
 template int launch_mortar_lift<DG_ONLY_N>(const Geo &, const Phys &, bool, const MortarDesc *, int, const double *,
                                            hipStream_t);
 template int launch_fv_face<DG_ONLY_N>(const Geo &, const Phys &, const FvGeo &, bool, const double *, hipStream_t);

@@ -65,12 +65,12 @@ extern "C" int dg_integrals_noalloc(dg_handle *h, const double *U, double *out_d
   int rc;
   switch (h->N) {
 #define DG_CASE(NN) \
-  case NN: rc = dg::launch_reduce<NN>(g, h->ph, dg::RED_INTEGRALS, U, 0.0, partial, h->stream); break;
+  case NN: rc = dg::launch_reduce<NN>(g, h->ph, dg::RED_INTEGRALS, U, partial, h->stream); break;
     DG_CASE(1) DG_CASE(2) DG_CASE(3) DG_CASE(4) DG_CASE(5) DG_CASE(6) DG_CASE(7) DG_CASE(8)
 #undef DG_CASE
     default: rc = DG_ERR_UNSUPPORTED;
   }
-  if (!rc) rc = dg::launch_final_reduce(dg::RED_INTEGRALS, partial, h->K, out_dev, h->stream);
+  if (!rc) rc = dg::launch_final_reduce(dg::RED_INTEGRALS, partial, dg::reduce_rows(h->K, h->n3), out_dev, h->stream);
   if (rc) h->err = "launch of the integral reduction failed";
   return rc;
 }
