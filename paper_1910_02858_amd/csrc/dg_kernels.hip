@@ -950,61 +950,33 @@ __global__ void __launch_bounds__(Sz<N>::NT, (lift_minb<LGL, OUT, GEN>()))
   lift_body<N, LGL, OUT, GEN, AFF>(g, ph, e, true, threadIdx.x, U, G, Fv, sm, sDh, sl, slh);
 }
 
-// ----------------------------------------------------------------------------- operator
-// waves per SIMD the Navier-Stokes weak- and strong-form operators are built for: 4 (128
-// registers, two workgroups per CU at N = 7; no spill on LGL nodes, 84 bytes on LG nodes) against
-// the 131-148 registers they take unbounded (one workgroup per CU): at 48^3, N = 7, weak form on
-// LG nodes 6.14 -> 5.17 ms.  Degrees below 5 (one or two waves per element) keep their registers,
-// and so do the Euler forms (at N = 3 on 96^3 a 128-register budget spills 108 bytes: 5.20 ->
-// 6.15 ms).
-#ifndef DG_WMAIN_MINB
-#define DG_WMAIN_MINB 4
-#endif
-template <int N, bool LGL, bool NS, int FORM, int GEN> constexpr int main_minb() {
-  return (NS && GEN < 2 && N >= 5 && FORM != 1) ? DG_WMAIN_MINB : 1;
-}
+// ----------------------------------------------------------------------------- operator, weak/strong
+// Weak- and strong-form operator (eqs. semiDiscrete, semiDiscreteStrong): k_line, and k_main for
+// Navier-Stokes on meshes with non-conforming faces, whose lifting leaves the gradients.
 
-// FORM: 0 weak, 1 split, 2 strong.  MODE: 0 write U_t, 1 fused RK stage.  GEN: face codes.
-// FVM: hybrid DG/FV mesh (Euler): finite-volume elements are left to k_fv_volume, and the sides
-// that meet one take their flux from Geo::fvFx.
-// TP: the surface flux is a two-point flux (riemann 2, 3).  Their logarithmic means alone raise the Euler
-// operator at N = 3 from 120 registers to 158, three wavefronts per SIMD instead of four; LLF and Roe take the
-// instance without them: 2640 -> 2409 us a step of 48^3 elements on LG nodes.
-template <int N, bool LGL, bool NS, int FORM, int GEN, bool FVM, bool AFF, bool TP>
-__global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()))
+// Navier-Stokes, non-conforming faces: one node per lane, face fluxes first, then per direction the node's
+// contravariant flux into LDS and the contraction along its line.  FORM: 0 weak, 2 strong.
+// mode 0: write U_t, 1: fused RK stage.  AFF: the metric terms are the element's constants (Geo::Jc).
+template <int N, bool LGL, int FORM, bool AFF>
+__global__ void __launch_bounds__(Sz<N>::NT)
     k_main(Geo g, Phys ph, const double *__restrict__ U, const double *__restrict__ G, double *__restrict__ out,
            double *__restrict__ R, double ca, double cb, double dt, int mode) {
   using S = Sz<N>;
   constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = S::NT;
-  constexpr int NX = (FORM == 1) ? 8 : 5;
-  // WVM: weak form, Navier-Stokes, conforming faces: the lifting kernel has formed the viscous
-  // volume term (Geo::Gd) and every side's viscous flux at its trace (Geo::Gf); no gradients
-  constexpr bool WVM = NS && FORM == 0 && GEN < 2;
-  // SVM: strong form on LGL nodes, Navier-Stokes, conforming faces: as for the split form, the
-  // lifting kernel has formed the strong-form viscous divergence (Geo::Gd) and the face traces of
-  // the contravariant viscous fluxes (Geo::Gf)
-  constexpr bool SVM = NS && FORM == 2 && LGL && GEN < 2;
-  // SVL: strong form on LG nodes, Navier-Stokes, conforming faces: the lifting kernel has formed
-  // the strong-form viscous volume and interior surface terms (Geo::Gd) and, as for the weak form,
-  // every side's viscous flux at its trace (Geo::Gf)
-  constexpr bool SVL = NS && FORM == 2 && !LGL && GEN < 2;
-  constexpr bool PFM = WVM || SVL;  // face viscous fluxes with each side's own normal
-  constexpr bool VH = WVM || SVM || SVL;  // no gradients read
   __shared__ double sU[5 * n3];
-  __shared__ double sX[NX * n3];
+  __shared__ double sX[5 * n3];
   __shared__ double sF[6 * 5 * n2];
   __shared__ double sD[n * n], sl[2 * n], slh[2 * n];
   const int e = xcd_element(blockIdx.x, g.K);
   const int t = threadIdx.x;
   if (e >= g.K) return;
-  if (FVM && g.fvflag[e]) return;  // a finite-volume element
   AffineConst jc = nullptr;
   if constexpr (AFF) jc = affine_const(g, e);
   const double gm1 = ph.gamma - 1.0;
   const Tab *tb = g.tab;
   // strong form on LG nodes: the derivative matrix carries the interior flux's interpolation
   // to the line's two faces (Tab::Ds), so the surface terms add the numerical flux alone
-  for (int c = t; c < n * n; c += NT) sD[c] = (FORM == 0) ? tb->Dh[c] : ((FORM == 2 && !LGL) ? tb->Ds[c] : tb->D[c]);
+  for (int c = t; c < n * n; c += NT) sD[c] = (FORM == 0) ? tb->Dh[c] : (LGL ? tb->D[c] : tb->Ds[c]);
   if (t < n) {
     sl[t] = tb->lm[t]; sl[n + t] = tb->lp[t];
     slh[t] = tb->lhm[t]; slh[n + t] = tb->lhp[t];
@@ -1025,20 +997,13 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
     const int s = p / n2, ab = p - s * n2, a = ab % n, b = ab / n, dn = s >> 1;
     const bool plus = s & 1;
     const int nb = g.nbr[(size_t)e * 6 + s];
-    const NbFace f = nbr_face<n, (GEN > 0)>(g, e, s, a, b);
-    const bool bnd = GEN && f.bnd;
-    if (GEN == 2 && bnd && f.kind == FACE_MORTAR) {
+    const NbFace f = nbr_face<n, true>(g, e, s, a, b);
+    const bool bnd = f.bnd;
+    if (bnd && f.kind == FACE_MORTAR) {
       // non-conforming face: the outward flux from the mortar face array
       const double *mf = g.mflux + (size_t)g.mslot[(size_t)e * 6 + s] * 5 * n2 + ab;
 #pragma unroll
       for (int v = 0; v < 5; ++v) sF[(s * 5 + v) * n2 + ab] = mf[v * n2];
-      continue;
-    }
-    if (FVM && g.fvflag[nb]) {
-      // face shared with a finite-volume element: the outward flux at the face nodes
-      const double *fx = g.fvFx + ((size_t)e * 6 + s) * 5 * n2 + ab;
-#pragma unroll
-      for (int v = 0; v < 5; ++v) sF[(s * 5 + v) * n2 + ab] = fx[v * n2];
       continue;
     }
     const double *Un = U + (size_t)(bnd ? e : nb) * 5 * n3;
@@ -1046,65 +1011,41 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
     double Uw[5], Ux[5], gw[12], gx[12];  // w: this element's trace, x: neighbour's trace
     if (LGL) {
       const int q = line_node<n>(dn, a, b, plus ? N : 0);
-      const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dn, a, b, plus ? 0 : N);
+      const int qn = line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0);
 #pragma unroll
       for (int v = 0; v < 5; ++v) { Uw[v] = sU[v * n3 + q]; Ux[v] = bnd ? 0.0 : Un[v * n3 + qn]; }
-      if (NS && !VH) {
 #pragma unroll
-        for (int c = 0; c < 12; ++c) { gw[c] = Ge[c * n3 + q]; gx[c] = bnd ? 0.0 : Gn[c * n3 + qn]; }
-      }
+      for (int c = 0; c < 12; ++c) { gw[c] = Ge[c * n3 + q]; gx[c] = bnd ? 0.0 : Gn[c * n3 + qn]; }
     } else {
-      const double *lo = sl + (plus ? n : 0), *ln = GEN ? sl + (f.plus ? n : 0) : sl + (plus ? 0 : n);
+      // the lifting kernel has interpolated every side's traces of U and of the gradients; this side's
+      // U trace from LDS, the rest read contiguously
+      const double *lo = sl + (plus ? n : 0);
+      const double *gt = g.Gtr + ((size_t)e * 6 + s) * 12 * n2 + ab;
+      const size_t sn = (size_t)(bnd ? e : nb) * 6 + 2 * f.dn + (f.plus ? 1 : 0);
+      const double *utn = g.Utr + sn * 5 * n2 + f.a + n * f.b;
+      const double *gtn = g.Gtr + sn * 12 * n2 + f.a + n * f.b;
 #pragma unroll
       for (int v = 0; v < 5; ++v) { Uw[v] = 0.0; Ux[v] = 0.0; }
-      if (NS) {
-#pragma unroll
-        for (int c = 0; c < 12; ++c) { gw[c] = 0.0; gx[c] = 0.0; }
-      }
-      if (NS) {
-        // Navier-Stokes: the lifting kernel has interpolated every side's traces of U and of the
-        // gradients; this side's U trace from LDS, the rest read contiguously
-        const double *gt = g.Gtr + ((size_t)e * 6 + s) * 12 * n2 + ab;
-        const size_t sn = (size_t)(bnd ? e : nb) * 6 + 2 * f.dn + (f.plus ? 1 : 0);
-        const double *utn = g.Utr + sn * 5 * n2 + f.a + n * f.b;
-        const double *gtn = g.Gtr + sn * 12 * n2 + f.a + n * f.b;
 #pragma unroll 1
-        for (int m = 0; m < n; ++m) {
-          const int q = line_node<n>(dn, a, b, m);
+      for (int m = 0; m < n; ++m) {
+        const int q = line_node<n>(dn, a, b, m);
 #pragma unroll
-          for (int v = 0; v < 5; ++v) Uw[v] += lo[m] * sU[v * n3 + q];
-        }
-        if (!VH) {
+        for (int v = 0; v < 5; ++v) Uw[v] += lo[m] * sU[v * n3 + q];
+      }
 #pragma unroll
-          for (int c = 0; c < 12; ++c) gw[c] = gt[c * n2];
-        }
-        if (!bnd) {
+      for (int c = 0; c < 12; ++c) { gw[c] = gt[c * n2]; gx[c] = 0.0; }
+      if (!bnd) {
 #pragma unroll
-          for (int v = 0; v < 5; ++v) Ux[v] = utn[v * n2];
-          if (!VH) {
+        for (int v = 0; v < 5; ++v) Ux[v] = utn[v * n2];
 #pragma unroll
-            for (int c = 0; c < 12; ++c) gx[c] = gtn[c * n2];
-          }
-        }
-      } else {
-        // two nodes' loads in flight: all n nodes' early loads spill
-#pragma unroll 2
-        for (int m = 0; m < n; ++m) {
-          const int q = line_node<n>(dn, a, b, m), qn = GEN ? line_node<n>(f.dn, f.a, f.b, m) : q;
-#pragma unroll
-          for (int v = 0; v < 5; ++v) Uw[v] += lo[m] * sU[v * n3 + q];
-          if (!bnd) {
-#pragma unroll
-            for (int v = 0; v < 5; ++v) Ux[v] += ln[m] * Un[v * n3 + qn];
-          }
-        }
+        for (int c = 0; c < 12; ++c) gx[c] = gtn[c * n2];
       }
     }
     // the master's normal and state go first (fn holds the outward normal, the master's
     // negated on the slave side)
     const double *fnp = AFF ? g.Jc + (size_t)e * AFFINE_DOUBLES + 10 + 3 * s : g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
     const int fst = AFF ? 1 : n2;
-    const bool mst = GEN ? f.master : plus;
+    const bool mst = f.master;
     const double sg = mst ? 1.0 : -1.0;
     const double nt[3] = {sg * fnp[0], sg * fnp[fst], sg * fnp[2 * fst]};
     const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
@@ -1122,114 +1063,52 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
 #pragma unroll
         for (int v = 0; v < 5; ++v) Ux[v] = ph.ub[v];
       }
-    } else if (bnd && f.kind == DG_BC_WALL_ISOTHERMAL) {
-      // isothermal wall: velocity reversed; outer gradient equal to the inner one
-      Ux[0] = Uw[0]; Ux[1] = -Uw[1]; Ux[2] = -Uw[2]; Ux[3] = -Uw[3]; Ux[4] = Uw[4];
-      if (NS && !VH) {
-#pragma unroll
-        for (int c = 0; c < 12; ++c) gx[c] = gw[c];
-      }
-    } else if (bnd && f.kind == DG_BC_WALL) {
-      // no-slip wall: velocity reversed; velocity gradient kept, temperature gradient mirrored
-      Ux[0] = Uw[0]; Ux[1] = -Uw[1]; Ux[2] = -Uw[2]; Ux[3] = -Uw[3]; Ux[4] = Uw[4];
-      if (NS && !VH) {
-#pragma unroll
-        for (int c = 0; c < 12; ++c) gx[c] = gw[c];
-        double tg[3] = {gw[3], gw[7], gw[11]};
-        mirror3(tg, nh);
-        gx[3] = tg[0]; gx[7] = tg[1]; gx[11] = tg[2];
-      }
     } else if (bnd) {
-      // symmetry plane: mirror image of the inner state and gradients
+#pragma unroll
+      for (int c = 0; c < 12; ++c) gx[c] = gw[c];
 #pragma unroll
       for (int v = 0; v < 5; ++v) Ux[v] = Uw[v];
-      mirror3(Ux + 1, nh);
-      if (NS && !VH) {
-#pragma unroll
-        for (int c = 0; c < 12; ++c) gx[c] = gw[c];
+      if (f.kind == DG_BC_WALL_ISOTHERMAL || f.kind == DG_BC_WALL) {
+        // no-slip wall: velocity reversed, velocity gradient kept; the temperature gradient kept at an
+        // isothermal wall, mirrored at an adiabatic one
+        Ux[1] = -Uw[1]; Ux[2] = -Uw[2]; Ux[3] = -Uw[3];
+        if (f.kind == DG_BC_WALL) {
+          double tg[3] = {gw[3], gw[7], gw[11]};
+          mirror3(tg, nh);
+          gx[3] = tg[0]; gx[7] = tg[1]; gx[11] = tg[2];
+        }
+      } else {
+        // symmetry plane: mirror image of the inner state and gradients
+        mirror3(Ux + 1, nh);
         mirror_grad(gx, nh);
       }
     }
     const double *UM = mst ? Uw : Ux, *US = mst ? Ux : Uw;
     double F[5];
-    if constexpr (TP) riemann(ph, UM, US, nh, F);
-    else if (ph.rs == DG_RS_LLF) riemann_t<DG_RS_LLF>(ph, UM, US, nh, F);
-    else riemann_t<DG_RS_ROE>(ph, UM, US, nh, F);
+    riemann(ph, UM, US, nh, F);
 #pragma unroll
     for (int v = 0; v < 5; ++v) F[v] *= sh;
-    if (NS && !VH) {
-      const double *gM = mst ? gw : gx, *gS = mst ? gx : gw;
-      double FvM[5], FvS[5];
-      const Pr5 PM = to_prim(UM, gm1), PS = to_prim(US, gm1);
-      flux_v(PM, gM, ph, nt, FvM);
-      if (given) {
+    const double *gM = mst ? gw : gx, *gS = mst ? gx : gw;
+    double FvM[5], FvS[5];
+    const Pr5 PM = to_prim(UM, gm1), PS = to_prim(US, gm1);
+    flux_v(PM, gM, ph, nt, FvM);
+    if (given) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) FvS[v] = FvM[v];
-      } else {
-        flux_v(PS, gS, ph, nt, FvS);
-      }
-#pragma unroll
-      for (int v = 0; v < 5; ++v) F[v] -= 0.5 * (FvM[v] + FvS[v]);
+      for (int v = 0; v < 5; ++v) FvS[v] = FvM[v];
+    } else {
+      flux_v(PS, gS, ph, nt, FvS);
     }
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sF[(s * 5 + v) * n2 + ab] = sg * F[v];
-    if (SVM) {
-      // minus the BR1 mean of the viscous flux along this side's +xi_dn direction (the split
-      // form's reading of the traces and boundary kinds), applied outward
-      const double *fo = g.Gf + ((size_t)e * 6 + s) * 4 * n2 + ab;
-      double V[4];
-      if (given) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) V[c] = fo[c * n2];
-      } else if (bnd && (f.kind == DG_BC_WALL || f.kind == DG_BC_WALL_ISOTHERMAL)) {
-        // no-slip wall: the momentum part of the inner flux; at an isothermal wall the inner heat
-        // flux (the energy flux minus the work of the stress)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) V[c] = fo[c * n2];
-        V[3] = f.kind == DG_BC_WALL_ISOTHERMAL
-                   ? fo[3 * n2] - (V[0] * Uw[1] + V[1] * Uw[2] + V[2] * Uw[3]) * (1.0 / Uw[0])
-                   : 0.0;
-      } else if (bnd) {
-        // symmetry plane: the normal part of the momentum flux
-        const double gm = fo[0] * nh[0] + fo[n2] * nh[1] + fo[2 * n2] * nh[2];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) V[c] = gm * nh[c];
-        V[3] = 0.0;
-      } else {
-        const double *pn = g.Gf + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
-        const double sn = (GEN && f.plus == plus) ? -1.0 : 1.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) V[c] = 0.5 * (fo[c * n2] + sn * pn[c * n2]);
-      }
-      const double sp = plus ? 1.0 : -1.0;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sF[(s * 5 + 1 + c) * n2 + ab] -= sp * V[c];
-    }
-    if (PFM) {
-      // minus the outward BR1 mean of the viscous flux: each side's flux carries its own outward
-      // normal (the two normals of a face are negatives of each other), a boundary side's the
-      // mean itself
-      const double *po = g.Gf + ((size_t)e * 6 + s) * 4 * n2 + ab;
-      if (bnd) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sF[(s * 5 + 1 + c) * n2 + ab] -= po[c * n2];
-      } else {
-        const double *pn = g.Gf + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sF[(s * 5 + 1 + c) * n2 + ab] -= 0.5 * (po[c * n2] - pn[c * n2]);
-      }
-    }
+    for (int v = 0; v < 5; ++v) sF[(s * 5 + v) * n2 + ab] = sg * (F[v] - 0.5 * (FvM[v] + FvS[v]));
   }
   double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   const int i = t % n, j = (t / n) % n, k = t / n2;
   Pr5 Po;
   double go[12];  // the node's lifted gradients, loaded after the face phase
   if (t < n3) {
-    if (!VH) Po = to_prim(Uo, gm1);
-    if (NS && !VH) {
+    Po = to_prim(Uo, gm1);
 #pragma unroll
-      for (int c = 0; c < 12; ++c) go[c] = Ge[c * n3 + t];
-    }
+    for (int c = 0; c < 12; ++c) go[c] = Ge[c * n3 + t];
   }
   for (int dir = 0; dir < 3; ++dir) {
     double Fint[5], nv[3];
@@ -1241,23 +1120,13 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
         const double *Jd = g.Ja + ((size_t)e * 9 + dir * 3) * n3 + t;
         nv[0] = Jd[0]; nv[1] = Jd[n3]; nv[2] = Jd[2 * n3];
       }
-      double Fc[5], Fv[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-      double Un[5];
+      double Fc[5], Fv[5];
+      flux_c(Uo, Po, nv, Fc);
+      flux_v(Po, go, ph, nv, Fv);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Un[v] = sU[v * n3 + t];
-      if (VH) Po = to_prim(Un, gm1);  // recomputed per direction: not held across the phases
-      flux_c(Un, Po, nv, Fc);
-      if (NS && !VH) flux_v(Po, go, ph, nv, Fv);
-#pragma unroll
-      for (int v = 0; v < 5; ++v) Fint[v] = Fc[v] - Fv[v];
-      if (FORM == 1) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sX[d * n3 + t] = nv[d];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) sX[(3 + v) * n3 + t] = Fv[v];
-      } else {
-#pragma unroll
-        for (int v = 0; v < 5; ++v) sX[v * n3 + t] = Fint[v];
+      for (int v = 0; v < 5; ++v) {
+        Fint[v] = Fc[v] - Fv[v];
+        sX[v * n3 + t] = Fint[v];
       }
     }
     __syncthreads();
@@ -1265,26 +1134,11 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
       const int id = dir == 0 ? i : (dir == 1 ? j : k);
       const int str = dir == 0 ? 1 : (dir == 1 ? n : n2);
       const int base = t - id * str;
-      // at most four nodes' loads in flight: with all n of the last direction's in flight beside
-      // the epilogue's loads the LG operators spilled 84 bytes
 #pragma unroll 4
       for (int m = 0; m < n; ++m) {
-        const int qm = base + m * str;
         const double Dm = sD[id * n + m];
-        if (FORM == 1) {
-          double Ub[5], F[5];
 #pragma unroll
-          for (int v = 0; v < 5; ++v) Ub[v] = sU[v * n3 + qm];
-          const Pr5 Pb = to_prim(Ub, gm1);
-          const double nm[3] = {0.5 * (nv[0] + sX[qm]), 0.5 * (nv[1] + sX[n3 + qm]), 0.5 * (nv[2] + sX[2 * n3 + qm])};
-          flux_2pt(ph.vf, Uo, Po, Ub, Pb, nm, gm1, F);
-          const double D2 = 2.0 * Dm;
-#pragma unroll
-          for (int v = 0; v < 5; ++v) acc[v] += D2 * F[v] - Dm * sX[(3 + v) * n3 + qm];
-        } else {
-#pragma unroll
-          for (int v = 0; v < 5; ++v) acc[v] += Dm * sX[v * n3 + qm];
-        }
+        for (int v = 0; v < 5; ++v) acc[v] += Dm * sX[v * n3 + base + m * str];
       }
       // surface integral of the two faces of this direction
 #pragma unroll
@@ -1295,8 +1149,8 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
         const int a = dir == 0 ? j : i, b = dir == 2 ? j : k;
         const int ab = a + n * b;
         const double sg = sd ? 1.0 : -1.0;
-        // strong and split forms on LGL nodes: minus the face node's own interior flux (on LG
-        // nodes its interpolation is part of Tab::Ds)
+        // strong form on LGL nodes: minus the face node's own interior flux (on LG nodes its
+        // interpolation is part of Tab::Ds)
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
           double pen = sF[(s * 5 + v) * n2 + ab];
@@ -1307,22 +1161,15 @@ __global__ void __launch_bounds__(Sz<N>::NT, (main_minb<N, LGL, NS, FORM, GEN>()
     }
   }
   if (t < n3) {
-    if (VH) {
-      // the viscous volume term, formed by the lifting kernel
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[1 + c] -= g.Gd[((size_t)e * 4 + c) * n3 + t];
-    }
     const double sj = AFF ? jc[9] : g.sJ[(size_t)e * n3 + t];
-    if (mode == 0) {
-      double *Oe = out + (size_t)e * 5 * n3;
+    double *Oe = out + (size_t)e * 5 * n3;
+    double *Re = R + (size_t)e * 5 * n3;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Oe[v * n3 + t] = -acc[v] * sj;
-    } else {
-      double *Oe = out + (size_t)e * 5 * n3;
-      double *Re = R + (size_t)e * 5 * n3;
-#pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        const double ut = -acc[v] * sj;
+    for (int v = 0; v < 5; ++v) {
+      const double ut = -acc[v] * sj;
+      if (mode == 0) {
+        Oe[v * n3 + t] = ut;
+      } else {
         // a = 0 (first stage) does not read R, so R may hold anything on entry
         const double r = (ca != 0.0 ? ca * Re[v * n3 + t] : 0.0) + dt * ut;
         Re[v * n3 + t] = r;
@@ -1886,6 +1733,366 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, split_minb(N)) k_split(Geo g, 
   if (e >= g.K) return;
   if (FVM && g.fvflag[e]) return;  // a finite-volume element
   split_body<N, NS, VF, GEN, FVM, AFF>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
+}
+
+// ----------------------------------------------------------------------------- weak/strong form, by lines
+// Waves per SIMD k_line is built for: at three no instance spills but those of boundary meshes with a two-point
+// flux (36 bytes); four (128 registers) spill in the Euler operator at N = 3 and take 2122 us a step of 48^3
+// elements instead of 2026.
+template <int N> constexpr int line_minb() { return N >= 8 ? 2 : 3; }
+
+// Weak- and strong-form operator of conforming meshes (Euler: also with non-conforming faces), one lane per
+// line as the split operator: the lane evaluates the numerical fluxes of the faces at its line's ends, adds
+// every node's flux along the line, times the matrix's column, to the line's n sums, and the two fluxes times
+// lhat(+-1).  FORM 0 weak (D-hat), 2 strong (D; on LG nodes Tab::Ds, whose surface term is the numerical flux
+// alone).  Navier-Stokes: the lifting has formed the viscous volume term (Geo::Gd) and the faces' viscous
+// fluxes (Geo::Gf): contravariant traces for the strong form on LGL nodes, else each side's flux along its
+// own outward normal.
+// What bounds it: with one node per lane the Euler operator on LG nodes at N = 3 waited for memory 70 % of
+// its wavefronts' time (seven dependent trips: a neighbour's index, then its lines two nodes at a time, for
+// each of two rounds of face points, and the register at the end).  Here every load of an element is issued
+// before the first barrier.  A step of 48^3 elements (Euler, LG, N = 3) 2408 -> 2026 us; of 16^3 (Navier-Stokes,
+// weak form, LG, N = 7: half the LDS accesses) 1433 -> 1247 us; strong form, LGL, N = 4, curved 467 -> 456 us.
+// AFF, FVM, mode as for the split operator.  TP: two-point surface flux (riemann 2, 3): its logarithmic means
+// cost 60 registers more, so LLF and Roe take the instance without them.
+template <int N, bool LGL, bool NS, int FORM, int GEN, bool FVM, bool AFF, bool TP>
+__global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
+    k_line(Geo g, Phys ph, const double *__restrict__ U, double *__restrict__ out, double *__restrict__ R, double ca,
+           double cb, double dt, int mode) {
+  using S = Sz<N>;
+  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = SplitSz<N>::NT, IT = (n3 + NT - 1) / NT;
+  constexpr bool PFM = NS && !(FORM == 2 && LGL);  // face viscous fluxes along each side's own normal
+  // state, metric terms (none on affine elements); the result takes the metric terms' place
+  __shared__ double sm[(AFF ? 10 : 14) * n3];
+  double *sU = sm, *sJ = sm + 5 * n3, *sAcc = sJ;
+  const int e = xcd_element(blockIdx.x, g.K), lane = threadIdx.x;
+  if (e >= g.K) return;
+  if (FVM && g.fvflag[e]) return;  // a finite-volume element
+  AffineConst jc = nullptr;
+  if constexpr (AFF) jc = affine_const(g, e);
+  const double gm1 = ph.gamma - 1.0;
+  const double *Ue = U + (size_t)e * 5 * n3;
+  const Tab *tab = g.tab;
+  typedef const __attribute__((address_space(4))) double *Scal;
+  const Scal M = (Scal)(FORM == 0 ? tab->Dh : (LGL ? tab->D : tab->Ds));
+  const Scal lm = (Scal)tab->lm, lp = (Scal)tab->lp, lhm = (Scal)tab->lhm, lhp = (Scal)tab->lhp;
+  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(lane / n2) : lane / n2;
+  const int ab = lane - dir * n2, a = ab % n, b = ab / n;
+  const bool act = lane < 3 * n2;
+  // the neighbours' indices first (loads return in order), then everything else the element reads
+  int nb2[2] = {0, 0};
+  NbFace f2[2];
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd)
+    if (act) {
+      nb2[sd] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
+      f2[sd] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
+    }
+  double Uq[IT][5], Rq[IT][5];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (t < n3) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Uq[it][v] = Ue[v * n3 + t];
+    }
+  }
+  double Jq[IT][9];
+  if constexpr (!AFF) {
+    const double *Jae = g.Ja + (size_t)e * 9 * n3;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int t = lane + it * NT;
+      if (t < n3) {
+#pragma unroll
+        for (int c = 0; c < 9; ++c) Jq[it][c] = Jae[c * n3 + t];
+      }
+    }
+  }
+  constexpr bool LINES = !LGL && !NS;     // the neighbours' traces are interpolated here from their lines
+  constexpr int CH = n <= 4 ? n : 2;      // nodes of both neighbours' lines in flight
+  double Ux[2][5], Vo[2][4], Vn[2][4], nt2[2][3];
+  int kind[2];  // -1 inner face, else the boundary kind; -2 a face whose outward flux is given (Ux)
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd) {
+    kind[sd] = -1;
+    if (!act) continue;
+    const int s = 2 * dir + sd;
+    const int nb = nb2[sd];
+    const NbFace f = f2[sd];
+    const bool bnd = GEN && f.bnd;
+    const double *fnp = AFF ? g.Jc + (size_t)e * AFFINE_DOUBLES + 10 + 3 * s : g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
+    const int fst = AFF ? 1 : n2;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) nt2[sd][d] = fnp[d * fst];
+    const double *gx = nullptr;
+    if (GEN == 2 && bnd && f.kind == FACE_MORTAR) gx = g.mflux + (size_t)g.mslot[(size_t)e * 6 + s] * 5 * n2 + ab;
+    if (FVM && !bnd && g.fvflag[nb]) gx = g.fvFx + ((size_t)e * 6 + s) * 5 * n2 + ab;
+    if ((GEN == 2 || FVM) && gx) {
+      // the outward flux from the mortar face array, or of a face shared with a finite-volume element
+      kind[sd] = -2;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Ux[sd][v] = gx[v * n2];
+      continue;
+    }
+    if (bnd) kind[sd] = f.kind;
+    if (!bnd && !LINES) {
+      if (LGL) {
+        const double *Un = U + (size_t)nb * 5 * n3;
+        const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dir, a, b, sd ? 0 : N);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Ux[sd][v] = Un[v * n3 + qn];
+      } else {
+        const double *ut = g.Utr + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 5 * n2 + f.a + n * f.b;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Ux[sd][v] = ut[v * n2];
+      }
+    }
+    if (NS) {
+      const double *fo = g.Gf + ((size_t)e * 6 + s) * 4 * n2 + ab;
+      const double *fnb = bnd ? fo : g.Gf + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) { Vo[sd][c] = fo[c * n2]; Vn[sd][c] = fnb[c * n2]; }
+    }
+  }
+  // the epilogue's loads: the register here where they are few, the rest below
+  constexpr bool PRE = IT == 1 && !NS;
+  double gd[IT][4], sjq[IT];
+  auto load_epilogue = [&]() {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int t = lane + it * NT;
+      if (t < n3) {
+        sjq[it] = AFF ? jc[9] : g.sJ[(size_t)e * n3 + t];
+        if (NS) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) gd[it][c] = g.Gd[((size_t)e * 4 + c) * n3 + t];
+        }
+        if (mode == 1 && ca != 0.0) {
+          const double *Re = R + (size_t)e * 5 * n3;
+#pragma unroll
+          for (int v = 0; v < 5; ++v) Rq[it][v] = Re[v * n3 + t];
+        }
+      }
+    }
+  };
+  if constexpr (PRE) load_epilogue();
+  if constexpr (LINES) {
+    if (act) {
+#pragma unroll
+      for (int sd = 0; sd < 2; ++sd)
+#pragma unroll
+        for (int v = 0; v < 5; ++v)
+          if (kind[sd] != -2) Ux[sd][v] = 0.0;
+#pragma unroll(n <= 4 ? n : 1)
+      for (int c = 0; c < n; c += CH) {
+        double x[2][CH][5];
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+          if (kind[sd] != -1) continue;
+          const NbFace f = f2[sd];
+          const double *Un = U + (size_t)nb2[sd] * 5 * n3;
+#pragma unroll
+          for (int m = 0; m < CH; ++m)
+            if (c + m < n) {
+              const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, c + m) : line_node<n>(dir, a, b, c + m);
+#pragma unroll
+              for (int v = 0; v < 5; ++v) x[sd][m][v] = Un[v * n3 + qn];
+            }
+        }
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+          if (kind[sd] != -1) continue;
+          const bool np = GEN ? f2[sd].plus : !sd;
+#pragma unroll
+          for (int m = 0; m < CH; ++m)
+            if (c + m < n) {
+              const double l = np ? lp[c + m] : lm[c + m];
+#pragma unroll
+              for (int v = 0; v < 5; ++v) Ux[sd][v] = fma(l, x[sd][m][v], Ux[sd][v]);
+            }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (t < n3) {
+      const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sU[v * n3 + q] = Uq[it][v];
+#pragma unroll
+      for (int c = 0; c < 9 && !AFF; ++c) sJ[c * n3 + q] = Jq[it][c];
+    }
+  }
+  __syncthreads();
+  double acc[n][5];
+  if (act) {
+    const LineSlots<n> slot(dir, a, b);
+    // numerical fluxes at the line's ends, outward
+    double F2[2][5];
+#pragma unroll
+    for (int sd = 0; sd < 2; ++sd) {
+      const bool plus = sd;
+      if ((GEN == 2 || FVM) && kind[sd] == -2) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) F2[sd][v] = Ux[sd][v];
+        continue;
+      }
+      double Uw[5];
+      if (LGL) {
+        const int qo = slot(plus ? N : 0);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Uw[v] = sU[v * n3 + qo];
+      } else {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Uw[v] = 0.0;
+#pragma unroll 4
+        for (int m = 0; m < n; ++m) {
+          const int q = slot(m);
+          const double l = plus ? lp[m] : lm[m];
+#pragma unroll
+          for (int v = 0; v < 5; ++v) Uw[v] = fma(l, sU[v * n3 + q], Uw[v]);
+        }
+      }
+      // the master's normal and state go first (the stored normal is outward, the master's negated on
+      // the slave side)
+      const bool mst = GEN ? f2[sd].master : plus;
+      const double sg = mst ? 1.0 : -1.0;
+      const double nt[3] = {sg * nt2[sd][0], sg * nt2[sd][1], sg * nt2[sd][2]};
+      const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
+      const double ish = 1.0 / sh;
+      const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
+      const bool bnd = GEN && kind[sd] >= 0;
+      const bool outflow = bnd && kind[sd] == DG_BC_OUTFLOW;
+      const bool given = bnd && (kind[sd] == DG_BC_STATE || outflow);
+      const bool iso = bnd && kind[sd] == DG_BC_WALL_ISOTHERMAL;
+      const bool wall = bnd && (kind[sd] == DG_BC_WALL || iso);
+      if (bnd) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Ux[sd][v] = Uw[v];
+        if (outflow) {
+          // pressure outflow: the own trace's density and velocity with p_out
+          Ux[sd][4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
+        } else if (given) {
+#pragma unroll
+          for (int v = 0; v < 5; ++v) Ux[sd][v] = ph.ub[v];  // given outer state
+        } else if (wall) {
+          Ux[sd][1] = -Uw[1]; Ux[sd][2] = -Uw[2]; Ux[sd][3] = -Uw[3];  // no-slip wall: velocity reversed
+        } else {
+          mirror3(Ux[sd] + 1, nh);  // symmetry plane: mirror image of the inner state
+        }
+      }
+      const double *UM = mst ? Uw : Ux[sd], *US = mst ? Ux[sd] : Uw;
+      double F[5];
+      if constexpr (TP) riemann(ph, UM, US, nh, F);
+      else if (ph.rs == DG_RS_LLF) riemann_t<DG_RS_LLF>(ph, UM, US, nh, F);
+      else riemann_t<DG_RS_ROE>(ph, UM, US, nh, F);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) F2[sd][v] = (sg * sh) * F[v];
+      if (PFM) {
+        // minus the outward BR1 mean of the viscous flux: each side's flux carries its own outward normal
+        // (the two normals of a face are negatives of each other), a boundary side's is the mean itself
+#pragma unroll
+        for (int c = 0; c < 4; ++c) F2[sd][1 + c] -= bnd ? Vo[sd][c] : 0.5 * (Vo[sd][c] - Vn[sd][c]);
+      } else if (NS) {
+        // minus the BR1 mean of the viscous flux along this side's +xi direction (the split form's reading
+        // of the traces and boundary kinds), applied outward
+        const double sp = plus ? 1.0 : -1.0;
+        const double sn = (GEN && f2[sd].plus == plus) ? -1.0 : 1.0;
+        double V[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[sd][c] : 0.5 * (Vo[sd][c] + sn * Vn[sd][c]);
+        if (wall) {
+          // the momentum part of the inner flux; at an isothermal wall the inner heat flux (the energy flux
+          // minus the work of the stress)
+          V[3] = iso ? V[3] - (V[0] * Uw[1] + V[1] * Uw[2] + V[2] * Uw[3]) * (1.0 / Uw[0]) : 0.0;
+        } else if (bnd && !given) {
+          // symmetry plane: the normal part of the momentum flux
+          const double gm = V[0] * nh[0] + V[1] * nh[1] + V[2] * nh[2];
+          V[0] = gm * nh[0]; V[1] = gm * nh[1]; V[2] = gm * nh[2];
+          V[3] = 0.0;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) F2[sd][1 + c] -= sp * V[c];
+      }
+      __builtin_amdgcn_sched_barrier(0);  // one end at a time: both in flight spill
+    }
+    // surface integral (on LGL nodes lhat is non-zero at the ends only)
+#pragma unroll
+    for (int m = 0; m < n; ++m)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        if (LGL) acc[m][v] = m == 0 ? lhm[0] * F2[0][v] : (m == N ? lhp[N] * F2[1][v] : 0.0);
+        else acc[m][v] = fma(lhm[m], F2[0][v], lhp[m] * F2[1][v]);
+      }
+    double jl[3] = {0.0, 0.0, 0.0};
+    if constexpr (AFF) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) jl[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
+    }
+    const double *sJd = sJ + 3 * dir * n3;
+    // volume integral: node by node, its flux times the matrix's column into the line's sums
+#pragma unroll
+    for (int m = 0; m < n; ++m) {
+      const int q = slot(m);
+      double Uo[5], Fc[5], nv[3];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Uo[v] = sU[v * n3 + q];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) nv[d] = AFF ? jl[d] : sJd[d * n3 + q];
+      flux_c(Uo, to_prim(Uo, gm1), nv, Fc);
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        double c = M[i * n + m];
+        // strong form on LGL nodes: minus the face node's own interior flux (on LG nodes part of Tab::Ds)
+        if (FORM != 0 && LGL && i == m && m == 0) c += lhm[0];
+        if (FORM != 0 && LGL && i == m && m == N) c -= lhp[N];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) acc[i][v] = fma(c, Fc[v], acc[i][v]);
+      }
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);  // one node's flux at a time: more in flight spill
+    }
+  }
+  if constexpr (!PRE) load_epilogue();
+  // the three directions' sums, in order
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    __syncthreads();
+    if (act && dir == d) {
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        const int q = d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m));
+#pragma unroll
+        for (int v = 0; v < 5; ++v) sAcc[v * n3 + q] = d == 0 ? acc[m][v] : sAcc[v * n3 + q] + acc[m][v];
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (t >= n3) continue;
+    const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+    double *Oe = out + (size_t)e * 5 * n3;
+    double *Re = R + (size_t)e * 5 * n3;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      double r = sAcc[v * n3 + q];
+      if (NS && v > 0) r -= gd[it][v - 1];  // the viscous volume term, formed by the lifting kernel
+      const double ut = -r * sjq[it];
+      if (mode == 0) {
+        Oe[v * n3 + t] = ut;
+      } else {
+        // a = 0 (first stage) does not read R, so R may hold anything on entry
+        const double x = (ca != 0.0 ? ca * Rq[it][v] : 0.0) + dt * ut;
+        Re[v * n3 + t] = x;
+        Oe[v * n3 + t] = sU[v * n3 + q] + cb * x;
+      }
+    }
+  }
 }
 
 // ----------------------------------------------------------------------------- ensemble batch
@@ -2793,25 +3000,35 @@ __global__ void __launch_bounds__(Sz<N>::NT) k_fv_switch(Geo g, Phys ph, FvGeo f
 template <int N, bool LGL, bool NS, int FORM>
 static int launch_main_t(const Geo &g, const Phys &ph, const double *U, const double *G, double *out, double *R,
                          double a, double b, double dt, int mode, hipStream_t st) {
-  dim3 grid(xcd_grid(g.K)), block(Sz<N>::NT);
+  const dim3 grid(xcd_grid(g.K));
+  // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
+  const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
+  if constexpr (NS) {
+    if (lev == 2) {
+      const dim3 block(Sz<N>::NT);
+      if (g.Jc) hipLaunchKernelGGL((k_main<N, LGL, FORM, true>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt, mode);
+      else hipLaunchKernelGGL((k_main<N, LGL, FORM, false>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt, mode);
+      DG_CHECK_LAUNCH();
+      return DG_OK;
+    }
+  }
+  const dim3 block(SplitSz<N>::NT);
   const bool tp = ph.rs >= DG_RS_VOLFLUX;
 #define DG_KMT(G_, F_, A_, T_) \
-  hipLaunchKernelGGL((k_main<N, LGL, NS, FORM, G_, F_, A_, T_>), grid, block, 0, st, g, ph, U, G, out, R, a, b, dt, mode)
+  hipLaunchKernelGGL((k_line<N, LGL, NS, FORM, G_, F_, A_, T_>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode)
 #define DG_KM(G_, F_) \
   do { \
     if (g.Jc) { if (tp) DG_KMT(G_, F_, true, true); else DG_KMT(G_, F_, true, false); } \
     else { if (tp) DG_KMT(G_, F_, false, true); else DG_KMT(G_, F_, false, false); } \
   } while (0)
   if constexpr (!NS) {
-    if (g.fvflag) {
-      DG_KM(1, true);
-      DG_CHECK_LAUNCH();
-      return DG_OK;
-    }
+    if (g.fvflag) DG_KM(1, true);
+    else if (lev == 2) DG_KM(2, false);
+    else if (lev == 1) DG_KM(1, false);
+    else DG_KM(0, false);
+  } else {
+    if (lev == 1) DG_KM(1, false); else DG_KM(0, false);
   }
-  // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
-  const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
-  if (lev == 0) DG_KM(0, false); else if (lev == 1) DG_KM(1, false); else DG_KM(2, false);
 #undef DG_KM
 #undef DG_KMT
   DG_CHECK_LAUNCH();
