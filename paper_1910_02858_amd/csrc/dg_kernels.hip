@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dg_internal.h"
+#include "dg_lines.h"
 
 // waves per SIMD the split-form kernel is built for: 2 (256 registers: a line of 8 nodes holds 112
 // doubles); at N = 8 one element's LDS fills the CU and one wave per SIMD is all there is
@@ -353,21 +354,6 @@ __device__ __forceinline__ void contra_visc(double *acc, const double *jo, doubl
     const double q = fma(dT2, nv[2], fma(dT1, nv[1], dT0 * nv[0]));
     acc[dir * 4 + 3] = fma(ph.kappa, q, fma(acc[dir * 4 + 2], w, fma(acc[dir * 4 + 1], v, acc[dir * 4] * u)));
   }
-}
-
-// LDS slot of node (i, j, k) in one component array of the viscous divergence stage.  For n = 8
-// the index bits are swizzled so that the 64 lanes that read the m-th node of 64 different lines
-// hit distinct banks in each direction (and in node order): i is XORed with two bits of j and k,
-// j with the low bits of k.
-template <int n> __device__ __forceinline__ int div_slot(int i, int j, int k) {
-  if constexpr (n == 8) return (i ^ ((j >> 2) | ((k & 3) << 1))) + 8 * (j ^ (k & 3)) + 64 * k;
-  else return i + n * (j + n * k);
-}
-
-// Constant metric terms of an affine element (Geo::Jc) through the scalar cache.
-typedef const __attribute__((address_space(4))) double *AffineConst;
-__device__ __forceinline__ AffineConst affine_const(const Geo &g, int e) {
-  return (AffineConst)(g.Jc + (size_t)__builtin_amdgcn_readfirstlane(e) * AFFINE_DOUBLES);
 }
 
 // sm: the slot's LiftLds<N> regions, contiguous (W, JA, WS).
@@ -1313,28 +1299,6 @@ __device__ __forceinline__ void riemann_vf(const Phys &ph, const double *UL, con
   }
 }
 
-// LDS slots (div_slot) of the nodes of one line, without a branch on its direction: n = 8's swizzle is
-// linear over the index bits, slot = base ^ (contribution of the position's bits); else base + m stride.
-template <int n> struct LineSlots {
-  int base, s1, s2, s4;
-  __device__ __forceinline__ LineSlots(int dir, int a, int b) {
-    const int i = dir == 0 ? 0 : a, j = dir == 0 ? a : (dir == 1 ? 0 : b), k = dir == 2 ? 0 : b;
-    base = div_slot<n>(i, j, k);
-    if constexpr (n == 8) {
-      s1 = dir == 0 ? 1 : (dir == 1 ? 8 : 74);
-      s2 = dir == 0 ? 2 : (dir == 1 ? 16 : 148);
-      s4 = dir == 0 ? 4 : (dir == 1 ? 33 : 256);
-    } else {
-      s1 = dir == 0 ? 1 : (dir == 1 ? n : n * n);
-      s2 = s4 = 0;
-    }
-  }
-  __device__ __forceinline__ int operator()(int m) const {
-    if constexpr (n == 8) return base ^ ((m & 1 ? s1 : 0) ^ (m & 2 ? s2 : 0) ^ (m & 4 ? s4 : 0));
-    else return base + m * s1;
-  }
-};
-
 // LDS sizes (doubles) of one element in the split-form kernel: the conservative state (5 per node), the
 // two-point state rho, u, v, w, beta|H (5 per node) and the metric terms Ja^i_d (9 per node; none on
 // affine elements); the accumulated result takes the place of the metric terms (affine: of the two-point
@@ -1342,12 +1306,6 @@ template <int n> struct LineSlots {
 template <int N> struct SplitLds {
   static constexpr int n = N + 1, n2 = n * n, n3 = n2 * n;
   static constexpr int A = 19 * n3, AFFINE = 10 * n3;
-};
-
-// Lanes of one element in the split-form kernel: one per line of the three directions, 3 n^2 of them.
-template <int N> struct SplitSz {
-  static constexpr int n = N + 1, NL = 3 * n * n;
-  static constexpr int NT = (NL + 63) / 64 * 64;
 };
 
 struct LineNode {  // a node of a line: its two-point state and the line direction's metric terms

@@ -1,0 +1,51 @@
+// Device helpers of the kernels that take one lane per line of an element: LDS slots, lanes per element, the
+// constants of affine elements.
+#pragma once
+#include "dg_internal.h"
+
+namespace dg {
+
+// LDS slot of node (i, j, k) in one component array.  For n = 8
+// the index bits are swizzled so that the 64 lanes that read the m-th node of 64 different lines
+// hit distinct banks in each direction (and in node order): i is XORed with two bits of j and k,
+// j with the low bits of k.
+template <int n> __device__ __forceinline__ int div_slot(int i, int j, int k) {
+  if constexpr (n == 8) return (i ^ ((j >> 2) | ((k & 3) << 1))) + 8 * (j ^ (k & 3)) + 64 * k;
+  else return i + n * (j + n * k);
+}
+
+// Constant metric terms of an affine element (Geo::Jc) through the scalar cache.
+typedef const __attribute__((address_space(4))) double *AffineConst;
+__device__ __forceinline__ AffineConst affine_const(const Geo &g, int e) {
+  return (AffineConst)(g.Jc + (size_t)__builtin_amdgcn_readfirstlane(e) * AFFINE_DOUBLES);
+}
+
+// LDS slots (div_slot) of the nodes of one line, without a branch on its direction: n = 8's swizzle is
+// linear over the index bits, slot = base ^ (contribution of the position's bits); else base + m stride.
+template <int n> struct LineSlots {
+  int base, s1, s2, s4;
+  __device__ __forceinline__ LineSlots(int dir, int a, int b) {
+    const int i = dir == 0 ? 0 : a, j = dir == 0 ? a : (dir == 1 ? 0 : b), k = dir == 2 ? 0 : b;
+    base = div_slot<n>(i, j, k);
+    if constexpr (n == 8) {
+      s1 = dir == 0 ? 1 : (dir == 1 ? 8 : 74);
+      s2 = dir == 0 ? 2 : (dir == 1 ? 16 : 148);
+      s4 = dir == 0 ? 4 : (dir == 1 ? 33 : 256);
+    } else {
+      s1 = dir == 0 ? 1 : (dir == 1 ? n : n * n);
+      s2 = s4 = 0;
+    }
+  }
+  __device__ __forceinline__ int operator()(int m) const {
+    if constexpr (n == 8) return base ^ ((m & 1 ? s1 : 0) ^ (m & 2 ? s2 : 0) ^ (m & 4 ? s4 : 0));
+    else return base + m * s1;
+  }
+};
+
+// Lanes of one element in the kernels that take one lane per line: the lines of the three directions, 3 n^2.
+template <int N> struct SplitSz {
+  static constexpr int n = N + 1, NL = 3 * n * n;
+  static constexpr int NT = (NL + 63) / 64 * 64;
+};
+
+}  // namespace dg

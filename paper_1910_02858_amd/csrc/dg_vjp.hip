@@ -28,6 +28,7 @@
 
 #include "dg_flux.h"
 #include "dg_internal.h"
+#include "dg_lines.h"
 
 // minimum waves per SIMD of the operator's vector-Jacobian kernel (caps its registers)
 #ifndef DG_VJP_MINB
@@ -49,7 +50,8 @@ template <int n> __device__ __forceinline__ int vline_node(int dn, int a, int b,
   return dn == 0 ? (m + n * (a + n * b)) : (dn == 1 ? (a + n * (m + n * b)) : (a + n * (b + n * m)));
 }
 
-// ---------------------------------------------------------------------------------- main
+// ---------------------------------------------------------------------------------- main, EC and central flux
+// One node per lane; the kinetic-energy preserving flux takes k_vjp_line below.
 // GEN: the mesh has face codes (faces on any side, in any orientation, symmetry planes), and
 // every neighbour value is read at the neighbour's matching face point.  The face terms
 // themselves need no change: with the two copies of a face flux related by the antisymmetry of
@@ -67,18 +69,18 @@ __global__ void __launch_bounds__(VSz<N>::NT, DG_VJP_MINB) k_vjp_main(Geo g, Phy
   constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = S::NT;
   constexpr int NF = NS ? 17 : 5;  // results per face point: primitive adjoint, gradient adjoint
   constexpr int NX = (NF * 6 * n2 > 9 * n3) ? NF * 6 * n2 : 9 * n3;
-  __shared__ double sQ[6 * n3];  // primitive state and total enthalpy
+  __shared__ double sQ[5 * n3];  // primitive state
   __shared__ double sA[5 * n3];  // Abar = -(1/J) Utbar
   // region X: first the face-point results, then H = (1/J) Gbar (9 per node, Navier-Stokes),
   // then Ja^dir of the current direction (3 per node) and the partner shares of the pair
-  // rounds (6 per node: primitive adjoint and enthalpy adjoint)
+  // rounds (5 per node)
   static_assert(!NS || NX >= 9 * n3, "region X holds H");
   static_assert(NX >= 9 * n3, "region X holds Ja^dir and the partner shares");
   // where the LDS allows it, all metric terms (9 per node) and the momentum part of the kept
   // viscous fluxes (9 per node) are staged once at the start, so that no later phase waits on a
   // global load after a barrier
   constexpr int NST = 9 + (NS ? 9 : 0);
-  constexpr bool STAGE = DG_VJP_STAGE && (11 + NST) * n3 + NX + 2 * n * n <= 160 * 1024 / 8;
+  constexpr bool STAGE = DG_VJP_STAGE && (10 + NST) * n3 + NX + 2 * n * n <= 160 * 1024 / 8;
   __shared__ double sX[NX];
   __shared__ double sD[n * n], sDh[n * n];
   __shared__ double sM[STAGE ? NST * n3 : 1];  // Ja^i_d at (i*3+d)*n3, then Fv^dir_c at (9+dir*3+c)*n3
@@ -120,7 +122,6 @@ __global__ void __launch_bounds__(VSz<N>::NT, DG_VJP_MINB) k_vjp_main(Geo g, Phy
     for (int v = 0; v < 5; ++v) Uq[v] = Ue[v * n3 + t];
     q = dgf::prim(Uq, gm1);
     sQ[t] = q.r; sQ[n3 + t] = q.u; sQ[2 * n3 + t] = q.v; sQ[3 * n3 + t] = q.w; sQ[4 * n3 + t] = q.p;
-    sQ[5 * n3 + t] = dgf::enthalpy(q, g1);
     const double sj = sJe[t];
 #pragma unroll
     for (int v = 0; v < 5; ++v) sA[v * n3 + t] = -sj * Utb[((size_t)e * 5 + v) * n3 + t];
@@ -370,10 +371,7 @@ __global__ void __launch_bounds__(VSz<N>::NT, DG_VJP_MINB) k_vjp_main(Geo g, Phy
       dgf::lift_vars_adj(q, ph.R, Wb, pl);
     }
   }
-  // ---- volume: pairs and diagonal, direction by direction.  With the KEP flux the adjoint of
-  // this node's total enthalpy is summed over all pairs and mapped once at the end.
-  const double Ht = act ? sQ[5 * n3 + t] : 0.0;
-  double Htb = 0.0;
+  // ---- volume: pairs and diagonal, direction by direction
   // the epilogue's loads are issued before the rounds
   double *Ube = Ub + (size_t)e * 5 * n3;
   double ub0[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
@@ -414,7 +412,6 @@ __global__ void __launch_bounds__(VSz<N>::NT, DG_VJP_MINB) k_vjp_main(Geo g, Phy
           const int qp = base + jp * str;
           dgf::P r;
           r.r = sQ[qp]; r.u = sQ[n3 + qp]; r.v = sQ[2 * n3 + qp]; r.w = sQ[3 * n3 + qp]; r.p = sQ[4 * n3 + qp];
-          const double Hr = sQ[5 * n3 + qp];  // the partner's total enthalpy
           const double nm[3] = {0.5 * (nvo[0] + sJd[qp]), 0.5 * (nvo[1] + sJd[n3 + qp]),
                                 0.5 * (nvo[2] + sJd[2 * n3 + qp])};
           const double Dij2 = 2.0 * sD[id * n + jp], Dji2 = 2.0 * sD[jp * n + id];
@@ -422,21 +419,16 @@ __global__ void __launch_bounds__(VSz<N>::NT, DG_VJP_MINB) k_vjp_main(Geo g, Phy
 #pragma unroll
           for (int v = 0; v < 5; ++v) Fb[v] = Dij2 * Ao[v] + (half ? 0.0 : Dji2 * sA[v * n3 + qp]);
           dgf::PA pr = dgf::zero_pa();
-          double Hrb = 0.0;
-          if (vf == 0) {
-            dgf::kep_flux_adj_h(q, r, Ht, Hr, nm, Fb, pa, pr, Htb, Hrb);
-          } else {
-            r.ir = 1.0 / r.r;  // the central flux's enthalpies need it
-            dgf::pair_flux_adj(vf, q, r, nm, g1, Fb, pa, pr);
-          }
+          r.ir = 1.0 / r.r;  // the central flux's enthalpies need it
+          dgf::pair_flux_adj(vf, q, r, nm, g1, Fb, pa, pr);
           // every node receives exactly one partner share per round
           sPA[qp] = pr.r; sPA[n3 + qp] = pr.u; sPA[2 * n3 + qp] = pr.v; sPA[3 * n3 + qp] = pr.w;
-          sPA[4 * n3 + qp] = pr.p; sPA[5 * n3 + qp] = Hrb;
+          sPA[4 * n3 + qp] = pr.p;
         }
         __syncthreads();
         if (act) {
           pa.r += sPA[t]; pa.u += sPA[n3 + t]; pa.v += sPA[2 * n3 + t]; pa.w += sPA[3 * n3 + t];
-          pa.p += sPA[4 * n3 + t]; Htb += sPA[5 * n3 + t];
+          pa.p += sPA[4 * n3 + t];
         }
         __syncthreads();
       }
@@ -451,13 +443,452 @@ __global__ void __launch_bounds__(VSz<N>::NT, DG_VJP_MINB) k_vjp_main(Geo g, Phy
     }
   }
   if (act) {
-    dgf::enthalpy_adj(q, g1, Htb, pa);
     dgf::PA pt;
     pt.r = fma(scale, pa.r, pl.r); pt.u = fma(scale, pa.u, pl.u); pt.v = fma(scale, pa.v, pl.v);
     pt.w = fma(scale, pa.w, pl.w); pt.p = fma(scale, pa.p, pl.p);
     dgf::cons_adj(q, gm1, pt, cb);
 #pragma unroll
     for (int v = 0; v < 5; ++v) Ube[v * n3 + t] = ub0[v] + cb[v];
+  }
+}
+
+// ---------------------------------------------------------------------------------- main, KEP flux
+// The same reverse for the kinetic-energy preserving two-point flux, one lane per line (as the split-form
+// operator): the lane evaluates the adjoints of the numerical fluxes at its line's ends, of each unordered
+// pair of its nodes once, and the line contractions of the viscous terms and of the transposed lifting.
+// What bounds it: with one node per lane a third of the LDS accesses and 18 of 24 barriers were the exchange
+// of the pairs' partner shares; vector instructions took 49 % and the LDS 46 % of the time at two waves per
+// SIMD.  One product (Navier-Stokes, Roe, with its lifting and face kernels): N = 5, 24^3 curved 802 -> 580 us;
+// N = 7, 16^3 curved 662 -> 485, affine 662 -> 429; N = 3, 32^3 579 -> 416; Euler N = 4, 24^3 177 -> 152.
+// The pair's adjoint is the same for both of its nodes: with sums over the pair r2, u2, H2, nS = n_q + n_p,
+// f = D_qp Abar_q + D_pq Abar_p, s = u2 . nS and g = 2 f_0 + f_m . u2 + f_4 H2 each node receives
+// (1/8) (g s, r2 (s f_m + g nS), 4 f_m . nS, r2 s f_4) in (rho, u, p, H).  The diagonal of D and the interior
+// surface flux cancel in the Euler part (2 D_ii = +-lhat on LGL nodes).
+template <int N> struct VjpLds {  // doubles of one element: rho, u, v, w, H and Abar (10 per node), metric terms (9)
+  static constexpr int n3 = (N + 1) * (N + 1) * (N + 1);
+  // Navier-Stokes: the viscous adjoints (12 per node) take the place of the state and Abar and need two more;
+  // where those cost a workgroup per CU they lie over the first two metric terms, which are then read again
+  static constexpr bool TIGHT = 160 * 1024 / (21 * n3 * 8) < 160 * 1024 / (19 * n3 * 8);
+};
+
+template <int N, bool NS, bool GEN, bool AFF>
+__global__ void __launch_bounds__(SplitSz<N>::NT, 2)
+    k_vjp_line(Geo g, Phys ph, const double *__restrict__ U, const double *__restrict__ G,
+               const double *__restrict__ Utb, double *__restrict__ Ub, double *__restrict__ Pf, double scale,
+               int accumulate) {
+  constexpr int n = N + 1, n2 = n * n, n3 = n2 * n, NT = SplitSz<N>::NT, IT = (n3 + NT - 1) / NT;
+  constexpr bool TIGHT = NS && !AFF && VjpLds<N>::TIGHT;
+  constexpr int J0 = (NS && !TIGHT) ? 12 : 10;  // first component of the metric terms
+  __shared__ double sm[(AFF ? (NS ? 12 : 10) : J0 + 9) * n3];
+  double *sQ = sm, *sA = sm + 5 * n3, *sJ = sm + J0 * n3;  // node slots: div_slot
+  const int e = xcd_element(blockIdx.x, g.K), lane = threadIdx.x;
+  if (e >= g.K) return;
+  AffineConst jc = nullptr;
+  if constexpr (AFF) jc = affine_const(g, e);
+  const double gamma = ph.gamma, gm1 = gamma - 1.0, g1 = gamma / gm1;
+  typedef const __attribute__((address_space(4))) double *Scal;
+  const Scal D = (Scal)g.tab->D, Dh = (Scal)g.tab->Dh;
+  const double lh = g.tab->lhp[N];  // lhat at a face node (the same value at both ends)
+  const double *Ue = U + (size_t)e * 5 * n3;
+  const double *Ge = G + (size_t)e * 12 * n3;
+  const double *Jae = g.Ja + (size_t)e * 9 * n3;
+  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(lane / n2) : lane / n2;
+  const int ab = lane - dir * n2, a = ab % n, b = ab / n;
+  const bool act = lane < 3 * n2;
+  // ---- loads: the neighbours' indices, the element's arrays, both sides' face nodes
+  int nb2[2] = {0, 0};
+  NbFace f2[2];
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd)
+    if (act) {
+      nb2[sd] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
+      f2[sd] = nbr_face<n, GEN>(g, e, 2 * dir + sd, a, b);
+    }
+  double U0[IT][5], Aq[IT][5], Jq[IT][9], sj[IT];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (t < n3) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) U0[it][v] = Ue[v * n3 + t];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Aq[it][v] = Utb[((size_t)e * 5 + v) * n3 + t];
+      sj[it] = AFF ? jc[9] : g.sJ[(size_t)e * n3 + t];
+#pragma unroll
+      for (int c = 0; c < 9 && !AFF; ++c) Jq[it][c] = Jae[c * n3 + t];
+    }
+  }
+  double Uw2[2][5], Ux2[2][5], Ax2[2][5], sx2[2];
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd)
+    if (act) {
+      const bool bnd = GEN && f2[sd].bnd;
+      const int nb = bnd ? e : nb2[sd];  // a boundary side reads nothing of a neighbour
+      const int qo = vline_node<n>(dir, a, b, sd ? N : 0);
+      const int qn = GEN ? vline_node<n>(f2[sd].dn, f2[sd].a, f2[sd].b, f2[sd].plus ? N : 0)
+                         : vline_node<n>(dir, a, b, sd ? 0 : N);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        Uw2[sd][v] = Ue[v * n3 + qo];
+        Ux2[sd][v] = U[((size_t)nb * 5 + v) * n3 + qn];
+        Ax2[sd][v] = Utb[((size_t)nb * 5 + v) * n3 + qn];
+      }
+      sx2[sd] = AFF ? g.Jc[(size_t)nb * AFFINE_DOUBLES + 9] : g.sJ[(size_t)nb * n3 + qn];
+    }
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (t < n3) {
+      const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+      const dgf::P p = dgf::prim(U0[it], gm1);
+      sQ[q] = p.r; sQ[n3 + q] = p.u; sQ[2 * n3 + q] = p.v; sQ[3 * n3 + q] = p.w;
+      sQ[4 * n3 + q] = dgf::enthalpy(p, g1);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sA[v * n3 + q] = -sj[it] * Aq[it][v];
+#pragma unroll
+      for (int c = 0; c < 9 && !AFF; ++c) sJ[c * n3 + q] = Jq[it][c];
+    }
+  }
+  __syncthreads();
+  const LineSlots<n> slot(act ? dir : 0, act ? a : 0, act ? b : 0);
+  const double *sJd = sJ + 3 * (act ? dir : 0) * n3;
+  double jl[3] = {0.0, 0.0, 0.0};
+  if constexpr (AFF) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) jl[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
+  }
+  auto metric = [&](int d, int q) -> double {
+    if constexpr (AFF) return jl[d];
+    else return sJd[d * n3 + q];
+  };
+  double acc[n][6];          // adjoints of rho, u, v, w, p, H of the line's nodes
+  double fv[NS ? n : 1][4];  // adjoints of the viscous fluxes along the line's direction
+  if (act) {
+    // ---- faces: Fbar = lhat (Abar_master - Abar_slave); own-trace derivative only
+    double pe[2][5], fe[2][4];
+#pragma unroll
+    for (int sd = 0; sd < 2; ++sd) {
+      const bool plus = sd;
+      const int qo = slot(plus ? N : 0);
+      const bool bnd = GEN && f2[sd].bnd;
+      const bool outflow = bnd && f2[sd].kind == DG_BC_OUTFLOW;
+      const bool given = bnd && (f2[sd].kind == DG_BC_STATE || outflow);
+      const bool iso = bnd && f2[sd].kind == DG_BC_WALL_ISOTHERMAL;
+      const bool wall = bnd && (f2[sd].kind == DG_BC_WALL || iso);
+      double *Uw = Uw2[sd], *Ux = Ux2[sd];
+      // normal along +xi_dir scaled by s-hat: this element's Ja^dir at the face node
+      const double nt[3] = {metric(0, qo), metric(1, qo), metric(2, qo)};
+      const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
+      const double ish = 1.0 / sh;
+      const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
+      if (outflow) {
+        // pressure outflow: the own trace's density and velocity with p_out
+        Ux[0] = Uw[0]; Ux[1] = Uw[1]; Ux[2] = Uw[2]; Ux[3] = Uw[3];
+        Ux[4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
+      } else if (given) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Ux[v] = ph.ub[v];  // given outer state, independent of U
+      } else if (wall) {
+        // no-slip wall: the outer state is the own trace with the velocity reversed
+        Ux[0] = Uw[0]; Ux[1] = -Uw[1]; Ux[2] = -Uw[2]; Ux[3] = -Uw[3]; Ux[4] = Uw[4];
+      } else if (bnd) {
+        // symmetry plane: the outer state is the mirrored own trace
+        const double mn = 2.0 * (Uw[1] * nh[0] + Uw[2] * nh[1] + Uw[3] * nh[2]);
+        Ux[0] = Uw[0]; Ux[4] = Uw[4];
+        Ux[1] = Uw[1] - mn * nh[0]; Ux[2] = Uw[2] - mn * nh[1]; Ux[3] = Uw[3] - mn * nh[2];
+      }
+      double Fb[5], Fbs[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        const double ao = sA[v * n3 + qo], ax = bnd ? 0.0 : -sx2[sd] * Ax2[sd][v];
+        Fb[v] = lh * (plus ? (ao - ax) : (ax - ao));
+        Fbs[v] = Fb[v] * sh;
+      }
+      const double *UM = plus ? Uw : Ux, *US = plus ? Ux : Uw;
+      const dgf::P PM = dgf::prim(UM, gm1), PS = dgf::prim(US, gm1);
+      dgf::PA aM = dgf::zero_pa(), aS = dgf::zero_pa();
+      dgf::riemann_adj_prim(ph.rs, 0, PM, PS, UM, US, nh, gamma, Fbs, aM, aS);
+      dgf::PA pc = plus ? aM : aS;
+      const dgf::PA ao = plus ? aS : aM;
+      const dgf::P Po = plus ? PM : PS;
+      if (outflow) {
+        // the outer argument's density and velocity are the own trace's, its pressure is fixed
+        pc.r += ao.r; pc.u += ao.u; pc.v += ao.v; pc.w += ao.w;
+      } else if (wall) {
+        // the outer argument is the own trace with the velocity reversed
+        pc.r += ao.r; pc.p += ao.p;
+        pc.u -= ao.u; pc.v -= ao.v; pc.w -= ao.w;
+      } else if (bnd && !given) {
+        // the outer argument is the mirror image of the own trace: its adjoint comes back mirrored
+        const double an = 2.0 * (ao.u * nh[0] + ao.v * nh[1] + ao.w * nh[2]);
+        pc.r += ao.r; pc.p += ao.p;
+        pc.u += ao.u - an * nh[0]; pc.v += ao.v - an * nh[1]; pc.w += ao.w - an * nh[2];
+      }
+      if (NS) {
+        // the face's own viscous flux, along the same Ja^dir as the node's: F contains -1/2 Fv . nt
+#pragma unroll
+        for (int c = 0; c < 4; ++c) fe[sd][c] = -0.5 * Fb[1 + c];
+        if (given) {
+          // given outer state: the term is -g, the whole own flux
+#pragma unroll
+          for (int c = 0; c < 4; ++c) fe[sd][c] = -Fb[1 + c];
+        } else if (iso) {
+          // isothermal wall: the terms are -g_m for the momentum and -(g_E - g_m . u) for the energy, with
+          // u this node's velocity
+          const int qg = vline_node<n>(dir, a, b, plus ? N : 0);
+          fe[sd][0] = -Fb[1] + Fb[4] * Po.u; fe[sd][1] = -Fb[2] + Fb[4] * Po.v; fe[sd][2] = -Fb[3] + Fb[4] * Po.w;
+          fe[sd][3] = -Fb[4];
+          pc.u += Fb[4] * Ge[(dir * 4) * n3 + qg]; pc.v += Fb[4] * Ge[(dir * 4 + 1) * n3 + qg];
+          pc.w += Fb[4] * Ge[(dir * 4 + 2) * n3 + qg];
+        } else if (wall) {
+          // no-slip wall: the term is -g for the momentum, nothing for the energy
+          fe[sd][0] = -Fb[1]; fe[sd][1] = -Fb[2]; fe[sd][2] = -Fb[3]; fe[sd][3] = 0.0;
+        } else if (bnd) {
+          // symmetry plane: the term is -(g.nh) nh of the own momentum flux g, no energy part
+          const double fn_ = Fb[1] * nh[0] + Fb[2] * nh[1] + Fb[3] * nh[2];
+          fe[sd][0] = -fn_ * nh[0]; fe[sd][1] = -fn_ * nh[1]; fe[sd][2] = -fn_ * nh[2]; fe[sd][3] = 0.0;
+        }
+        // the interior face term -F_int contributes +lhat sg Abar
+#pragma unroll
+        for (int c = 0; c < 4; ++c) fe[sd][c] += (plus ? lh : -lh) * sA[(1 + c) * n3 + qo];
+      }
+      pe[sd][0] = pc.r; pe[sd][1] = pc.u; pe[sd][2] = pc.v; pe[sd][3] = pc.w; pe[sd][4] = pc.p;
+      __builtin_amdgcn_sched_barrier(0);  // one end at a time: both in flight spill
+    }
+#pragma unroll
+    for (int m = 0; m < n; ++m)
+#pragma unroll
+      for (int v = 0; v < 6; ++v) acc[m][v] = 0.0;
+    // ---- pairs
+    struct Nd { double s[5], A[5], nv[3]; };
+    auto node = [&](int m) -> Nd {
+      Nd x;
+      const int q = slot(m);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) { x.s[v] = sQ[v * n3 + q]; x.A[v] = sA[v * n3 + q]; }
+#pragma unroll
+      for (int d = 0; d < 3; ++d) x.nv[d] = metric(d, q);
+      return x;
+    };
+#pragma unroll
+    for (int i = 0; i + 1 < n; ++i) {
+      const Nd X = node(i);
+#pragma unroll
+      for (int j = i + 1; j < n; ++j) {
+        const Nd Y = node(j);
+        const double Dij = D[i * n + j], Dji = D[j * n + i];
+        const double r2 = X.s[0] + Y.s[0], u2 = X.s[1] + Y.s[1], v2 = X.s[2] + Y.s[2], w2 = X.s[3] + Y.s[3];
+        const double H2 = X.s[4] + Y.s[4];
+        const double nS[3] = {X.nv[0] + Y.nv[0], X.nv[1] + Y.nv[1], X.nv[2] + Y.nv[2]};
+        double f[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) f[v] = fma(Dij, X.A[v], Dji * Y.A[v]);
+        const double s = fma(u2, nS[0], fma(v2, nS[1], w2 * nS[2]));
+        const double gg = fma(2.0, f[0], fma(f[1], u2, fma(f[2], v2, fma(f[3], w2, f[4] * H2))));
+        const double rs = r2 * s, rg = r2 * gg;
+        const double pp = fma(f[1], nS[0], fma(f[2], nS[1], f[3] * nS[2]));
+        auto add = [&](double *x) {
+          x[0] = fma(gg, s, x[0]);
+#pragma unroll
+          for (int d = 0; d < 3; ++d) x[1 + d] = fma(rs, f[1 + d], fma(rg, nS[d], x[1 + d]));
+          x[4] += pp;
+          x[5] = fma(rs, f[4], x[5]);
+        };
+        add(acc[i]);
+        add(acc[j]);
+        if ((j - i) % 2 == 0) __builtin_amdgcn_sched_barrier(0);  // at most two pairs in flight
+      }
+      asm volatile("" ::: "memory");  // the next row's partners are read again, not kept
+    }
+#pragma unroll
+    for (int m = 0; m < n; ++m) {
+#pragma unroll
+      for (int v = 0; v < 6; ++v) acc[m][v] *= v == 4 ? 0.5 : 0.125;
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) { acc[0][v] += pe[0][v]; acc[N][v] += pe[1][v]; }
+    // ---- viscous volume term: acc_m -= sum_i D_mi Fv_i gives Fvbar_i = -sum_m D_mi Abar_m
+    if constexpr (NS) {
+#pragma unroll
+      for (int m = 0; m < n; ++m)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) fv[m][c] = m == 0 ? fe[0][c] : (m == N ? fe[1][c] : 0.0);
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        const int q = slot(i);
+        double A[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) A[c] = sA[(1 + c) * n3 + q];
+#pragma unroll
+        for (int m = 0; m < n; ++m) {
+          const double d = -D[i * n + m];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) fv[m][c] = fma(d, A[c], fv[m][c]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  double pv[IT][3];        // the viscous fluxes' adjoint in the node's velocity
+  double W[NS ? n : 1][4];  // the transposed lifting's Wbar of the line's nodes
+  if constexpr (NS) {
+    __syncthreads();
+    if (act) {
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        const int q = slot(m);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sm[(dir * 4 + c) * n3 + q] = fv[m][c];
+      }
+    }
+    __syncthreads();
+    // ---- node by node: the viscous fluxes' adjoint in the gradients, H = (1/J) scale Gbar.  The velocity block
+    // of H is symmetric: six distinct entries (00, 11, 22, 01, 02, 12) and the three of the temperature.
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int t = lane + it * NT;
+      pv[it][0] = pv[it][1] = pv[it][2] = 0.0;
+      if (t < n3) {
+        const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+        const double ir = 1.0 / Ue[t];
+        const double u[3] = {Ue[n3 + t] * ir, Ue[2 * n3 + t] * ir, Ue[3 * n3 + t] * ir};
+        const double sj = (AFF ? jc[9] : g.sJ[(size_t)e * n3 + t]) * scale;
+        double T[3][3], k[3] = {0.0, 0.0, 0.0}, J01[2] = {0.0, 0.0};
+#pragma unroll
+        for (int x = 0; x < 3; ++x)
+#pragma unroll
+          for (int y = 0; y < 3; ++y) T[x][y] = 0.0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          double nv[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            if constexpr (AFF) nv[c] = jc[3 * d + c];
+            else nv[c] = (TIGHT && 3 * d + c < 2) ? Jae[(3 * d + c) * n3 + t] : sJ[(3 * d + c) * n3 + q];
+          }
+          if (TIGHT && d == 0) { J01[0] = nv[0]; J01[1] = nv[1]; }
+          const double F4 = sm[(d * 4 + 3) * n3 + q];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const double bm = fma(F4, u[c], sm[(d * 4 + c) * n3 + q]);
+#pragma unroll
+            for (int y = 0; y < 3; ++y) T[c][y] = fma(bm, nv[y], T[c][y]);
+            k[c] = fma(F4, nv[c], k[c]);
+            pv[it][c] = fma(F4, Ge[(d * 4 + c) * n3 + t], pv[it][c]);
+          }
+        }
+        const double ms = ph.mu * sj, tr = (2.0 / 3.0) * (T[0][0] + T[1][1] + T[2][2]), ks = ph.kappa * sj;
+        sm[q] = ms * fma(2.0, T[0][0], -tr);
+        sm[n3 + q] = ms * fma(2.0, T[1][1], -tr);
+        sm[2 * n3 + q] = ms * fma(2.0, T[2][2], -tr);
+        sm[3 * n3 + q] = ms * (T[0][1] + T[1][0]);
+        sm[4 * n3 + q] = ms * (T[0][2] + T[2][0]);
+        sm[5 * n3 + q] = ms * (T[1][2] + T[2][1]);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) sm[(6 + d) * n3 + q] = ks * k[d];
+        if (TIGHT) { sJ[q] = J01[0]; sJ[n3 + q] = J01[1]; }
+      }
+    }
+    __syncthreads();
+    // ---- lifting transposed, own part: Wbar = Ja^dir . (Dhat^T H) along the line and the own face terms, which
+    // also go to the face array for the neighbours
+    if (act) {
+#pragma unroll
+      for (int m = 0; m < n; ++m)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) W[m][v] = 0.0;
+#pragma unroll
+      for (int sd = 0; sd < 2; ++sd) {
+        const int m = sd ? N : 0, q = slot(m);
+        const double c0 = (sd ? 0.5 : -0.5) * lh;
+        const double nv[3] = {metric(0, q), metric(1, q), metric(2, q)};
+        double h[9];
+#pragma unroll
+        for (int c = 0; c < 9; ++c) h[c] = sm[c * n3 + q];
+        const double f[4] = {c0 * (nv[0] * h[0] + nv[1] * h[3] + nv[2] * h[4]),
+                             c0 * (nv[0] * h[3] + nv[1] * h[1] + nv[2] * h[5]),
+                             c0 * (nv[0] * h[4] + nv[1] * h[5] + nv[2] * h[2]),
+                             c0 * (nv[0] * h[6] + nv[1] * h[7] + nv[2] * h[8])};
+        double *pf = Pf + ((size_t)e * 6 + 2 * dir + sd) * 4 * n2 + ab;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          W[m][v] = f[v];
+          pf[v * n2] = f[v];
+        }
+      }
+      // one entry of H after the other: (Wbar component, normal component) pairs it enters
+#pragma unroll
+      for (int c = 0; c < 9; ++c) {
+        constexpr int wa[9] = {0, 1, 2, 0, 0, 1, 3, 3, 3}, na[9] = {0, 1, 2, 1, 2, 2, 0, 1, 2};
+        constexpr int wb[9] = {-1, -1, -1, 1, 2, 2, -1, -1, -1}, nb[9] = {0, 0, 0, 0, 0, 1, 0, 0, 0};
+        double hs[n];
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+          const double h = sm[c * n3 + slot(i)];
+#pragma unroll
+          for (int m = 0; m < n; ++m) hs[m] = i == 0 ? Dh[m] * h : fma(Dh[i * n + m], h, hs[m]);
+        }
+#pragma unroll
+        for (int m = 0; m < n; ++m) {
+          const int q = slot(m);
+          W[m][wa[c]] = fma(metric(na[c], q), hs[m], W[m][wa[c]]);
+          if (wb[c] >= 0) W[m][wb[c]] = fma(metric(nb[c], q), hs[m], W[m][wb[c]]);
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);  // one entry at a time
+      }
+    }
+  }
+  // ---- the three directions' sums, in order, and the epilogue's loads
+  double Uq[IT][5], ub0[IT][5];
+  double *Ube = Ub + (size_t)e * 5 * n3;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      Uq[it][v] = t < n3 ? Ue[v * n3 + t] : 1.0;
+      ub0[it][v] = (t < n3 && accumulate) ? Ube[v * n3 + t] : 0.0;
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    __syncthreads();
+    if (act && dir == d) {
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        const int q = d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m));
+#pragma unroll
+        for (int v = 0; v < 6; ++v) sm[v * n3 + q] = d == 0 ? acc[m][v] : sm[v * n3 + q] + acc[m][v];
+        if constexpr (NS) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sm[(6 + v) * n3 + q] = d == 0 ? W[m][v] : sm[(6 + v) * n3 + q] + W[m][v];
+        }
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (t >= n3) continue;
+    const int s = div_slot<n>(t % n, (t / n) % n, t / n2);
+    const dgf::P q = dgf::prim(Uq[it], gm1);
+    dgf::PA pa = {sm[s], sm[n3 + s], sm[2 * n3 + s], sm[3 * n3 + s], sm[4 * n3 + s]};
+    dgf::PA pl = dgf::zero_pa();
+    if constexpr (NS) {
+      pa.u += pv[it][0]; pa.v += pv[it][1]; pa.w += pv[it][2];
+      const double Wb[4] = {sm[6 * n3 + s], sm[7 * n3 + s], sm[8 * n3 + s], sm[9 * n3 + s]};
+      dgf::lift_vars_adj(q, ph.R, Wb, pl);
+    }
+    dgf::enthalpy_adj(q, g1, sm[5 * n3 + s], pa);
+    dgf::PA pt;
+    pt.r = fma(scale, pa.r, pl.r); pt.u = fma(scale, pa.u, pl.u); pt.v = fma(scale, pa.v, pl.v);
+    pt.w = fma(scale, pa.w, pl.w); pt.p = fma(scale, pa.p, pl.p);
+    double cb[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    dgf::cons_adj(q, gm1, pt, cb);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) Ube[v * n3 + t] = ub0[it][v] + cb[v];
   }
 }
 
@@ -760,31 +1191,28 @@ int launch_vjp(const Geo &g, const Phys &ph, int eqn, int form, bool lgl, const 
     return hipGetLastError() == hipSuccess ? DG_OK : DG_ERR_HIP;
   }
   if (form != DG_FORM_SPLIT) return DG_ERR_UNSUPPORTED;
-  {
-  dim3 grid(xcd_grid(g.K)), block(VSz<N>::NT);
-  if (eqn == DG_NAVIER_STOKES) {
-    if (gen)
-      hipLaunchKernelGGL((k_vjp_main<N, true, true>), grid, block, 0, st, g, ph, U, G, Ubar_t, Ubar, Pf, scale,
-                         accumulate);
-    else
-      hipLaunchKernelGGL((k_vjp_main<N, true, false>), grid, block, 0, st, g, ph, U, G, Ubar_t, Ubar, Pf, scale,
-                         accumulate);
-    if (hipGetLastError() != hipSuccess) return DG_ERR_HIP;
+  const dim3 grid(xcd_grid(g.K)), block(VSz<N>::NT), lines(SplitSz<N>::NT);
+  const bool ns = eqn == DG_NAVIER_STOKES;
+#define DG_VM(K_, B_, ...) \
+  hipLaunchKernelGGL((K_<N, __VA_ARGS__>), grid, B_, 0, st, g, ph, U, G, Ubar_t, Ubar, Pf, scale, accumulate)
+#define DG_VN(NS_) \
+  do { \
+    if (ph.vf != 0) { if (gen) DG_VM(k_vjp_main, block, NS_, true); else DG_VM(k_vjp_main, block, NS_, false); } \
+    else if (g.Jc) { if (gen) DG_VM(k_vjp_line, lines, NS_, true, true); else DG_VM(k_vjp_line, lines, NS_, false, true); } \
+    else { if (gen) DG_VM(k_vjp_line, lines, NS_, true, false); else DG_VM(k_vjp_line, lines, NS_, false, false); } \
+  } while (0)
+  if (ns) DG_VN(true); else DG_VN(false);
+#undef DG_VN
+#undef DG_VM
+  if (hipGetLastError() != hipSuccess) return DG_ERR_HIP;
+  if (ns) {
     if (gen)
       hipLaunchKernelGGL((k_vjp_face<N, true>), grid, block, 0, st, g, ph, U, Pf, Ubar, Rb, ra, rb, Rb ? 1 : 0);
     else
       hipLaunchKernelGGL((k_vjp_face<N, false>), grid, block, 0, st, g, ph, U, Pf, Ubar, Rb, ra, rb, Rb ? 1 : 0);
-  } else {
-    if (gen)
-      hipLaunchKernelGGL((k_vjp_main<N, false, true>), grid, block, 0, st, g, ph, U, G, Ubar_t, Ubar, Pf, scale,
-                         accumulate);
-    else
-      hipLaunchKernelGGL((k_vjp_main<N, false, false>), grid, block, 0, st, g, ph, U, G, Ubar_t, Ubar, Pf, scale,
-                         accumulate);
+    if (hipGetLastError() != hipSuccess) return DG_ERR_HIP;
   }
-  if (hipGetLastError() != hipSuccess) return DG_ERR_HIP;
   return DG_OK;
-  }
 }
 
 #ifdef DG_ONLY_N
