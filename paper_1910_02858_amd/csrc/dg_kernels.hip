@@ -295,6 +295,7 @@ template <int N> struct LiftLds {
   // the three regions together hold 12 values per node at the end (the staged viscous fluxes of
   // LIFT_DIV)
   static constexpr int W = 4 * n3, JA = 3 * n3, WS = (24 * n2 > 5 * n3) ? 24 * n2 : 5 * n3;
+  static constexpr int AFFINE = 12 * n3;  // affine elements: no metric terms, no face means
 };
 
 // 1D tables of the lifting kernel into LDS (by the first threads of the workgroup)
@@ -357,10 +358,7 @@ __device__ __forceinline__ void contra_visc(double *acc, const double *jo, doubl
 }
 
 // sm: the slot's LiftLds<N> regions, contiguous (W, JA, WS).
-// AFF: every element is affine; the metric terms are the element's constants (Geo::Jc).  The gradient is
-// then Ja^dir_d times the reference derivative: 4 LDS reads and 4 fused multiply-adds per line node instead
-// of 7 and 15, and 10 of the 20 doubles read per node (Ja, 1/J) stay out of memory traffic.
-template <int N, bool LGL, int OUT, int GEN, bool AFF>
+template <int N, bool LGL, int OUT, int GEN>
 __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, bool valid, int t,
                                           const double *__restrict__ U, double *__restrict__ G,
                                           double *__restrict__ Fv, double *sm, const double *sDh,
@@ -376,14 +374,9 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
   // node's 1/J are loaded one phase ahead
   constexpr int JPT = (3 * n3 + NT - 1) / NT;
   double jn[JPT], sjn = 0.0;
-  AffineConst jc = nullptr;
-  if constexpr (AFF) {
-    jc = affine_const(g, e);
-  } else {
-    const double *Jd = g.Ja + (size_t)e * 9 * n3;
+  const double *Jd0 = g.Ja + (size_t)e * 9 * n3;
 #pragma unroll
-    for (int r = 0; r < JPT; ++r) jn[r] = (valid && t + r * NT < 3 * n3) ? Jd[t + r * NT] : 0.0;
-  }
+  for (int r = 0; r < JPT; ++r) jn[r] = (valid && t + r * NT < 3 * n3) ? Jd0[t + r * NT] : 0.0;
   // on LGL nodes with one face point per thread, the neighbour's trace is loaded before the
   // first barrier
   constexpr bool PF = LGL && 6 * n2 <= NT;
@@ -499,50 +492,6 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
   const int i = t % n, j = (t / n) % n, k = t / n2;
   double jo[9];  // this node's metric terms, kept for the viscous fluxes
   double gd[4] = {0.0, 0.0, 0.0, 0.0};  // the viscous divergence (LIFT_DIV, LIFT_DIVK)
-  if constexpr (AFF) {
-    __syncthreads();  // W and the face means are complete
-    if (valid && t < n3) {
-#pragma unroll
-      for (int c = 0; c < 9; ++c) jo[c] = jc[c];
-#pragma unroll
-      for (int dir = 0; dir < 3; ++dir) {
-        const int id = dir == 0 ? i : (dir == 1 ? j : k);
-        const int str = dir == 0 ? 1 : (dir == 1 ? n : n2);
-        const int base = t - id * str;
-        const int a = dir == 0 ? j : i, b = dir == 2 ? j : k, ab = a + n * b;
-        double dw[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int m = 0; m < n; ++m) {
-          const int qm = base + m * str;
-          const double Dh = sDh[id * n + m];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) dw[v] = fma(Dh, sW[v * n3 + qm], dw[v]);
-        }
-        // surface: +-lhat(+-1) W*, the normal times s-hat being +-Ja^dir on both faces of the direction
-#pragma unroll
-        for (int sd = 0; sd < 2; ++sd) {
-          const int s = 2 * dir + sd;
-          if (LGL && id != (sd ? N : 0)) continue;
-          const double lh = slh[(sd ? n : 0) + id];
-          if (GEN == 2 && is_mortar(g, e, s)) {
-            // non-conforming face: W* s n_d (outward) from the mortar face array
-            const double *ml = g.mlift + (size_t)g.mslot[(size_t)e * 6 + s] * 12 * n2 + ab;
-#pragma unroll
-            for (int c = 0; c < 12; ++c) acc[c] += lh * ml[c * n2];
-          } else {
-            const double sl_ = sd ? lh : -lh;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) dw[v] = fma(sl_, sWs[(s * 4 + v) * n2 + ab], dw[v]);
-          }
-        }
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[d * 4 + v] = fma(jo[dir * 3 + d], dw[v], acc[d * 4 + v]);
-      }
-    }
-    sjn = jc[9];
-  } else {
 #pragma unroll
   for (int dir = 0; dir < 3; ++dir) {
     __syncthreads();
@@ -601,8 +550,7 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
       }
     }
   }
-  }
-  if (!LGL && !AFF && valid && t < n3) {
+  if (!LGL && valid && t < n3) {
     // surface: lhat(+-1) [W* nt_d] on each side
     for (int s = 0; s < 6; ++s) {
       const int dn = s >> 1;
@@ -729,9 +677,8 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
 #pragma unroll
         for (int c = 0; c < 5; ++c) Uq[c] = ut[c * n2];
       }
-      const double *fnp = AFF ? g.Jc + (size_t)e * AFFINE_DOUBLES + 10 + 3 * s : g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
-      const int fst = AFF ? 1 : n2;
-      const double nt[3] = {fnp[0], fnp[fst], fnp[2 * fst]};
+      const double *fnp = g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
+      const double nt[3] = {fnp[0], fnp[n2], fnp[2 * n2]};
       double Fo[5];
       flux_v(to_prim(Uq, gm1), gq, ph, nt, Fo);
       const NbFace f = nbr_face<n, (GEN > 0)>(g, e, s, a, b);
@@ -868,6 +815,376 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
   }
 }
 
+// BR1 lifting of an affine element e by NT lanes, outputs as lift_body (dir-direction Fv along the element's
+// constant Ja^dir).  The reference derivatives and the divergence are line tasks: a lane holds its line's four
+// values of W in registers, forms the surface means at its two ends, and writes its n results to LDS, where
+// every node collects its three directions' values.
+// What bounds it: with one node per lane each value was read n times, 120 of the 190 LDS accesses of a node at
+// N = 7; the LDS was busy 75 % of the time.  Here 40 of 60: weak form on LG nodes (N = 7, 16^3) 136 -> 87 us a launch,
+// split form (N = 7, 32^3) 557 -> 505; a step of the 32-member ensemble 3115 -> 2933 us.
+// Every rounding step is spelled out (explicit fma, no contraction): the same bits from every launch shape.
+// sm: 12 values per node (slots: div_slot).  valid = false keeps the lanes in step with the barriers.
+template <int N, bool LGL, int OUT, int GEN, int NT>
+__device__ __forceinline__ void lift_affine(const Geo &g, const Phys &ph, const Tab *tab, int e, bool valid, int lane,
+                                            const double *__restrict__ U, double *__restrict__ G,
+                                            double *__restrict__ Fv, double *sm) {
+#pragma clang fp contract(off)
+  constexpr int n = N + 1, n2 = n * n, n3 = n2 * n, IT = (n3 + NT - 1) / NT;
+  const double gm1 = ph.gamma - 1.0;
+  const double *Ue = U + (size_t)e * 5 * n3;
+  const AffineConst jc = affine_const(g, e);
+  const Scalars tb(tab);
+  const int dir = (n2 % 64 == 0 && NT % 64 == 0) ? __builtin_amdgcn_readfirstlane(lane / n2) : lane / n2;
+  const int ab = lane - dir * n2, a = ab % n, b = ab / n;
+  const bool act = valid && lane < 3 * n2;
+  // loads: the neighbours' indices, the element's state, the traces beyond the line's two ends
+  int nb2[2] = {0, 0};
+  NbFace f2[2];
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd)
+    if (act) {
+      nb2[sd] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
+      f2[sd] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
+    }
+  double Uq[IT][5];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Uq[it][v] = Ue[v * n3 + t];
+    }
+  }
+  constexpr int NX = LGL ? 5 : 4;  // the other side's conservative state, on LG nodes its trace of W (k_prolong)
+  double Ux[2][NX];
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd)
+    if (act && !(GEN && f2[sd].bnd)) {
+      const NbFace f = f2[sd];
+      const double *x;
+      int st;
+      if (LGL) {
+        x = U + (size_t)nb2[sd] * 5 * n3 + (GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dir, a, b, sd ? 0 : N));
+        st = n3;
+      } else {
+        x = g.Wtr + ((size_t)nb2[sd] * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
+        st = n2;
+      }
+#pragma unroll
+      for (int v = 0; v < NX; ++v) Ux[sd][v] = x[v * st];
+    }
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+      const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+      double W[4];
+      grad_prim_to_W(Uq[it], gm1, ph.R, W);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sm[v * n3 + q] = W[v];
+    }
+  }
+  __syncthreads();
+  const LineSlots<n> slot(act ? dir : 0, act ? a : 0, act ? b : 0);
+  double f[4][n];      // W of the line's nodes; the velocities are kept for the viscous work
+  double ws[2][4];     // surface means at its ends
+  double nd[3];        // Ja^dir, +- the outward normal of the line's two faces times s-hat
+#pragma unroll
+  for (int d = 0; d < 3; ++d) nd[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
+  if (act) {
+#pragma unroll
+    for (int m = 0; m < n; ++m) {
+      const int q = slot(m);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) f[v][m] = sm[v * n3 + q];
+    }
+#pragma unroll
+    for (int sd = 0; sd < 2; ++sd) {
+      double WL[4], WR[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (LGL) {
+          WL[v] = f[v][sd ? N : 0];
+        } else {
+          WL[v] = 0.0;
+#pragma unroll
+          for (int m = 0; m < n; ++m) WL[v] = fma(sd ? tb.lp[m] : tb.lm[m], f[v][m], WL[v]);
+        }
+        WR[v] = WL[v];
+      }
+      const bool bnd = GEN && f2[sd].bnd;
+      const int kind = f2[sd].kind;
+      if (!bnd) {
+        if constexpr (LGL) {
+          grad_prim_to_W(Ux[sd], gm1, ph.R, WR);
+        } else {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) WR[v] = Ux[sd][v];
+        }
+      } else if (kind == DG_BC_STATE) {
+        grad_prim_to_W(ph.ub, gm1, ph.R, WR);  // given outer state
+      } else if (kind == DG_BC_WALL || kind == DG_BC_WALL_ISOTHERMAL) {
+        // no-slip wall: velocity reversed, temperature kept; isothermal: mean temperature T_w
+#pragma unroll
+        for (int v = 0; v < 3; ++v) WR[v] = -WL[v];
+        if (kind == DG_BC_WALL_ISOTHERMAL) WR[3] = 2.0 * ph.tw - WL[3];
+      } else if (kind == DG_BC_OUTFLOW) {
+        // pressure outflow: the own trace's density and velocity with p_out (the conservative trace: the
+        // face node on LGL nodes, interpolated with l(+-1) on LG nodes)
+        double Ut[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int m = LGL ? (sd ? N : 0) : 0; m < (LGL && !sd ? 1 : n); ++m) {
+          const double l = LGL ? 1.0 : (sd ? tb.lp[m] : tb.lm[m]);
+#pragma unroll
+          for (int v = 0; v < 5; ++v) Ut[v] = fma(l, Ue[v * n3 + line_node<n>(dir, a, b, m)], Ut[v]);
+        }
+        Ut[4] = ph.pout / gm1 + 0.5 * (Ut[1] * Ut[1] + Ut[2] * Ut[2] + Ut[3] * Ut[3]) / Ut[0];
+        grad_prim_to_W(Ut, gm1, ph.R, WR);
+      } else if (kind != FACE_MORTAR) {
+        // symmetry plane: the outer W is the inner one with the velocity reflected
+        double nh[3];
+        unit3(nd, nh);
+        mirror3(WR, nh);
+      }
+      // a non-conforming face's surface term comes from the mortar face array (below)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ws[sd][v] = GEN == 2 && bnd && kind == FACE_MORTAR ? 0.0 : 0.5 * (WL[v] + WR[v]);
+    }
+  }
+  __syncthreads();  // every line has read its values
+  if (act) {
+#pragma unroll
+    for (int id = 0; id < n; ++id) {
+      double o[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        const double d = tb.Dh[id * n + m];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = fma(d, f[v][m], o[v]);
+      }
+      // surface: +-lhat(+-1) W*
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (!LGL || id == 0) o[v] = fma(-tb.lhm[id], ws[0][v], o[v]);
+        if (!LGL || id == N) o[v] = fma(tb.lhp[id], ws[1][v], o[v]);
+      }
+      const int q = slot(id);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sm[(dir * 4 + v) * n3 + q] = o[v];
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);  // one result at a time
+    }
+  }
+  __syncthreads();
+  // ---- node by node: gradients, then the contravariant viscous fluxes
+  constexpr bool DIVO = OUT == LIFT_DIV || OUT == LIFT_DIVK || OUT == LIFT_WV || OUT == LIFT_SV;
+#pragma unroll(IT <= 2 ? IT : 1)
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (!valid || t >= n3) continue;
+    const int i = t % n, j = (t / n) % n, k = t / n2, q = div_slot<n>(i, j, k);
+    double acc[12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[c] = 0.0;
+#pragma unroll
+    for (int dr = 0; dr < 3; ++dr) {
+      if (GEN == 2) {
+        // non-conforming faces: W* s n_d (outward) from the mortar face array
+        const int id = dr == 0 ? i : (dr == 1 ? j : k), fab = (dr == 0 ? j : i) + n * (dr == 2 ? j : k);
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+          if (!is_mortar(g, e, 2 * dr + sd) || (LGL && id != (sd ? N : 0))) continue;
+          const double lh = sd ? tab->lhp[id] : tab->lhm[id];
+          const double *ml = g.mlift + (size_t)g.mslot[(size_t)e * 6 + 2 * dr + sd] * 12 * n2 + fab;
+#pragma unroll
+          for (int c = 0; c < 12; ++c) acc[c] = fma(lh, ml[c * n2], acc[c]);
+        }
+      }
+      double dw[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dw[v] = sm[(dr * 4 + v) * n3 + q];
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[d * 4 + v] = fma(jc[dr * 3 + d], dw[v], acc[d * 4 + v]);
+    }
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[c] *= jc[9];
+    if (GEN == 2 && LGL) {
+      // face nodes of non-conforming sides keep their gradients for the mortar flux kernel
+#pragma unroll
+      for (int dr = 0; dr < 3; ++dr) {
+        const int id = dr == 0 ? i : (dr == 1 ? j : k);
+        if (id != 0 && id != N) continue;
+        const int ms = g.mslot[(size_t)e * 6 + 2 * dr + (id == N ? 1 : 0)];
+        if (ms < 0) continue;
+        double *mg = g.mg + (size_t)ms * 12 * n2 + (dr == 0 ? j : i) + n * (dr == 2 ? j : k);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) mg[c * n2] = acc[c];
+      }
+    }
+    if (OUT == LIFT_G || OUT == LIFT_GT || ((OUT == LIFT_WV || OUT == LIFT_SV || OUT == LIFT_DIV) && G)) {
+      double *Ge = G + (size_t)e * 12 * n3;
+#pragma unroll
+      for (int c = 0; c < 12; ++c) Ge[c * n3 + t] = acc[c];
+    }
+    if constexpr (OUT == LIFT_GT) {
+#pragma unroll
+      for (int c = 0; c < 12; ++c) sm[c * n3 + q] = acc[c];
+    }
+    if constexpr (DIVO || OUT == LIFT_FV) {
+      const double div = acc[0] + acc[5] + acc[10];
+      const double t00 = ph.mu * fma(-2.0 / 3.0, div, 2.0 * acc[0]);
+      const double t11 = ph.mu * fma(-2.0 / 3.0, div, 2.0 * acc[5]);
+      const double t22 = ph.mu * fma(-2.0 / 3.0, div, 2.0 * acc[10]);
+      const double t01 = ph.mu * (acc[4] + acc[1]);
+      const double t02 = ph.mu * (acc[8] + acc[2]);
+      const double t12 = ph.mu * (acc[9] + acc[6]);
+      double W[4];
+      if (OUT == LIFT_FV || OUT == LIFT_DIVK) {
+        double Un[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Un[v] = Ue[v * n3 + t];
+        grad_prim_to_W(Un, gm1, ph.R, W);
+      }
+#pragma unroll
+      for (int dr = 0; dr < 3; ++dr) {
+        const double n0 = jc[3 * dr], n1 = jc[3 * dr + 1], n2_ = jc[3 * dr + 2];
+        // momentum fluxes and the temperature gradient along Ja^dr
+        const double F0 = fma(t02, n2_, fma(t01, n1, t00 * n0));
+        const double F1 = fma(t12, n2_, fma(t11, n1, t01 * n0));
+        const double F2 = fma(t22, n2_, fma(t12, n1, t02 * n0));
+        const double qn = fma(acc[11], n2_, fma(acc[7], n1, acc[3] * n0));
+        if (OUT == LIFT_FV || OUT == LIFT_DIVK) {
+          double *Fe = Fv + ((size_t)e * 12 + dr * 4) * n3 + t;
+          Fe[0] = F0; Fe[n3] = F1; Fe[2 * n3] = F2;
+          Fe[3 * n3] = fma(ph.kappa, qn, fma(F2, W[2], fma(F1, W[1], F0 * W[0])));
+        }
+        if constexpr (DIVO) {
+          sm[(dr * 4) * n3 + q] = F0;
+          sm[(dr * 4 + 1) * n3 + q] = F1;
+          sm[(dr * 4 + 2) * n3 + q] = F2;
+          sm[(dr * 4 + 3) * n3 + q] = qn;
+        }
+      }
+    }
+  }
+  if constexpr (DIVO) {
+    __syncthreads();
+    if (act) {
+      // the line's fluxes along its direction: momentum, energy
+      double F[4][n];
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        const int q = slot(m);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) F[c][m] = sm[(dir * 4 + c) * n3 + q];
+      }
+      if constexpr (OUT == LIFT_WV || OUT == LIFT_SV) {
+        // every side's viscous flux at its trace along its own outward normal (both linear in the gradients:
+        // interpolated after the contraction with the constant normal); on a boundary side the BR1 mean with
+        // the outer state, in closed form
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+          double T[4] = {0.0, 0.0, 0.0, 0.0}, ut[3];
+          if (LGL) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) T[c] = F[c][sd ? N : 0];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) ut[c] = f[c][sd ? N : 0];
+          } else {
+#pragma unroll
+            for (int m = 0; m < n; ++m)
+#pragma unroll
+              for (int c = 0; c < 4; ++c) T[c] = fma(sd ? tb.lp[m] : tb.lm[m], F[c][m], T[c]);
+            const double *utr = g.Utr + ((size_t)e * 6 + 2 * dir + sd) * 5 * n2 + ab;
+            const double ir = 1.0 / utr[0];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) ut[c] = utr[(1 + c) * n2] * ir;
+          }
+          T[3] *= ph.kappa;
+          const bool bnd = GEN && f2[sd].bnd && f2[sd].kind != DG_BC_STATE && f2[sd].kind != DG_BC_OUTFLOW;
+          if (!bnd) {
+            T[3] = fma(T[2], ut[2], fma(T[1], ut[1], fma(T[0], ut[0], T[3])));
+          } else if (f2[sd].kind == DG_BC_WALL) {
+            T[3] = 0.0;  // no-slip wall: reversed velocity and mirrored heat flux
+          } else if (f2[sd].kind != DG_BC_WALL_ISOTHERMAL) {
+            // symmetry plane: the normal part of the momentum flux (an isothermal wall keeps the heat flux)
+            double nh[3];
+            unit3(nd, nh);
+            const double gm = T[0] * nh[0] + T[1] * nh[1] + T[2] * nh[2];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) T[c] = gm * nh[c];
+            T[3] = 0.0;
+          }
+          double *pv = g.Gf + ((size_t)e * 6 + 2 * dir + sd) * 4 * n2 + ab;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) pv[c * n2] = sd ? T[c] : -T[c];
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < n; ++m)
+        F[3][m] = fma(ph.kappa, F[3][m], fma(F[2][m], f[2][m], fma(F[1][m], f[1][m], F[0][m] * f[0][m])));
+      if constexpr (OUT == LIFT_DIV || OUT == LIFT_DIVK) {
+        // the traces on the line's two faces
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+          double *gf = g.Gf + ((size_t)e * 6 + 2 * dir + sd) * 4 * n2 + ab;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) gf[c * n2] = F[c][sd ? N : 0];
+        }
+      }
+      const Scalar M = OUT == LIFT_WV ? tb.Dh : (OUT == LIFT_SV ? tb.Ds : tb.D);
+#pragma unroll
+      for (int id = 0; id < n; ++id) {
+        double o[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int m = 0; m < n; ++m) {
+          double d = M[id * n + m];
+          // the interior part of the surface term: -+lhat(+-1) Fv at the face nodes
+          if ((OUT == LIFT_DIV || OUT == LIFT_DIVK) && m == id && id == 0) d += tb.lhm[0];
+          if ((OUT == LIFT_DIV || OUT == LIFT_DIVK) && m == id && id == N) d -= tb.lhp[N];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) o[c] = fma(d, F[c][m], o[c]);
+        }
+        const int q = slot(id);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sm[(dir * 4 + c) * n3 + q] = o[c];
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int t = lane + it * NT;
+      if (!valid || t >= n3) continue;
+      const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+      double *Gde = g.Gd + (size_t)e * 4 * n3 + t;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) Gde[c * n3] = (sm[c * n3 + q] + sm[(4 + c) * n3 + q]) + sm[(8 + c) * n3 + q];
+    }
+  }
+  if constexpr (OUT == LIFT_GT) {
+    // the gradients' traces on the line's two faces
+    __syncthreads();
+    if (act) {
+#pragma unroll 1
+      for (int c = 0; c < 12; ++c) {
+        double x0 = 0.0, x1 = 0.0;
+#pragma unroll
+        for (int m = 0; m < n; ++m) {
+          const double v = sm[c * n3 + slot(m)];
+          x0 = fma(tb.lm[m], v, x0);
+          x1 = fma(tb.lp[m], v, x1);
+        }
+        double *gt = g.Gtr + (((size_t)e * 6 + 2 * dir) * 12 + c) * n2 + ab;
+        gt[0] = x0;
+        gt[12 * n2] = x1;
+      }
+    }
+  }
+}
+
 // Prolongation on LG nodes (Navier-Stokes): every side's traces of the conservative state and of
 // W = (u, v, w, T), each interpolated with l(+-1) along the face-normal lines of the element
 // (Utr, Wtr of Geo), so that the lifting and operator kernels read their neighbours' traces
@@ -923,7 +1240,7 @@ template <bool LGL, int OUT, int GEN> constexpr int lift_minb() {
   return (LGL || GEN == 0) ? DG_LIFT_MINB : 2;
 }
 
-template <int N, bool LGL, int OUT, int GEN, bool AFF>
+template <int N, bool LGL, int OUT, int GEN>
 __global__ void __launch_bounds__(Sz<N>::NT, (lift_minb<LGL, OUT, GEN>()))
     k_lift(Geo g, Phys ph, const double *__restrict__ U, double *__restrict__ G, double *__restrict__ Fv) {
   using L = LiftLds<N>;
@@ -933,7 +1250,19 @@ __global__ void __launch_bounds__(Sz<N>::NT, (lift_minb<LGL, OUT, GEN>()))
   lift_tables<N>(g.tab, threadIdx.x, Sz<N>::NT, sDh, sl, slh);
   const int e = xcd_element(blockIdx.x, g.K);
   if (e >= g.K) return;
-  lift_body<N, LGL, OUT, GEN, AFF>(g, ph, e, true, threadIdx.x, U, G, Fv, sm, sDh, sl, slh);
+  lift_body<N, LGL, OUT, GEN>(g, ph, e, true, threadIdx.x, U, G, Fv, sm, sDh, sl, slh);
+}
+
+// waves per SIMD the affine lifting is built for
+template <int N> constexpr int lift_affine_minb() { return N <= 5 ? 4 : 3; }
+
+template <int N, bool LGL, int OUT, int GEN>
+__global__ void __launch_bounds__(SplitSz<N>::NT, lift_affine_minb<N>())
+    k_lift_affine(Geo g, Phys ph, const double *__restrict__ U, double *__restrict__ G, double *__restrict__ Fv) {
+  __shared__ double sm[LiftLds<N>::AFFINE];
+  const int e = xcd_element(blockIdx.x, g.K);
+  if (e >= g.K) return;
+  lift_affine<N, LGL, OUT, GEN, SplitSz<N>::NT>(g, ph, g.tab, e, true, threadIdx.x, U, G, Fv, sm);
 }
 
 // ----------------------------------------------------------------------------- operator, weak/strong
@@ -2070,13 +2399,19 @@ __device__ __forceinline__ int member_of(const int *first, int count, int item) 
   return lo;
 }
 
+template <int N, int AFF> constexpr int lift_b_lanes() { return AFF == AFF_ALL ? SplitSz<N>::NT : Sz<N>::NT; }
+template <int N, int AFF> constexpr int lift_b_minb() {
+  return AFF == AFF_NONE ? DG_LIFT_MINB : (AFF == AFF_ALL ? lift_affine_minb<N>() : 4);
+}
+
 template <int N, int EPB, bool GEN, int AFF>
-__global__ void __launch_bounds__(Sz<N>::NT * EPB, DG_LIFT_MINB) k_lift_b(BatchView bv) {
+__global__ void __launch_bounds__((lift_b_lanes<N, AFF>()) * EPB, (lift_b_minb<N, AFF>())) k_lift_b(BatchView bv) {
   using L = LiftLds<N>;
-  constexpr int n = L::n, NT = Sz<N>::NT, SM = L::W + L::JA + L::WS;
+  constexpr int n = L::n, NT = lift_b_lanes<N, AFF>(), SM = AFF == AFF_ALL ? L::AFFINE : L::W + L::JA + L::WS;
+  constexpr bool TAB = AFF != AFF_ALL;
   __shared__ double sm[EPB * SM];
-  __shared__ double sDh[n * n], sl[2 * n], slh[2 * n];
-  lift_tables<N>(bv.tab, threadIdx.x, NT * EPB, sDh, sl, slh);
+  __shared__ double sDh[TAB ? n * n : 1], sl[TAB ? 2 * n : 1], slh[TAB ? 2 * n : 1];
+  if constexpr (TAB) lift_tables<N>(bv.tab, threadIdx.x, NT * EPB, sDh, sl, slh);
   const int nblk = (bv.total + EPB - 1) / EPB;
   const int blk = xcd_element(blockIdx.x, nblk);
   if (blk >= nblk) return;
@@ -2087,10 +2422,11 @@ __global__ void __launch_bounds__(Sz<N>::NT * EPB, DG_LIFT_MINB) k_lift_b(BatchV
   const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
   const Member &M = bv.m[mi];
   const int e = valid ? item - bv.first[mi] : 0;
-  if (AFF == AFF_ALL || (AFF == AFF_MIXED && M.g.Jc))
-    lift_body<N, true, LIFT_DIV, GEN, true>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm + slot * SM, sDh, sl, slh);
-  else
-    lift_body<N, true, LIFT_DIV, GEN, false>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm + slot * SM, sDh, sl, slh);
+  if (AFF == AFF_ALL || (AFF == AFF_MIXED && M.g.Jc)) {
+    lift_affine<N, true, LIFT_DIV, GEN, NT>(M.g, M.ph, bv.tab, e, valid, t, M.U, nullptr, nullptr, sm + slot * SM);
+  } else {
+    if constexpr (TAB) lift_body<N, true, LIFT_DIV, GEN>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm + slot * SM, sDh, sl, slh);
+  }
 }
 
 template <int N, bool NS, int VF, int EPB, bool GEN, int AFF>
@@ -3041,13 +3377,13 @@ int launch_prolong(const Geo &g, const Phys &ph, const double *U, hipStream_t st
 template <int N>
 int launch_lift(const Geo &g, const Phys &ph, bool lgl, int out, const double *U, double *G, double *Fv,
                 hipStream_t st) {
-  dim3 grid(xcd_grid(g.K)), block(Sz<N>::NT);
+  const dim3 grid(xcd_grid(g.K)), block(Sz<N>::NT), lines(SplitSz<N>::NT);
   // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
   const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
 #define DG_KLG(L_, O_, G_) \
   do { \
-    if (g.Jc) hipLaunchKernelGGL((k_lift<N, L_, O_, G_, true>), grid, block, 0, st, g, ph, U, G, Fv); \
-    else hipLaunchKernelGGL((k_lift<N, L_, O_, G_, false>), grid, block, 0, st, g, ph, U, G, Fv); \
+    if (g.Jc) hipLaunchKernelGGL((k_lift_affine<N, L_, O_, G_>), grid, lines, 0, st, g, ph, U, G, Fv); \
+    else hipLaunchKernelGGL((k_lift<N, L_, O_, G_>), grid, block, 0, st, g, ph, U, G, Fv); \
   } while (0)
 #define DG_KL(L_, O_) \
   do { \
@@ -3102,7 +3438,7 @@ int launch_main(const Geo &g, const Phys &ph, bool lgl, int eqn, int form, const
 
 template <int N, int EPB, int AFF>
 static int launch_batch_lift_t(const BatchView &bv, hipStream_t st) {
-  const dim3 grid(xcd_grid((bv.total + EPB - 1) / EPB)), block(Sz<N>::NT * EPB);
+  const dim3 grid(xcd_grid((bv.total + EPB - 1) / EPB)), block(lift_b_lanes<N, AFF>() * EPB);
   if (bv.general) hipLaunchKernelGGL((k_lift_b<N, EPB, true, AFF>), grid, block, 0, st, bv);
   else hipLaunchKernelGGL((k_lift_b<N, EPB, false, AFF>), grid, block, 0, st, bv);
   DG_CHECK_LAUNCH();
@@ -3396,12 +3732,12 @@ __device__ __forceinline__ void fused_lift_group(const BatchView &bv, int blk, d
   const int e = valid ? item - bv.first[mi] : 0;
   double *sm = smem + slot * (L::W + L::JA + L::WS);
   if (fused_affine(bv, blk * epb))
-    lift_body<N, true, LIFT_DIV, 0, true>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm, sDh, sl, slh);
+    lift_affine<N, true, LIFT_DIV, 0, NT>(M.g, M.ph, bv.tab, e, valid, t, M.U, nullptr, nullptr, sm);
   else
-    lift_body<N, true, LIFT_DIV, 0, false>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm, sDh, sl, slh);
+    lift_body<N, true, LIFT_DIV, 0>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm, sDh, sl, slh);
 }
 
-__global__ void __launch_bounds__(512, DG_LIFT_MINB) k_lift_f(FusedView fv) {
+__global__ void __launch_bounds__(512, 4) k_lift_f(FusedView fv) {
   __shared__ double smem[LiftLds<7>::W + LiftLds<7>::JA + LiftLds<7>::WS];
   __shared__ double sDh[64], sl[16], slh[16];
   const int nb = fv.start[fv.ng];

@@ -48,4 +48,13 @@ template <int N> struct SplitSz {
   static constexpr int NT = (NL + 63) / 64 * 64;
 };
 
+// The 1D tables through the scalar cache.
+typedef const __attribute__((address_space(4))) double *Scalar;
+struct Scalars {
+  Scalar D, Dh, Ds, lm, lp, lhm, lhp;
+  __device__ __forceinline__ Scalars(const Tab *t)
+      : D((Scalar)t->D), Dh((Scalar)t->Dh), Ds((Scalar)t->Ds), lm((Scalar)t->lm), lp((Scalar)t->lp),
+        lhm((Scalar)t->lhm), lhp((Scalar)t->lhp) {}
+};
+
 }  // namespace dg
