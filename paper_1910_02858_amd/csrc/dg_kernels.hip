@@ -21,8 +21,14 @@
 #include "dg_lines.h"
 
 // waves per SIMD the split-form kernel is built for: 2 (256 registers: a line of 8 nodes holds 112
-// doubles); at N = 8 one element's LDS fills the CU and one wave per SIMD is all there is
-constexpr int split_minb(int N) { return N >= 8 ? 1 : 2; }
+// doubles); at N = 8 one element's LDS fills the CU and one wave per SIMD is all there is.  Affine elements with
+// the kinetic-energy preserving flux (vf 0) at N = 6, 7 need 176 registers: 168, three waves and four workgroups
+// per CU instead of two, spill 44 and 60 bytes and still gain (32^3 elements: N = 7 7021 -> 6650 us a step, N = 6
+// 5195 -> 4824).  Not below N = 6 (N = 5 6100 against 6090, N = 4 6940 -> 6975, N = 3 7950 -> 8900) and not for the
+// entropy-conserving flux, which spills 356 bytes (N = 7 7715 -> 8795).
+constexpr int split_minb(int N, int vf, bool affine) {
+  return N >= 8 ? 1 : (affine && vf == 0 && N >= 6 ? 3 : 2);
+}
 // minimum waves per SIMD for the lifting kernel: 6 fits three 512-thread workgroups per CU
 #ifndef DG_LIFT_MINB
 #define DG_LIFT_MINB 6
@@ -2012,7 +2018,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
 }
 
 template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
-__global__ void __launch_bounds__(SplitSz<N>::NT, split_minb(N)) k_split(Geo g, Phys ph, const double *__restrict__ U,
+__global__ void __launch_bounds__(SplitSz<N>::NT, split_minb(N, VF, AFF)) k_split(Geo g, Phys ph, const double *__restrict__ U,
                                                      double *__restrict__ out, double *__restrict__ R, double ca,
                                                      double cb, double dt, int mode) {
   __shared__ double sm[AFF ? SplitLds<N>::AFFINE : SplitLds<N>::A];
@@ -2430,7 +2436,7 @@ __global__ void __launch_bounds__((lift_b_lanes<N, AFF>()) * EPB, (lift_b_minb<N
 }
 
 template <int N, bool NS, int VF, int EPB, bool GEN, int AFF>
-__global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N)) k_split_b(BatchView bv) {
+__global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N, VF, AFF == AFF_ALL)) k_split_b(BatchView bv) {
   constexpr int NT = SplitSz<N>::NT, L = AFF == AFF_ALL ? SplitLds<N>::AFFINE : SplitLds<N>::A;
   __shared__ double sm[EPB * L];
   const int nblk = (bv.total + EPB - 1) / EPB;
