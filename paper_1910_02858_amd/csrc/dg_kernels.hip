@@ -318,11 +318,12 @@ __device__ __forceinline__ void lift_tables(const Tab *tb, int t, int nthreads, 
 // BR1 lifting of element e by the NT threads t of one slot.  valid = false keeps the slot's
 // threads in step with the workgroup barriers without touching memory.
 // OUT: LIFT_G writes the gradients G[e][d*4+c][node] = dW_c/dx_d (weak and strong forms);
-// LIFT_FV writes instead the contravariant viscous fluxes Fv[e][dir*4+c][node] =
-// (F^v . Ja^dir)_{1+c} (momentum, energy), which the reverse sweep consumes; LIFT_DIV writes what
+// LIFT_FV writes instead the momentum components c < 3 of the contravariant viscous fluxes
+// Fv[e][dir*4+c][node] = (F^v . Ja^dir)_{1+c} (momentum, energy), which the reverse sweep reads (the energy's
+// entries stay as they are); LIFT_DIV writes what
 // the split-form operator reads, the strong-form divergence Geo::Gd (sums along the lines of D
 // times Fv^dir, and the interior part of the surface term) and the face traces Geo::Gf of Fv;
-// LIFT_DIVK writes both (the stage kept for a reverse sweep).  LIFT_GT (LG nodes) writes the
+// LIFT_DIVK writes both, all of Fv (the stage kept for a reverse sweep).  LIFT_GT (LG nodes) writes the
 // gradients and every side's traces of them, interpolated with l(+-1) (Geo::Gtr), which the
 // operator kernel reads at its faces instead of interpolating along the lines of its own and the
 // neighbour's element.  On LG nodes the neighbours' traces of W come from k_prolong (Geo::Wtr).
@@ -615,7 +616,8 @@ __device__ __forceinline__ void lift_body(const Geo &g, const Phys &ph, int e, b
       if (OUT == LIFT_FV || OUT == LIFT_DIVK) {
         double *Fe = Fv + (size_t)e * 12 * n3;
 #pragma unroll
-        for (int c = 0; c < 12; ++c) Fe[c * n3 + t] = acc[c];
+        for (int c = 0; c < 12; ++c)
+          if (OUT == LIFT_DIVK || c % 4 != 3) Fe[c * n3 + t] = acc[c];
       }
       if (OUT == LIFT_DIV || OUT == LIFT_DIVK) {
         // the traces Fv^dir on the element's faces through this node, and their interior part
@@ -1046,7 +1048,7 @@ __device__ __forceinline__ void lift_affine(const Geo &g, const Phys &ph, const 
       const double t02 = ph.mu * (acc[8] + acc[2]);
       const double t12 = ph.mu * (acc[9] + acc[6]);
       double W[4];
-      if (OUT == LIFT_FV || OUT == LIFT_DIVK) {
+      if (OUT == LIFT_DIVK) {
         double Un[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) Un[v] = Ue[v * n3 + t];
@@ -1063,7 +1065,7 @@ __device__ __forceinline__ void lift_affine(const Geo &g, const Phys &ph, const 
         if (OUT == LIFT_FV || OUT == LIFT_DIVK) {
           double *Fe = Fv + ((size_t)e * 12 + dr * 4) * n3 + t;
           Fe[0] = F0; Fe[n3] = F1; Fe[2 * n3] = F2;
-          Fe[3 * n3] = fma(ph.kappa, qn, fma(F2, W[2], fma(F1, W[1], F0 * W[0])));
+          if (OUT == LIFT_DIVK) Fe[3 * n3] = fma(ph.kappa, qn, fma(F2, W[2], fma(F1, W[1], F0 * W[0])));
         }
         if constexpr (DIVO) {
           sm[(dr * 4) * n3 + q] = F0;
