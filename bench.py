@@ -10,8 +10,8 @@ Prints one JSON line.  value = DOF-updates/s = nodes * steps * 5 / wall (DOF cou
 variable, as the paper's performance index does); PID = 1/value seconds per DOF per stage.
 The roofline object is for the dominant kernel, timed with HIP events on the library's
 stream over extra profiled stages after the timed region; its algorithmic bytes are the
-compulsory HBM traffic per node (37 doubles read+write for the main kernel, 22 for the
-lifting kernel).  cpu_baseline is the FP64 oracle on the host cores on a bounded sample.
+compulsory HBM traffic per node (27 doubles read+write for the main kernel, 12 for the
+lifting kernel: the lattice's elements are affine and their metric terms constants).  cpu_baseline is the FP64 oracle on the host cores on a bounded sample.
 """
 from __future__ import annotations
 
@@ -29,15 +29,15 @@ if ROOT not in sys.path:
 
 METRIC = "DOF-updates/s (PID s/DOF/stage) at N=7 TGV; adjoint/forward cost ratio"
 HBM_PEAK_GBS = 8000.0
-# split-form operator at N = 7: U 5 + viscous divergence 4 + own face traces of the viscous
-# fluxes 3 (24 n^2 values per element, n = 8) + Ja 9 + 1/J 1 + R 5 read, U_new 5 + R 5 written
-BYTES_MAIN = 37 * 8
-# lifting for the split form: U 5 + Ja 9 + 1/J 1 read, viscous divergence 4 + face traces 3 written
-BYTES_LIFT = 22 * 8
-# weak-form operator at N = 7 (Navier-Stokes): U 5 + viscous volume term 4 + own face viscous fluxes 3
-# (24 n^2 per element) + face normals 2.25 (18 n^2) + Ja 9 + 1/J 1 + R 5 read, U_new 5 + R 5 written
-BYTES_WEAK_MAIN = 39.25 * 8
-# reverse stage: k_vjp_main reads U 5, the kept viscous fluxes' momentum part 9, Ja 9, 1/J 1,
+# split-form operator at N = 7 on affine elements: U 5 + viscous divergence 4 + own face traces of the viscous
+# fluxes 3 (24 n^2 values per element, n = 8) + R 5 read, U_new 5 + R 5 written (curved elements: Ja 9 + 1/J 1 more)
+BYTES_MAIN = 27 * 8
+# lifting for the split form: U 5 read, viscous divergence 4 + face traces 3 written (curved: Ja 9 + 1/J 1 more)
+BYTES_LIFT = 12 * 8
+# weak-form operator at N = 7 (Navier-Stokes) on affine elements: U 5 + viscous volume term 4 + own face viscous
+# fluxes 3 (24 n^2 per element) + R 5 read, U_new 5 + R 5 written
+BYTES_WEAK_MAIN = 27 * 8
+# reverse stage on curved elements: k_vjp_line reads U 5, the kept viscous fluxes' momentum part 9, Ja 9, 1/J 1,
 # Ubar_t 5, Ubar 5 and writes Ubar 5; k_vjp_face reads Ubar 5, Rbar 5 and writes Rbar 5
 BYTES_VJP_MAIN = 39 * 8
 BYTES_VJP_FACE = 15 * 8
@@ -54,7 +54,7 @@ def bytes_fv(n: int) -> float:
 # device-to-device copy gives on the same box; valid only while the kernel sources still hash
 # to the value recorded with the counters.
 COUNTERS = os.path.join(ROOT, "profiles", "k_split_ns_ec_n7_k48_counters.txt")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1910_02858_amd", "csrc", f) for f in ("dg_kernels.hip", "dg_internal.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1910_02858_amd", "csrc", f) for f in ("dg_kernels.hip", "dg_internal.h", "dg_lines.h")]
 
 
 def kernel_source_hash() -> str:
@@ -300,16 +300,15 @@ def ec_branch_bench(S, U_smooth, torch, wl, smooth_main_ms: float, stages: int =
 
 
 def weak_form_bench(dgsem, inputs, torch, stages: int = 10):
-    """The weak and strong forms (k_main: the D-hat or D contraction of the fluxes along every
+    """The weak and strong forms (k_line: the D-hat or D contraction of the fluxes along every
     line, on LG nodes the face prolongation): the Euler density-wave scheme at N=3 on 96^3 LG
     elements, the Navier-Stokes TGV (central volume flux, Roe, BR1) in weak and strong form at N=7
     on 48^3 on LG and on LGL nodes (strong form on LGL nodes: the split form's reads), all
     56.6 M nodes; per-kernel times (the lifting's includes the LG prolongation), the operator
-    kernel priced at 314 B per node (weak form, strong form on LG nodes: face normals and face
-    fluxes), 296 B (strong form on LGL nodes) or at its Euler reads and writes (U 5, Ja 9, 1/J 1,
-    R 5 read, U_new 5, R 5 written: 240 B)."""
+    kernel priced at 216 B per node (affine elements) or at its Euler reads and writes (U 5, R 5
+    read, U_new 5, R 5 written: 160 B)."""
     out = {}
-    for name, wl, nbytes in (("euler_dwave_lg3_k96_weak", inputs.workload(1, K1=96), 30 * 8),
+    for name, wl, nbytes in (("euler_dwave_lg3_k96_weak", inputs.workload(1, K1=96), 20 * 8),
                              ("ns_tgv_central_roe_lg7_k48_weak",
                               inputs.workload(3, form="weak", volflux="central", nodes="lg", K1=48), BYTES_WEAK_MAIN),
                              ("ns_tgv_central_roe_lgl7_k48_weak",
@@ -341,7 +340,7 @@ def weak_form_bench(dgsem, inputs, torch, stages: int = 10):
         gbs = nbytes * dof / (main_ms * 1e-3) / 1e9
         out[name] = {"dof": dof, "kernels_ms": {"main": main_ms, "lift": lift_ms},
                      "value": dof / ((main_ms + lift_ms) * 1e-3),
-                     "roofline": {"bound": "hbm", "kernel": "k_main (" + name.rsplit("_", 1)[1] + " form)", "achieved": gbs,
+                     "roofline": {"bound": "hbm", "kernel": "k_line (" + name.rsplit("_", 1)[1] + " form)", "achieved": gbs,
                                   "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                                   "algorithmic_bytes_per_dof": nbytes}}
         del S, U, R, nxt, cur
@@ -495,7 +494,7 @@ def fv_bench(dgsem, inputs, torch, steps: int, k: int = 32):
 def adjoint_roofline(dgsem, inputs, torch, k: int = 32, repeats: int = 3):
     """The reverse sweep at an HBM-resident size: 32^3 curved hexes, N=5, split KEP + Roe + BR1
     (7.1 M nodes, 283 MB per state, beyond the 256 MB last-level cache).  One forward step keeps
-    its stage inputs and lifting outputs; its reverse (five k_vjp_main + k_vjp_face pairs and one
+    its stage inputs and lifting outputs; its reverse (five k_vjp_line + k_vjp_face pairs and one
     register update) is applied ``repeats`` times (the adjoint of one step applied again: linear,
     no reset needed) and timed with events on the library's stream, beside the same forward
     stages, and priced at BYTES_VJP_MAIN + BYTES_VJP_FACE per node and stage."""
@@ -537,7 +536,7 @@ def adjoint_roofline(dgsem, inputs, torch, k: int = 32, repeats: int = 3):
     gbs = (BYTES_VJP_MAIN + BYTES_VJP_FACE) * dof / (rev_stage_ms * 1e-3) / 1e9
     return {"workload": f"ns_tgv_kep_roe_lgl5_k{k}_curved", "dof": dof, "forward_stage_ms": fwd_stage_ms,
             "reverse_stage_ms": rev_stage_ms, "reverse_over_forward_stage": rev_stage_ms / fwd_stage_ms,
-            "roofline": {"bound": "hbm", "kernel": "k_vjp_main + k_vjp_face (one reverse stage)", "achieved": gbs,
+            "roofline": {"bound": "hbm", "kernel": "k_vjp_line + k_vjp_face (one reverse stage)", "achieved": gbs,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                          "algorithmic_bytes_per_dof": BYTES_VJP_MAIN + BYTES_VJP_FACE}}
 

@@ -450,6 +450,7 @@ std::vector<double> affine_constants(int K, int ngeo, const double *xgeo, const 
     o[9] = (double)(1.0L / J);
     return true;
   };
+  if (!element(0)) return {};  // a curved mesh starts no threads
   auto work = [&](unsigned tid) {
     const int e0 = (int)((size_t)K * tid / nthr), e1 = (int)((size_t)K * (tid + 1) / nthr);
     for (int e = e0; e < e1 && affine.load(std::memory_order_relaxed); ++e)
