@@ -1,11 +1,11 @@
 // HIP kernels of the DGSEM operator for gfx950 (one workgroup per element).
 //
 // Paper map (Krais et al., FLEXI):
-//   k_lift  ... BR1 lifting of W = (u,v,w,T): Sec. 3.1, eq. discreteGradient, U* = mean of traces
-//   k_main  ... volume integral (weak eq. semiDiscrete / strong eq. semiDiscreteStrong / split
-//               flux differencing eq. semiDiscreteSplit), numerical surface flux (Riemann + BR1
-//               viscous mean), surface integral, -1/J scaling, and optionally the 2N-storage
-//               Runge-Kutta update of Sec. 4.4 fused into the epilogue.
+//   k_lift, k_lift_affine ... BR1 lifting of W = (u,v,w,T): Sec. 3.1, eq. discreteGradient, U* = mean of traces
+//   k_split, k_line, k_main . volume integral (split flux differencing eq. semiDiscreteSplit / weak eq.
+//               semiDiscrete and strong eq. semiDiscreteStrong / these for Navier-Stokes with mortars),
+//               numerical surface flux (Riemann + BR1 viscous mean), surface integral, -1/J scaling, and
+//               optionally the 2N-storage Runge-Kutta update of Sec. 4.4 fused into the epilogue.
 //   k_reduce .. partial results for the time step (eqs. CFLCondition, DFLCondition), quadrature
 //               integrals and the finiteness check, then one final pass.
 //
