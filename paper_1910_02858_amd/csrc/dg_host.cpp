@@ -13,7 +13,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -30,6 +29,8 @@
 using dg::NMAX;
 
 namespace {
+
+using dg::is_mortar_side;
 
 const char *status_name(int s) {
   switch (s) {
@@ -251,8 +252,6 @@ inline bool face_master(int e, int s, int nb, int ns) {
 
 // xgeo holds the mapping at the LGL nodes of degree ngeo (Sec. 2.1: the geometry degree N_geo is
 // independent of N); it is interpolated to the degree-N LGL nodes, where the curl form is taken
-inline bool is_mortar_side(const int8_t *mort, int q) { return mort && mort[q] != 0; }
-
 int build_geometry(int K, int N, int ngeo, int type, const double *xgeo, const int32_t *nbr, const int8_t *nside,
                    const int8_t *flip, const int8_t *mort, HostGeo &G, std::string &msg) {
   const int n = N + 1, n2 = n * n, n3 = n2 * n;
@@ -396,83 +395,6 @@ int build_geometry(int K, int N, int ngeo, int type, const double *xgeo, const i
         }
     }
   return DG_OK;
-}
-
-// Constant metric terms of every element (see dg::AFFINE_DOUBLES), or empty if one of them is not affine.
-// An element is affine if its coordinates lie on x = c + sum_d a_d xi_d, a_d from its eight corners, to the
-// rounding of the coordinates themselves (4 ulp of the largest): what the metric terms of its nodes differ by
-// is then rounding of the input (1e-13 relative at 48 elements per direction, N = 7), not geometry.
-std::vector<double> affine_constants(int K, int ngeo, const double *xgeo, const int32_t *nbr, const int8_t *nside,
-                                     const int8_t *mort) {
-  const int ng = ngeo + 1, ng3 = ng * ng * ng;
-  const Basis1D B = make_basis(ngeo, DG_NODES_LGL);
-  std::vector<double> C((size_t)K * dg::AFFINE_DOUBLES, 0.0);
-  std::vector<xf> Ja((size_t)K * 9);
-  std::atomic<bool> affine{true};
-  // elements are independent: split them over host threads, which all stop at the first that is not affine
-  unsigned nthr = std::thread::hardware_concurrency();
-  if (const char *env = std::getenv("OMP_NUM_THREADS")) nthr = (unsigned)std::max(1, std::atoi(env));
-  nthr = std::max(1u, std::min(nthr, 32u));
-  if ((size_t)K < 64 * (size_t)nthr) nthr = 1;
-  auto element = [&](int e) -> bool {
-    xf A[3][3], c[3];  // A[d] = dx/dxi_d
-    for (int x = 0; x < 3; ++x) {
-      const double *X = xgeo + ((size_t)e * 3 + x) * ng3;
-      double big = 0.0;
-      for (int q = 0; q < ng3; ++q) big = std::max(big, std::fabs(X[q]));
-      c[x] = A[0][x] = A[1][x] = A[2][x] = 0.0L;
-      for (int k = 0; k < 8; ++k) {
-        const int i = (k & 1) ? ngeo : 0, j = (k & 2) ? ngeo : 0, l = (k & 4) ? ngeo : 0;
-        const xf v = (xf)X[i + ng * (j + ng * l)] / 8.0L;
-        c[x] += v;
-        A[0][x] += (k & 1) ? v : -v; A[1][x] += (k & 2) ? v : -v; A[2][x] += (k & 4) ? v : -v;
-      }
-      const xf tol = 4.0L * 2.220446049250313e-16L * big;
-      for (int l = 0; l < ng; ++l)
-        for (int j = 0; j < ng; ++j)
-          for (int i = 0; i < ng; ++i) {
-            const xf at = c[x] + A[0][x] * B.x[i] + A[1][x] * B.x[j] + A[2][x] * B.x[l];
-            if (!(std::fabs((xf)X[i + ng * (j + ng * l)] - at) <= tol)) return false;
-          }
-    }
-    double *o = C.data() + (size_t)e * dg::AFFINE_DOUBLES;
-    xf J = 0.0L;
-    for (int i = 0; i < 3; ++i) {
-      const xf *p = A[(i + 1) % 3], *q = A[(i + 2) % 3];
-      for (int d = 0; d < 3; ++d) {
-        const int d1 = (d + 1) % 3, d2 = (d + 2) % 3;
-        Ja[(size_t)e * 9 + i * 3 + d] = p[d1] * q[d2] - p[d2] * q[d1];
-        o[i * 3 + d] = (double)Ja[(size_t)e * 9 + i * 3 + d];
-        if (i == 0) J += A[0][d] * Ja[(size_t)e * 9 + d];
-      }
-    }
-    if (!(J > 0.0L)) return false;
-    o[9] = (double)(1.0L / J);
-    return true;
-  };
-  if (!element(0)) return {};  // a curved mesh starts no threads
-  auto work = [&](unsigned tid) {
-    const int e0 = (int)((size_t)K * tid / nthr), e1 = (int)((size_t)K * (tid + 1) / nthr);
-    for (int e = e0; e < e1 && affine.load(std::memory_order_relaxed); ++e)
-      if (!element(e)) affine = false;
-  };
-  if (nthr == 1) {
-    work(0);
-  } else {
-    std::vector<std::thread> pool;
-    for (unsigned t = 0; t < nthr; ++t) pool.emplace_back(work, t);
-    for (auto &th : pool) th.join();
-  }
-  if (!affine) return {};
-  for (int e = 0; e < K; ++e)
-    for (int s = 0; s < 6; ++s) {
-      const int nb = nbr[e * 6 + s], ns = nside[e * 6 + s];
-      const bool own = is_mortar_side(mort, e * 6 + s) || face_master(e, s, nb, ns);
-      const xf *m = own ? &Ja[(size_t)e * 9 + (s >> 1) * 3] : &Ja[(size_t)nb * 9 + (ns >> 1) * 3];
-      const double sg = own ? ((s & 1) ? 1.0 : -1.0) : ((ns & 1) ? -1.0 : 1.0);
-      for (int d = 0; d < 3; ++d) C[(size_t)e * dg::AFFINE_DOUBLES + 10 + 3 * s + d] = sg * (double)m[d];
-    }
-  return C;
 }
 
 // face codes for the kernels (see dg::Geo::fc); empty on a structured mesh
@@ -892,7 +814,8 @@ int dg_init(const dg_mesh *mesh, int N, int node_type, const dg_scheme *sc, void
                           mesh->mortar, G, msg);
   if (rc) { delete h; return rc; }
   const std::vector<uint8_t> fc = face_codes(mesh);
-  const std::vector<double> Jc = affine_constants(K, mesh->n_geo, mesh->xgeo, mesh->nbr_elem, mesh->nbr_side, mesh->mortar);
+  const std::vector<double> Jc = dg::affine_constants(K, mesh->n_geo + 1, make_basis(mesh->n_geo, DG_NODES_LGL).x.data(),
+                                                      mesh->xgeo, mesh->nbr_elem, mesh->nbr_side, mesh->mortar);
   for (int q = 0; q < 6 * K; ++q)
     if (mesh->nbr_elem[q] < 0) {
       h->has_boundary = true;

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/dgsem.h"
+#include "dg_affine.h"
 
 namespace dg {
 
@@ -41,10 +42,6 @@ struct MortarDesc {
   int es[4], ss[4], o[4], sl[4];   // small sides by position: element, side, orientation code, slot
 };
 
-// Constant metric terms of an affine element: Ja^i_d at i*3+d, 1/J at 9, and the outward scaled normal of
-// every side (the master's, negated on slaves) at 10 + 3*side + d.
-constexpr int AFFINE_DOUBLES = 28;
-
 // Device-resident geometry of one mesh.
 struct Geo {
   const double *Ja;   // [K][9][n3]: Ja^i_d at (i*3+d)
@@ -58,8 +55,7 @@ struct Geo {
   const uint8_t *fc;
   const Tab *tab;
   int K;
-  // [K][AFFINE_DOUBLES] where every element of the mesh is affine (its nodes lie on an affine map of the
-  // reference cube to the rounding of the coordinates), else NULL
+  // [K][AFFINE_DOUBLES] where every element of the mesh is affine (affine_constants), else NULL
   const double *Jc;
   // non-conforming faces (NULL without): slot of every side [K][6] (-1 for conforming sides), and
   // per slot the side's outward numerical flux times the surface element minus the BR1 viscous
