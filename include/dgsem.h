@@ -354,8 +354,9 @@ const char *dg_last_error(const dg_handle *h);
  * share the equations, the volume flux and the Riemann solver, and use the split form on LGL
  * nodes.  A stage launches, for each degree present, one lifting kernel (Navier-Stokes) and one
  * operator kernel over the concatenated elements of all members of that degree, on the stream
- * of members[0] (read at every call).  Members are referenced, not copied: they must outlive
- * the batch, and their gradient scratch is used by the batch's kernels.  Arrays passed below
+ * of members[0] (read at every call).  Members are referenced, not copied, and their
+ * gradient scratch is used by the batch's kernels; a member destroyed before the batch (dg_destroy) is
+ * freed with it, so the two may be destroyed in either order.  Arrays passed below
  * have one entry per member, in the order given to dg_batch_create.
  *
  * dg_batch_create  -> DG_ERR_UNSUPPORTED if a member is not split/LGL, has non-conforming faces or

@@ -299,6 +299,7 @@ int dg_batch_create(dg_handle *const *members, int n_members, dg_batch **out) {
   dg_batch *b = new (std::nothrow) dg_batch();
   if (!b) return DG_ERR_OOM;
   b->mem.assign(members, members + n_members);
+  for (dg_handle *h : b->mem) h->refs.fetch_add(1);
   b->ns = h0->sc.eqn == DG_NAVIER_STOKES;
   b->vf = h0->sc.volflux;
   int offset = 0;
@@ -601,6 +602,7 @@ void dg_batch_destroy(dg_batch *b) {
   for (hipEvent_t ev : b->br_ev) (void)hipEventDestroy(ev);
   for (hipStream_t st : b->br) (void)hipStreamDestroy(st);
   if (b->cap) (void)hipStreamDestroy(b->cap);
+  for (dg_handle *h : b->mem) dg_destroy(h);
   delete b;
 }
 

@@ -1416,7 +1416,7 @@ int dg_fv_switch(dg_handle *h, double *U) {
 }
 
 void dg_destroy(dg_handle *h) {
-  if (!h) return;
+  if (!h || h->refs.fetch_sub(1) > 1) return;  // a batch still holds it
   for (int i = 0; i < 5; ++i)
     if (h->ev[i]) (void)hipEventDestroy(h->ev[i]);
   (void)hipFree(h->d_Ja); (void)hipFree(h->d_sJ); (void)hipFree(h->d_fn); (void)hipFree(h->d_nbr);

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -260,6 +261,7 @@ int launch_mass(const double *sJ, const double *w, int n, size_t total, double *
 struct dg_handle {
   int K = 0, N = 0, n = 0, n2 = 0, n3 = 0, node_type = 0;
   int device = -1;  // HIP device current at dg_init
+  std::atomic<int> refs{1};  // the caller's and every batch's: the last dg_destroy or dg_batch_destroy frees it
   dg_scheme sc{};
   dg::Phys ph{};
   hipStream_t stream = nullptr;
