@@ -373,8 +373,8 @@ const char *dg_last_error(const dg_handle *h);
  * dg_batch_step    : one full step of the five-stage scheme of dg_rk_coefficients for every
  *                     member: reads U[i], leaves the new state in U_out[i]; U[i] (overwritten
  *                     with the fourth stage) and R[i] are working storage.  use_graph != 0
- *                     captures the five stages into a HIP graph on first use of an argument set
- *                     and replays it afterwards (ordered after the caller's queued work on the
+ *                     captures the five stages into HIP graphs on first use of an argument set
+ *                     and replays them afterwards (ordered after the caller's queued work on the
  *                     members[0] stream, and later work on that stream after it).
  * dg_batch_tune    : times every elements-per-workgroup choice (1, 2, 4 as built for the
  *                     degree) of both kernels of every degree on the states U (read only;

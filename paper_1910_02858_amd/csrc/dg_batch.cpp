@@ -37,10 +37,16 @@ struct Table {
   dg::Member *dev = nullptr;
 };
 
+// the step graphs of one argument set: one per group, or a single one for the fused launches
 struct Graph {
   uint64_t key = 0;
-  hipGraphExec_t exec = nullptr;
+  std::vector<hipGraphExec_t> exec;
 };
+
+void destroy(Graph &g) {
+  for (hipGraphExec_t e : g.exec) (void)hipGraphExecDestroy(e);
+  g.exec.clear();
+}
 
 uint64_t fnv1a(const void *p, size_t n, uint64_t h = 1469598103934665603ull) {
   const unsigned char *c = (const unsigned char *)p;
@@ -60,13 +66,11 @@ struct dg_batch {
   std::vector<Group> groups;
   std::vector<Table> tables;  // most recently used last
   std::vector<Graph> graphs;
-  hipStream_t cap = nullptr;  // private stream for graph capture and replay
-  hipEvent_t ev_in = nullptr, ev_out = nullptr;
-  // one branch per degree group inside the step graph (the groups share no data), forked from
-  // and joined to the capture stream with events
+  // graph capture and replay: one private stream per degree group (the groups share no data, so
+  // their launches may overlap), each with the event that the caller's stream waits for
   std::vector<hipStream_t> br;
   std::vector<hipEvent_t> br_ev;
-  hipEvent_t fork_ev = nullptr;
+  hipEvent_t ev_in = nullptr;
   bool ns = false;
   int vf = 0;
   int fused = 0;  // 1: one lifting and one operator launch per stage for all degrees
@@ -239,25 +243,30 @@ int launch_stage(dg_batch *b, const dg::Member *table, hipStream_t st) {
   return DG_OK;
 }
 
-#ifndef DG_BATCH_BRANCHES
-#define DG_BATCH_BRANCHES 1
-#endif
-// the five stages of a step into the capture stream: with several degree groups, each group's
-// ten launches on its own branch (fork and join through events), so that the graph lets the
-// groups' kernels overlap
-int capture_step(dg_batch *b, const dg::Member *const *tabs) {
-  if (b->fused || b->groups.size() < 2 || !DG_BATCH_BRANCHES) {
-    for (int s = 0; s < 5; ++s)
-      if (int rc = launch_stage(b, tabs[s], b->cap)) return rc;
-    return DG_OK;
-  }
-  if (hipEventRecord(b->fork_ev, b->cap) != hipSuccess) return bfail(b, DG_ERR_HIP, "graph fork failed");
-  for (size_t gi = 0; gi < b->groups.size(); ++gi) {
-    if (hipStreamWaitEvent(b->br[gi], b->fork_ev, 0) != hipSuccess) return bfail(b, DG_ERR_HIP, "graph fork failed");
-    for (int s = 0; s < 5; ++s)
-      if (int rc = launch_group_stage(b, b->groups[gi], tabs[s], b->br[gi])) return rc;
-    if (hipEventRecord(b->br_ev[gi], b->br[gi]) != hipSuccess || hipStreamWaitEvent(b->cap, b->br_ev[gi], 0) != hipSuccess)
-      return bfail(b, DG_ERR_HIP, "graph join failed");
+// The five stages of a step as graphs, each a plain chain on its own stream: the group's ten launches, or the
+// fused pairs.  The overlap of the groups is left to their streams.  One graph with a branch per group, forked and
+// joined by events inside the capture, ended in a segmentation fault in the runtime for five groups.
+int capture_step(dg_batch *b, const dg::Member *const *tabs, Graph &gr) {
+  const size_t ng = b->fused ? 1 : b->groups.size();
+  for (size_t gi = 0; gi < ng; ++gi) {
+    hipStream_t st = b->br[gi];
+    if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess)
+      return bfail(b, DG_ERR_HIP, "stream capture could not start");
+    int rc = DG_OK;
+    for (int s = 0; s < 5 && !rc; ++s)
+      rc = b->fused ? launch_stage_fused(b, tabs[s], st) : launch_group_stage(b, b->groups[gi], tabs[s], st);
+    hipGraph_t graph = nullptr;
+    const hipError_t ec = hipStreamEndCapture(st, &graph);
+    if (rc) {
+      if (graph) (void)hipGraphDestroy(graph);
+      return rc;
+    }
+    if (ec != hipSuccess || !graph) return bfail(b, DG_ERR_HIP, "stream capture failed");
+    hipGraphExec_t exec = nullptr;
+    const hipError_t ei = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(graph);
+    if (ei != hipSuccess) return bfail(b, DG_ERR_HIP, "graph instantiation failed");
+    gr.exec.push_back(exec);
   }
   return DG_OK;
 }
@@ -323,10 +332,7 @@ int dg_batch_create(dg_handle *const *members, int n_members, dg_batch **out) {
     }
     b->groups.push_back(g);
   }
-  bool ok = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&b->fork_ev, hipEventDisableTiming) == hipSuccess;
+  bool ok = hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming) == hipSuccess;
   for (size_t gi = 0; ok && gi < b->groups.size(); ++gi) {
     hipStream_t st = nullptr;
     hipEvent_t ev = nullptr;
@@ -403,35 +409,34 @@ int dg_batch_step(dg_batch *b, double *const *U, double *const *U_out, double *c
     key = fnv1a(&g.epb_main, sizeof(int), key);
   }
   key = fnv1a(&b->fused, sizeof(int), key);
-  hipGraphExec_t exec = nullptr;
+  const Graph *run = nullptr;
   for (const Graph &gr : b->graphs)
-    if (gr.key == key) exec = gr.exec;
-  if (!exec) {
+    if (gr.key == key) run = &gr;
+  if (!run) {
     if ((int)b->graphs.size() >= kMaxGraphs) {
-      if (hipStreamSynchronize(b->cap) != hipSuccess) return bfail(b, DG_ERR_HIP, "stream synchronisation failed");
-      (void)hipGraphExecDestroy(b->graphs.front().exec);
+      for (hipStream_t st : b->br)
+        if (hipStreamSynchronize(st) != hipSuccess) return bfail(b, DG_ERR_HIP, "stream synchronisation failed");
+      destroy(b->graphs.front());
       b->graphs.erase(b->graphs.begin());
     }
-    if (hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal) != hipSuccess)
-      return bfail(b, DG_ERR_HIP, "stream capture could not start");
-    const int lrc = capture_step(b, tabs);
-    hipGraph_t graph = nullptr;
-    const hipError_t ec = hipStreamEndCapture(b->cap, &graph);
-    if (lrc) {
-      if (graph) (void)hipGraphDestroy(graph);
-      return lrc;
+    Graph gr;
+    gr.key = key;
+    rc = capture_step(b, tabs, gr);
+    if (rc) {
+      destroy(gr);
+      return rc;
     }
-    if (ec != hipSuccess || !graph) return bfail(b, DG_ERR_HIP, "stream capture failed");
-    const hipError_t ei = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    if (ei != hipSuccess) return bfail(b, DG_ERR_HIP, "graph instantiation failed");
-    b->graphs.push_back({key, exec});
+    b->graphs.push_back(gr);
+    run = &b->graphs.back();
   }
-  // order the replay after the caller's queued work and the caller's later work after it
-  if (hipEventRecord(b->ev_in, b->stream()) != hipSuccess || hipStreamWaitEvent(b->cap, b->ev_in, 0) != hipSuccess ||
-      hipGraphLaunch(exec, b->cap) != hipSuccess || hipEventRecord(b->ev_out, b->cap) != hipSuccess ||
-      hipStreamWaitEvent(b->stream(), b->ev_out, 0) != hipSuccess)
-    return bfail(b, DG_ERR_HIP, "graph launch failed");
+  // order the replays after the caller's queued work and the caller's later work after them
+  bool ok = hipEventRecord(b->ev_in, b->stream()) == hipSuccess;
+  for (size_t gi = 0; gi < run->exec.size() && ok; ++gi)
+    ok = hipStreamWaitEvent(b->br[gi], b->ev_in, 0) == hipSuccess && hipGraphLaunch(run->exec[gi], b->br[gi]) == hipSuccess &&
+         hipEventRecord(b->br_ev[gi], b->br[gi]) == hipSuccess;
+  for (size_t gi = 0; gi < run->exec.size() && ok; ++gi)
+    ok = hipStreamWaitEvent(b->stream(), b->br_ev[gi], 0) == hipSuccess;
+  if (!ok) return bfail(b, DG_ERR_HIP, "graph launch failed");
   return DG_OK;
 }
 
@@ -591,17 +596,14 @@ const char *dg_batch_last_error(const dg_batch *b) { return b ? b->err.c_str() :
 void dg_batch_destroy(dg_batch *b) {
   if (!b) return;
   if (!b->mem.empty()) (void)hipStreamSynchronize(b->stream());
-  if (b->cap) (void)hipStreamSynchronize(b->cap);
-  for (Graph &g : b->graphs) (void)hipGraphExecDestroy(g.exec);
+  for (hipStream_t st : b->br) (void)hipStreamSynchronize(st);
+  for (Graph &g : b->graphs) destroy(g);
   for (Table &t : b->tables) (void)hipFree(t.dev);
   for (Group &g : b->groups)
     if (g.d_first) (void)hipFree(g.d_first);
   if (b->ev_in) (void)hipEventDestroy(b->ev_in);
-  if (b->ev_out) (void)hipEventDestroy(b->ev_out);
-  if (b->fork_ev) (void)hipEventDestroy(b->fork_ev);
   for (hipEvent_t ev : b->br_ev) (void)hipEventDestroy(ev);
   for (hipStream_t st : b->br) (void)hipStreamDestroy(st);
-  if (b->cap) (void)hipStreamDestroy(b->cap);
   for (dg_handle *h : b->mem) dg_destroy(h);
   delete b;
 }
