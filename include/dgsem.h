@@ -384,11 +384,13 @@ const char *dg_last_error(const dg_handle *h);
  *                     codes, at most 8 degrees), it then also times one stage of all members
  *                     with the per-degree launches against one lifting and one operator launch
  *                     for all degrees (512-lane workgroups of the degree's elements, the
- *                     largest degree's LDS) and keeps the faster; the results are the same bits.
+ *                     largest degree's LDS) and keeps the faster, once as the launches follow
+ *                     each other on the stream and once as a step's graphs run them (the degrees
+ *                     may overlap there); the results are the same bits.
  * dg_batch_set_tile: fixes the choices of degree N by hand.
  * dg_batch_set_fused: 1 selects the single pair of launches per stage, 0 the per-degree
  *                     launches (DG_ERR_UNSUPPORTED where one launch cannot cover every degree).
- * dg_batch_fused   : the current choice (0 or 1).
+ * dg_batch_fused   : the current choice (0 or 1) of launches outside a step's graphs.
  * dg_batch_info    : writes N, members, elements, elements per workgroup of the lifting and of
  *                     the operator kernel for each degree present (5 ints each, up to cap ints)
  *                     and returns the number of degrees. */

@@ -24,8 +24,9 @@ constexpr int kMaxGraphs = 16;  // cached step graphs
 
 struct Group {
   int N = 0;
-  std::vector<int> idx;  // member indices (caller order) of this degree
+  std::vector<int> idx;  // member indices of this degree: those on affine meshes, then the others
   int total = 0;         // elements
+  int n_affine = 0;      // of the affine members
   int offset = 0;        // first descriptor of the group in every table
   int *d_first = nullptr;
   int epb_lift = 1, epb_main = 1;
@@ -73,7 +74,8 @@ struct dg_batch {
   hipEvent_t ev_in = nullptr;
   bool ns = false;
   int vf = 0;
-  int fused = 0;  // 1: one lifting and one operator launch per stage for all degrees
+  // 1: one lifting and one operator launch per stage for all degrees; for launches one by one, and for a step's graphs
+  int fused = 0, fused_graph = 0;
   std::string err;
 
   hipStream_t stream() const { return mem[0]->stream; }
@@ -114,12 +116,9 @@ dg::BatchView view(const dg_batch *b, const Group &g, const dg::Member *table) {
   v.total = g.total;
   v.tab = b->mem[g.idx[0]]->d_tab;
   v.general = 0;
-  int affine = 0;
-  for (int i : g.idx) {
+  for (int i : g.idx)
     if (b->mem[i]->d_fc) v.general = 1;
-    if (b->mem[i]->d_Jc) ++affine;
-  }
-  v.affine = affine == 0 ? dg::AFF_NONE : (affine == v.count ? dg::AFF_ALL : dg::AFF_MIXED);
+  v.n_affine = g.n_affine;
   return v;
 }
 
@@ -208,11 +207,9 @@ int launch_stage_fused(dg_batch *b, const dg::Member *table, hipStream_t st) {
     const Group &g = b->groups[gi];
     fl.v[gi] = fs.v[gi] = view(b, g, table);
     fl.N[gi] = fs.N[gi] = g.N;
-    // (a group with affine and other members: one element per workgroup)
-    const bool mixed = fl.v[gi].affine == dg::AFF_MIXED;
-    const int el = mixed ? 1 : dg::fused_epb(g.N, true), es = mixed ? 1 : dg::fused_epb(g.N, false);
-    fl.start[gi + 1] = fl.start[gi] + (g.total + el - 1) / el;
-    fs.start[gi + 1] = fs.start[gi] + (g.total + es - 1) / es;
+    const int el = dg::fused_epb(g.N, true), es = dg::fused_epb(g.N, false);
+    fl.start[gi + 1] = fl.start[gi] + dg::affine_blocks(fl.v[gi], el) + dg::other_blocks(fl.v[gi], el);
+    fs.start[gi + 1] = fs.start[gi] + dg::affine_blocks(fs.v[gi], es) + dg::other_blocks(fs.v[gi], es);
   }
   if (b->ns) {
     const int rc = dg::launch_fused_lift(fl, st);
@@ -247,14 +244,14 @@ int launch_stage(dg_batch *b, const dg::Member *table, hipStream_t st) {
 // fused pairs.  The overlap of the groups is left to their streams.  One graph with a branch per group, forked and
 // joined by events inside the capture, ended in a segmentation fault in the runtime for five groups.
 int capture_step(dg_batch *b, const dg::Member *const *tabs, Graph &gr) {
-  const size_t ng = b->fused ? 1 : b->groups.size();
+  const size_t ng = b->fused_graph ? 1 : b->groups.size();
   for (size_t gi = 0; gi < ng; ++gi) {
     hipStream_t st = b->br[gi];
     if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess)
       return bfail(b, DG_ERR_HIP, "stream capture could not start");
     int rc = DG_OK;
     for (int s = 0; s < 5 && !rc; ++s)
-      rc = b->fused ? launch_stage_fused(b, tabs[s], st) : launch_group_stage(b, b->groups[gi], tabs[s], st);
+      rc = b->fused_graph ? launch_stage_fused(b, tabs[s], st) : launch_group_stage(b, b->groups[gi], tabs[s], st);
     hipGraph_t graph = nullptr;
     const hipError_t ec = hipStreamEndCapture(st, &graph);
     if (rc) {
@@ -315,8 +312,12 @@ int dg_batch_create(dg_handle *const *members, int n_members, dg_batch **out) {
   for (int N = 1; N <= dg::NMAX; ++N) {
     Group g;
     g.N = N;
-    for (int i = 0; i < n_members; ++i)
-      if (members[i]->N == N) g.idx.push_back(i);
+    for (int affine = 1; affine >= 0; --affine)
+      for (int i = 0; i < n_members; ++i)
+        if (members[i]->N == N && (members[i]->d_Jc != nullptr) == (affine == 1)) {
+          g.idx.push_back(i);
+          if (affine) g.n_affine += members[i]->K;
+        }
     if (g.idx.empty()) continue;
     std::vector<int> first(g.idx.size() + 1, 0);
     for (size_t j = 0; j < g.idx.size(); ++j) first[j + 1] = first[j] + members[g.idx[j]]->K;
@@ -408,7 +409,7 @@ int dg_batch_step(dg_batch *b, double *const *U, double *const *U_out, double *c
     key = fnv1a(&g.epb_lift, sizeof(int), key);
     key = fnv1a(&g.epb_main, sizeof(int), key);
   }
-  key = fnv1a(&b->fused, sizeof(int), key);
+  key = fnv1a(&b->fused_graph, sizeof(int), key);
   const Graph *run = nullptr;
   for (const Graph &gr : b->graphs)
     if (gr.key == key) run = &gr;
@@ -554,6 +555,32 @@ int dg_batch_tune(dg_batch *b, const double *const *U, int repeats) {
       (void)hipEventElapsedTime(&t_mode[mode], e0, e1);
     }
     b->fused = (!rc && t_mode[1] < t_mode[0]) ? 1 : 0;
+    // the five stages as a step's graphs run them: every group's on its own stream, or the fused pairs on one
+    for (int mode = 0; mode < 2 && !rc; ++mode) {
+      auto step = [&]() -> bool {
+        const size_t ng = mode ? 1 : b->groups.size();
+        bool ok = hipEventRecord(b->ev_in, st) == hipSuccess;
+        for (size_t gi = 0; gi < ng && ok; ++gi) {
+          ok = hipStreamWaitEvent(b->br[gi], b->ev_in, 0) == hipSuccess;
+          for (int s = 0; s < 5 && ok && !rc; ++s)
+            rc = mode ? launch_stage_fused(b, table, b->br[gi]) : launch_group_stage(b, b->groups[gi], table, b->br[gi]);
+          ok = ok && hipEventRecord(b->br_ev[gi], b->br[gi]) == hipSuccess;
+        }
+        for (size_t gi = 0; gi < ng && ok; ++gi) ok = hipStreamWaitEvent(st, b->br_ev[gi], 0) == hipSuccess;
+        if (!ok && !rc) rc = bfail(b, DG_ERR_HIP, "tuning launch failed");
+        return ok && !rc;
+      };
+      (void)step();  // warm-up
+      (void)hipEventRecord(e0, st);
+      for (int r = 0; r < repeats && !rc; ++r) (void)step();
+      (void)hipEventRecord(e1, st);
+      if (rc || hipEventSynchronize(e1) != hipSuccess) {
+        rc = rc ? rc : DG_ERR_HIP;
+        break;
+      }
+      (void)hipEventElapsedTime(&t_mode[mode], e0, e1);
+    }
+    b->fused_graph = (!rc && t_mode[1] < t_mode[0]) ? 1 : 0;
     if (hipStreamSynchronize(st) != hipSuccess && !rc) rc = bfail(b, DG_ERR_HIP, "stream synchronisation failed");
     for (size_t i = 0; i < n; ++i) {
       if (outs[i]) (void)hipFree(outs[i]);
@@ -569,7 +596,7 @@ int dg_batch_tune(dg_batch *b, const double *const *U, int repeats) {
 int dg_batch_set_fused(dg_batch *b, int fused) {
   if (!b || (fused != 0 && fused != 1)) return DG_ERR_ARG;
   if (fused && !fusable(b)) return bfail(b, DG_ERR_UNSUPPORTED, "a degree above 7 or a member with face codes");
-  b->fused = fused;
+  b->fused = b->fused_graph = fused;
   return DG_OK;
 }
 

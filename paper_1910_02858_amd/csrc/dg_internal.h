@@ -159,17 +159,25 @@ struct Member {
   double a, b, dt;  // stage coefficients: R = a R + dt L(U); out = U + b R
 };
 
-// All members of one degree N: m[0..count), element prefix sums first[0..count] (device),
-// total = first[count]; tab = the 1D tables of degree N (identical for every member).
+// All members of one degree N: m[0..count), those on affine meshes (Geo::Jc) first, element prefix sums
+// first[0..count] (device), total = first[count]; tab = the 1D tables of degree N (identical for every member).
 struct BatchView {
   const Member *m;
   const int *first;
   int count, total;
   const Tab *tab;
-  int general;  // some member's mesh has face codes (Geo::fc): launch the kernels that read them
-  int affine;   // AFF_NONE, AFF_ALL or AFF_MIXED: no, every or some member's elements are affine (Geo::Jc)
+  int general;    // some member's mesh has face codes (Geo::fc): launch the kernels that read them
+  int n_affine;   // elements of the affine members
 };
-enum { AFF_NONE = 0, AFF_ALL = 1, AFF_MIXED = 2 };
+
+// The two kinds of members take different code with different numbers of workgroup barriers, so their elements never
+// share a workgroup: each kind's range is rounded up to whole workgroups of EPB elements.
+struct BatchBlock {
+  int item, end;  // a workgroup's first element, and the end of its kind's
+  bool affine;
+};
+__host__ __device__ inline int affine_blocks(const BatchView &v, int epb) { return (v.n_affine + epb - 1) / epb; }
+__host__ __device__ inline int other_blocks(const BatchView &v, int epb) { return (v.total - v.n_affine + epb - 1) / epb; }
 
 // elements per workgroup the batched kernels are built for (1, 2, 4 up to this bound)
 __host__ __device__ constexpr int batch_max_epb(int N) { return N <= 3 ? 4 : (N <= 5 ? 2 : 1); }
@@ -183,6 +191,18 @@ __host__ __device__ inline int xcd_element(int b, int K) {
   return (b & 7) * per + (b >> 3);
 }
 __host__ __device__ inline int xcd_grid(int K) { return 8 * ((K + 7) / 8); }
+
+// The elements of workgroup b of a launch over one degree, item >= end: none.  The members on curved meshes, whose
+// elements take longer, come first, and each XCD takes its share of either kind (one range over both would leave the
+// curved elements to some of the XCDs).
+__host__ __device__ inline int batch_grid(const BatchView &v, int epb) {
+  return xcd_grid(other_blocks(v, epb)) + xcd_grid(affine_blocks(v, epb));
+}
+__host__ __device__ inline BatchBlock batch_block(const BatchView &v, int epb, int b) {
+  const int no = other_blocks(v, epb), go = xcd_grid(no);
+  if (b < go) return {v.n_affine + xcd_element(b, no) * epb, v.total, false};
+  return {xcd_element(b - go, affine_blocks(v, epb)) * epb, v.n_affine, true};
+}
 
 // The neighbour's face point matching face point (a,b) of side s of element e: its direction,
 // indices along the other two directions, whether it lies on the neighbour's +xi side, and

@@ -896,10 +896,10 @@ __device__ __forceinline__ void lift_affine(const Geo &g, const Phys &ph, const 
   const LineSlots<n> slot(act ? dir : 0, act ? a : 0, act ? b : 0);
   double f[4][n];      // W of the line's nodes; the velocities are kept for the viscous work
   double ws[2][4];     // surface means at its ends
-  double nd[3];        // Ja^dir, +- the outward normal of the line's two faces times s-hat
-#pragma unroll
-  for (int d = 0; d < 3; ++d) nd[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
+  double nd[3] = {0.0, 0.0, 0.0};  // Ja^dir, +- the outward normal of the line's two faces times s-hat
   if (act) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) nd[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
 #pragma unroll
     for (int m = 0; m < n; ++m) {
       const int q = slot(m);
@@ -2395,8 +2395,11 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
 // degree; EPB elements share a workgroup (one slot of Sz<N>::NT threads each, SplitSz<N>::NT in
 // the split-form kernel, wave aligned).
 // Each slot finds its member by bisection of the element prefix sums.
-// AFF: AFF_NONE, AFF_ALL (every member's elements are affine) or AFF_MIXED, which takes each member's own
-// path, so that a member's result has the bits of its one-mesh launch whatever its neighbours in the batch.
+// AFF: no, every or some member's elements are affine.  AFF_MIXED takes each member's own path, so that a member's
+// result has the bits of its one-mesh launch whatever its neighbours in the batch; one launch for both kinds, at the
+// registers and LDS of the larger: a launch each took 201 us a step instead of 163 (16 members of degree 3 with 4^3 to
+// 7^3 elements).
+enum { AFF_NONE = 0, AFF_ALL = 1, AFF_MIXED = 2 };
 __device__ __forceinline__ int member_of(const int *first, int count, int item) {
   int lo = 0, hi = count - 1;
   while (lo < hi) {
@@ -2420,17 +2423,16 @@ __global__ void __launch_bounds__((lift_b_lanes<N, AFF>()) * EPB, (lift_b_minb<N
   __shared__ double sm[EPB * SM];
   __shared__ double sDh[TAB ? n * n : 1], sl[TAB ? 2 * n : 1], slh[TAB ? 2 * n : 1];
   if constexpr (TAB) lift_tables<N>(bv.tab, threadIdx.x, NT * EPB, sDh, sl, slh);
-  const int nblk = (bv.total + EPB - 1) / EPB;
-  const int blk = xcd_element(blockIdx.x, nblk);
-  if (blk >= nblk) return;
+  const BatchBlock B = batch_block(bv, EPB, blockIdx.x);
+  if (B.item >= B.end) return;
   const int slot = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int t = threadIdx.x - slot * NT;
-  const int item = blk * EPB + slot;
-  const bool valid = item < bv.total;
-  const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
+  const int item = B.item + slot;
+  const bool valid = item < B.end;
+  const int mi = member_of(bv.first, bv.count, valid ? item : B.end - 1);
   const Member &M = bv.m[mi];
   const int e = valid ? item - bv.first[mi] : 0;
-  if (AFF == AFF_ALL || (AFF == AFF_MIXED && M.g.Jc)) {
+  if (AFF == AFF_ALL || (AFF == AFF_MIXED && B.affine)) {
     lift_affine<N, true, LIFT_DIV, GEN, NT>(M.g, M.ph, bv.tab, e, valid, t, M.U, nullptr, nullptr, sm + slot * SM);
   } else {
     if constexpr (TAB) lift_body<N, true, LIFT_DIV, GEN>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm + slot * SM, sDh, sl, slh);
@@ -2441,17 +2443,16 @@ template <int N, bool NS, int VF, int EPB, bool GEN, int AFF>
 __global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N, VF, AFF == AFF_ALL)) k_split_b(BatchView bv) {
   constexpr int NT = SplitSz<N>::NT, L = AFF == AFF_ALL ? SplitLds<N>::AFFINE : SplitLds<N>::A;
   __shared__ double sm[EPB * L];
-  const int nblk = (bv.total + EPB - 1) / EPB;
-  const int blk = xcd_element(blockIdx.x, nblk);
-  if (blk >= nblk) return;
+  const BatchBlock B = batch_block(bv, EPB, blockIdx.x);
+  if (B.item >= B.end) return;
   const int slot = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int t = threadIdx.x - slot * NT;
-  const int item = blk * EPB + slot;
-  const bool valid = item < bv.total;
-  const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
+  const int item = B.item + slot;
+  const bool valid = item < B.end;
+  const int mi = member_of(bv.first, bv.count, valid ? item : B.end - 1);
   const Member &M = bv.m[mi];
   const int e = valid ? item - bv.first[mi] : 0;
-  if (AFF == AFF_ALL || (AFF == AFF_MIXED && M.g.Jc))
+  if (AFF == AFF_ALL || (AFF == AFF_MIXED && B.affine))
     split_body<N, NS, VF, GEN, false, true>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
   else
     split_body<N, NS, VF, GEN, false, false>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
@@ -3446,23 +3447,22 @@ int launch_main(const Geo &g, const Phys &ph, bool lgl, int eqn, int form, const
 
 template <int N, int EPB, int AFF>
 static int launch_batch_lift_t(const BatchView &bv, hipStream_t st) {
-  const dim3 grid(xcd_grid((bv.total + EPB - 1) / EPB)), block(lift_b_lanes<N, AFF>() * EPB);
+  const dim3 grid(batch_grid(bv, EPB)), block(lift_b_lanes<N, AFF>() * EPB);
   if (bv.general) hipLaunchKernelGGL((k_lift_b<N, EPB, true, AFF>), grid, block, 0, st, bv);
   else hipLaunchKernelGGL((k_lift_b<N, EPB, false, AFF>), grid, block, 0, st, bv);
   DG_CHECK_LAUNCH();
   return DG_OK;
 }
 
-// a group with affine and other members runs one element per workgroup, whatever the tile choice: the two
-// paths pass different numbers of workgroup barriers, so the slots of one workgroup may not differ
 template <int N, int EPB> static int launch_batch_lift_a(const BatchView &bv, hipStream_t st) {
-  if (bv.affine == AFF_MIXED) return launch_batch_lift_t<N, 1, AFF_MIXED>(bv, st);
-  return bv.affine == AFF_ALL ? launch_batch_lift_t<N, EPB, AFF_ALL>(bv, st) : launch_batch_lift_t<N, EPB, AFF_NONE>(bv, st);
+  if (bv.n_affine == 0) return launch_batch_lift_t<N, EPB, AFF_NONE>(bv, st);
+  if (bv.n_affine == bv.total) return launch_batch_lift_t<N, EPB, AFF_ALL>(bv, st);
+  return launch_batch_lift_t<N, EPB, AFF_MIXED>(bv, st);
 }
 
 template <int N, bool NS, int VF, int EPB, int AFF>
 static int launch_batch_split_t(const BatchView &bv, hipStream_t st) {
-  const dim3 grid(xcd_grid((bv.total + EPB - 1) / EPB)), block(SplitSz<N>::NT * EPB);
+  const dim3 grid(batch_grid(bv, EPB)), block(SplitSz<N>::NT * EPB);
   if (bv.general) hipLaunchKernelGGL((k_split_b<N, NS, VF, EPB, true, AFF>), grid, block, 0, st, bv);
   else hipLaunchKernelGGL((k_split_b<N, NS, VF, EPB, false, AFF>), grid, block, 0, st, bv);
   DG_CHECK_LAUNCH();
@@ -3470,9 +3470,9 @@ static int launch_batch_split_t(const BatchView &bv, hipStream_t st) {
 }
 
 template <int N, bool NS, int VF, int EPB> static int launch_batch_split_a(const BatchView &bv, hipStream_t st) {
-  if (bv.affine == AFF_MIXED) return launch_batch_split_t<N, NS, VF, 1, AFF_MIXED>(bv, st);
-  return bv.affine == AFF_ALL ? launch_batch_split_t<N, NS, VF, EPB, AFF_ALL>(bv, st)
-                              : launch_batch_split_t<N, NS, VF, EPB, AFF_NONE>(bv, st);
+  if (bv.n_affine == 0) return launch_batch_split_t<N, NS, VF, EPB, AFF_NONE>(bv, st);
+  if (bv.n_affine == bv.total) return launch_batch_split_t<N, NS, VF, EPB, AFF_ALL>(bv, st);
+  return launch_batch_split_t<N, NS, VF, EPB, AFF_MIXED>(bv, st);
 }
 
 template <int N, bool NS, int EPB>
@@ -3676,29 +3676,27 @@ __device__ __forceinline__ int fused_group(const FusedView &fv, int b) {
   return gi;
 }
 
-// elements of group bv per workgroup: one where affine and other members mix (the two paths pass different
-// numbers of workgroup barriers, so every slot of a workgroup takes the path of its first element's member)
-__device__ __forceinline__ int fused_slots(const BatchView &bv, int epb) { return bv.affine == AFF_MIXED ? 1 : epb; }
-__device__ __forceinline__ bool fused_affine(const BatchView &bv, int first_item) {
-  if (bv.affine != AFF_MIXED) return bv.affine == AFF_ALL;
-  return bv.m[member_of(bv.first, bv.count, first_item)].g.Jc != nullptr;
+// workgroup blk of group bv: its affine members' elements, then the others'
+__device__ __forceinline__ BatchBlock fused_block(const BatchView &bv, int epb, int blk) {
+  const int na = affine_blocks(bv, epb);
+  if (blk < na) return {blk * epb, bv.n_affine, true};
+  return {bv.n_affine + (blk - na) * epb, bv.total, false};
 }
 
 template <int N, bool NS, int VF>
 __device__ __forceinline__ void fused_split_group(const BatchView &bv, int blk, double *smem) {
-  using L = SplitLds<N>;
-  constexpr int NT = SplitSz<N>::NT, EPB = fused_epb_split<N>();
-  const int epb = fused_slots(bv, EPB);
+  constexpr int NT = SplitSz<N>::NT, EPB = fused_epb_split<N>(), L = SplitLds<N>::A;
+  const BatchBlock B = fused_block(bv, EPB, blk);
   const int raw = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int slot = raw < EPB ? raw : EPB - 1;
   const int t = threadIdx.x - raw * NT;
-  const int item = blk * epb + slot;
-  const bool valid = raw < epb && item < bv.total;
-  const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
+  const int item = B.item + slot;
+  const bool valid = raw < EPB && item < B.end;
+  const int mi = member_of(bv.first, bv.count, valid ? item : B.end - 1);
   const Member &M = bv.m[mi];
   const int e = valid ? item - bv.first[mi] : 0;
-  double *sm = smem + slot * L::A;
-  if (fused_affine(bv, blk * epb))
+  double *sm = smem + slot * L;
+  if (B.affine)
     split_body<N, NS, VF, 0, false, true>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
   else
     split_body<N, NS, VF, 0, false, false>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
@@ -3729,17 +3727,17 @@ __device__ __forceinline__ void fused_lift_group(const BatchView &bv, int blk, d
   using L = LiftLds<N>;
   constexpr int NT = Sz<N>::NT, EPB = fused_epb_lift<N>();
   lift_tables<N>(bv.tab, threadIdx.x, 512, sDh, sl, slh);
-  const int epb = fused_slots(bv, EPB);
+  const BatchBlock B = fused_block(bv, EPB, blk);
   const int raw = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int slot = raw < EPB ? raw : EPB - 1;
   const int t = threadIdx.x - raw * NT;
-  const int item = blk * epb + slot;
-  const bool valid = raw < epb && item < bv.total;
-  const int mi = member_of(bv.first, bv.count, valid ? item : bv.total - 1);
+  const int item = B.item + slot;
+  const bool valid = raw < EPB && item < B.end;
+  const int mi = member_of(bv.first, bv.count, valid ? item : B.end - 1);
   const Member &M = bv.m[mi];
   const int e = valid ? item - bv.first[mi] : 0;
   double *sm = smem + slot * (L::W + L::JA + L::WS);
-  if (fused_affine(bv, blk * epb))
+  if (B.affine)
     lift_affine<N, true, LIFT_DIV, 0, NT>(M.g, M.ph, bv.tab, e, valid, t, M.U, nullptr, nullptr, sm);
   else
     lift_body<N, true, LIFT_DIV, 0>(M.g, M.ph, e, valid, t, M.U, nullptr, nullptr, sm, sDh, sl, slh);
