@@ -17,6 +17,8 @@
 // the master's state as the left argument, so the two contributions cancel to rounding.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "dg_internal.h"
 #include "dg_lines.h"
 
@@ -1640,9 +1642,20 @@ __device__ __forceinline__ void riemann_vf(const Phys &ph, const double *UL, con
 // two-point state rho, u, v, w, beta|H (5 per node) and the metric terms Ja^i_d (9 per node; none on
 // affine elements); the accumulated result takes the place of the metric terms (affine: of the two-point
 // state) once every line has read them.
+// ENDS: whether the far ends' lanes also take the sums of their half of the line.  Pairs across the middle are then
+// evaluated twice (44 instead of 28 at N = 7, 22 by each lane), which pays for the short fluxes; with the logarithmic
+// means (VF 1) it does not (64 elements, curved: N = 7 125.7 us a step against 123.7, N = 8 161.7 against 154.9).  Where
+// both halves lie in one wave it cannot.
+template <int N, int VF> constexpr bool split_halves() { return EndsSz<N>::HALF % 64 == 0 && VF != 1; }
+
 template <int N> struct SplitLds {
   static constexpr int n = N + 1, n2 = n * n, n3 = n2 * n;
   static constexpr int A = 19 * n3, AFFINE = 10 * n3;
+  template <bool AFF, bool ENDS> static constexpr int nodes() { return line_apart<N, ENDS>() ? 20 * n3 : (AFF ? AFFINE : A); }
+  // ENDS without split sums: and the far ends' fluxes
+  template <int VF, bool AFF, bool ENDS> static constexpr int size() {
+    return nodes<AFF, ENDS>() + (ENDS && !split_halves<N, VF>() ? 15 * n2 : 0);
+  }
 };
 
 struct LineNode {  // a node of a line: its two-point state and the line direction's metric terms
@@ -1661,41 +1674,49 @@ struct LineNode {  // a node of a line: its two-point state and the line directi
 // element, at 2 waves per SIMD.
 // valid = false keeps the slot's lanes in step with the workgroup barriers without touching memory.
 // AFF: every element is affine, its metric terms and 1/J are the element's constants (Geo::Jc): 10 of the
-// 43 doubles per node are not read, and 41 KB of LDS at N = 7 instead of 78 fit three workgroups per CU.
+// 43 doubles per node are not read, and of the 41 KB of LDS at N = 7 instead of 78 four workgroups fit a CU; by
+// registers two do with the EC and central fluxes, four with the KEP flux (split_minb).
+// ENDS: a lane per end of every line (see EndsSz): the fluxes at the two ends are evaluated at once, and with the
+// short pair fluxes each lane sums one half of the line's nodes.  For degrees 1 and 2, where both ends' lanes fit the
+// one wave (1 M nodes, curved, KEP: N = 1 2570 -> 1797 us a step, N = 2 913 -> 756), and for small meshes (small_mesh).
 // mode 0 writes U_t, 1 the fused RK stage.  FVM: the sides that meet a finite-volume element take their
 // flux from Geo::fvFx.
-template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
+template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF, bool ENDS>
 __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const Tab *tab, int e, bool valid, int lane,
                                            const double *__restrict__ U, double *__restrict__ out,
                                            double *__restrict__ R, double ca, double cb, double dt, int mode,
                                            double *sm) {
   using S = Sz<N>;
-  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = SplitSz<N>::NT;
+  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = line_lanes<N, ENDS>(), NL = 3 * n2, NE = ENDS ? 1 : 2;
+  constexpr bool WU = split_halves<N, VF>();
+  constexpr bool SEP = line_apart<N, ENDS>();  // the directions' sums in LDS of their own
   constexpr int IT = (n3 + NT - 1) / NT;  // nodes per lane in the node loops
   const double gm1 = ph.gamma - 1.0, kg = 1.0 / gm1, gg = gm1 / ph.gamma;
   const double *Ue = U + (size_t)e * 5 * n3;
   const double *Jae = g.Ja + (size_t)e * 9 * n3;
   double *sU = sm, *sS = sm + 5 * n3, *sJ = sm + 10 * n3;  // node slots: div_slot
-  double *sAcc = AFF ? sS : sJ;
+  double *sAcc = AFF || line_apart<N, ENDS>() ? sS : sJ;
   AffineConst jc = nullptr;
   if constexpr (AFF) jc = affine_const(g, e);
   // the 1D tables through the scalar cache
   const __attribute__((address_space(4))) double *D = (const __attribute__((address_space(4))) double *)tab->D;
   const double lh0 = tab->lhm[0], lhN = tab->lhp[N];
   // this lane's line: direction, and its position (a, b) among the direction's lines, which is also the
-  // face point of its two ends
-  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(lane / n2) : lane / n2;
-  const int ab = lane - dir * n2, a = ab % n, b = ab / n;
-  const bool act = valid && lane < 3 * n2;
+  // face point of its two ends; ENDS: and the end whose flux it evaluates
+  const int end = line_end<N, ENDS>(lane), line = lane - end * EndsSz<N>::HALF;
+  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(line / n2) : line / n2;
+  const int ab = line - dir * n2, a = ab % n, b = ab / n;
+  const bool act = valid && line < NL && end < 2;
   // the two end faces' neighbours first (loads return in order: behind the others, the neighbours' traces
   // would wait for all of them), then the state and metric terms for LDS and the faces' other sides
-  int nb2[2] = {0, 0};
-  NbFace f2[2];
+  int nb2[NE] = {};
+  NbFace f2[NE];
 #pragma unroll
-  for (int sd = 0; sd < 2; ++sd)
+  for (int x = 0; x < NE; ++x)
     if (act) {
-      nb2[sd] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
-      f2[sd] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
+      const int sd = ENDS ? end : x;
+      nb2[x] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
+      f2[x] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
     }
   double Uq[IT][5];
 #pragma unroll
@@ -1715,39 +1736,39 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       for (int c = 0; c < 9; ++c) Jq[it][c] = Jae[c * n3 + t];
     }
   }
-  double Ux[2][5], Vo[2][4], Vn[2][4];  // the end faces: the other side's state, both sides' viscous fluxes
-  int kind[2];                // -1 inner face, else the boundary kind; -2 a face whose flux is given (Ux)
+  double Ux[NE][5], Vo[NE][4], Vn[NE][4];  // the end faces: the other side's state, both sides' viscous fluxes
+  int kind[NE];                // -1 inner face, else the boundary kind; -2 a face whose flux is given (Ux)
 #pragma unroll
-  for (int sd = 0; sd < 2; ++sd) {
-    kind[sd] = -1;
+  for (int x = 0; x < NE; ++x) {
+    kind[x] = -1;
     if (!act) continue;
-    const int s = 2 * dir + sd;
+    const int sd = ENDS ? end : x, s = 2 * dir + sd;
     const bool plus = sd;
-    const int nb = nb2[sd];
-    const NbFace f = f2[sd];
+    const int nb = nb2[x];
+    const NbFace f = f2[x];
     const bool bnd = GEN && f.bnd;
     if (GEN == 2 && bnd && f.kind == FACE_MORTAR) {
       // non-conforming face: the outward flux from the mortar face array
       const double *mf = g.mflux + (size_t)g.mslot[(size_t)e * 6 + s] * 5 * n2 + ab;
-      kind[sd] = -2;
+      kind[x] = -2;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Ux[sd][v] = mf[v * n2];
+      for (int v = 0; v < 5; ++v) Ux[x][v] = mf[v * n2];
       continue;
     }
     if (FVM && g.fvflag[nb]) {
       // face shared with a finite-volume element: the outward flux at the face nodes
       const double *fx = g.fvFx + ((size_t)e * 6 + s) * 5 * n2 + ab;
-      kind[sd] = -2;
+      kind[x] = -2;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Ux[sd][v] = fx[v * n2];
+      for (int v = 0; v < 5; ++v) Ux[x][v] = fx[v * n2];
       continue;
     }
-    if (bnd) kind[sd] = f.kind;
+    if (bnd) kind[x] = f.kind;
     if (!bnd) {
       const double *Un = U + (size_t)nb * 5 * n3;
       const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dir, a, b, plus ? 0 : N);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Ux[sd][v] = Un[v * n3 + qn];
+      for (int v = 0; v < 5; ++v) Ux[x][v] = Un[v * n3 + qn];
     }
     if (NS) {
       // both sides' contravariant viscous flux of the face's direction from the lifting (a boundary side:
@@ -1755,7 +1776,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       const double *fo = g.Gf + ((size_t)e * 6 + s) * 4 * n2 + ab;
       const double *fnb = bnd ? fo : g.Gf + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) { Vo[sd][c] = fo[c * n2]; Vn[sd][c] = fnb[c * n2]; }
+      for (int c = 0; c < 4; ++c) { Vo[x][c] = fo[c * n2]; Vn[x][c] = fnb[c * n2]; }
     }
   }
 #pragma unroll
@@ -1775,25 +1796,25 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
   }
   __syncthreads();
   double acc[n][5];
-  if (act) {
-    const LineSlots<n> slot(dir, a, b);
-    // the line direction's metric terms at a node
-    const double *sJd = sJ + 3 * dir * n3;
-    double jl[3] = {0.0, 0.0, 0.0};
+  constexpr int NF = ENDS && WU ? 1 : 2;
+  double fe[NF][5];
+  // the line direction's metric terms at a node
+  const double *sJd = sJ + 3 * dir * n3;
+  double jl[3] = {0.0, 0.0, 0.0};
+  auto metric = [&](int d, int q) -> double {
+    if constexpr (AFF) return jl[d];
+    else return sJd[d * n3 + q];
+  };
+  auto faces = [&](const LineSlots<n> &slot) {
     if constexpr (AFF) {
 #pragma unroll
       for (int d = 0; d < 3; ++d) jl[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
     }
-    auto metric = [&](int d, int q) -> double {
-      if constexpr (AFF) return jl[d];
-      else return sJd[d * n3 + q];
-    };
     // numerical surface fluxes at the line's ends, lifted (outward times lhat), and the interior
     // convective part: 2 D_ii F(U_i) (D_ii is non-zero only at the ends of LGL lines) -+ lhat F_int
-    double fe[2][5];
 #pragma unroll
-    for (int sd = 0; sd < 2; ++sd) {
-      const bool plus = sd;
+    for (int x = 0; x < NE; ++x) {
+      const bool plus = ENDS ? end : x;
       const int qo = slot(plus ? N : 0);
       const double sg = plus ? 1.0 : -1.0, lh = plus ? lhN : lh0;
       double Uw[5], Fo[5];
@@ -1805,36 +1826,39 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       const Pr5 Pw = {Uw[0], sS[n3 + qo], sS[2 * n3 + qo], sS[3 * n3 + qo],
                       gm1 * (Uw[4] - 0.5 * (Uw[1] * sS[n3 + qo] + Uw[2] * sS[2 * n3 + qo] + Uw[3] * sS[3 * n3 + qo]))};
       flux_c(Uw, Pw, nt, Fo);
-      const double cd = 2.0 * D[plus ? N * n + N : 0] - sg * lh;
+      const double cd = 2.0 * (plus ? D[N * n + N] : D[0]) - sg * lh;
       double F[5];
-      if ((GEN == 2 || FVM) && kind[sd] == -2) {
+      if ((GEN == 2 || FVM) && kind[x] == -2) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) F[v] = sg * Ux[sd][v];
+        for (int v = 0; v < 5; ++v) F[v] = sg * Ux[x][v];
       } else {
         const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
         const double ish = 1.0 / sh;
         const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
-        const bool bnd = GEN && kind[sd] >= 0;
-        const bool outflow = bnd && kind[sd] == DG_BC_OUTFLOW;
-        const bool given = bnd && (kind[sd] == DG_BC_STATE || outflow);
-        const bool iso = bnd && kind[sd] == DG_BC_WALL_ISOTHERMAL;
-        const bool wall = bnd && (kind[sd] == DG_BC_WALL || iso);
+        const bool bnd = GEN && kind[x] >= 0;
+        const bool outflow = bnd && kind[x] == DG_BC_OUTFLOW;
+        const bool given = bnd && (kind[x] == DG_BC_STATE || outflow);
+        const bool iso = bnd && kind[x] == DG_BC_WALL_ISOTHERMAL;
+        const bool wall = bnd && (kind[x] == DG_BC_WALL || iso);
         if (bnd) {
 #pragma unroll
-          for (int v = 0; v < 5; ++v) Ux[sd][v] = Uw[v];
+          for (int v = 0; v < 5; ++v) Ux[x][v] = Uw[v];
           if (outflow) {
             // pressure outflow: the own trace's density and velocity with p_out
-            Ux[sd][4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
+            Ux[x][4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
           } else if (given) {
 #pragma unroll
-            for (int v = 0; v < 5; ++v) Ux[sd][v] = ph.ub[v];  // given outer state
+            for (int v = 0; v < 5; ++v) Ux[x][v] = ph.ub[v];  // given outer state
           } else if (wall) {
-            Ux[sd][1] = -Uw[1]; Ux[sd][2] = -Uw[2]; Ux[sd][3] = -Uw[3];  // no-slip wall: velocity reversed
+            Ux[x][1] = -Uw[1]; Ux[x][2] = -Uw[2]; Ux[x][3] = -Uw[3];  // no-slip wall: velocity reversed
           } else {
-            mirror3(Ux[sd] + 1, nh);  // symmetry plane: mirror image of the inner state
+            mirror3(Ux[x] + 1, nh);  // symmetry plane: mirror image of the inner state
           }
         }
-        riemann_vf<VF>(ph, plus ? Uw : Ux[sd], plus ? Ux[sd] : Uw, nh, F);
+        double UM[5], US[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) { UM[v] = plus ? Uw[v] : Ux[x][v]; US[v] = plus ? Ux[x][v] : Uw[v]; }
+        riemann_vf<VF>(ph, UM, US, nh, F);
 #pragma unroll
         for (int v = 0; v < 5; ++v) F[v] *= sh;
         if (NS) {
@@ -1842,9 +1866,9 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
           // conforming face is continuous: the neighbour's Ja of its face direction is +-Ja^dir, + where
           // one side is a +xi side and the other a -xi side)
           double V[4];
-          const double sn = (GEN && f2[sd].plus == plus) ? -1.0 : 1.0;
+          const double sn = (GEN && f2[x].plus == plus) ? -1.0 : 1.0;
 #pragma unroll
-          for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[sd][c] : 0.5 * (Vo[sd][c] + sn * Vn[sd][c]);
+          for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[x][c] : 0.5 * (Vo[x][c] + sn * Vn[x][c]);
           if (!bnd || given) {
             // given outer state: the outer viscous flux equals the inner one
 #pragma unroll
@@ -1867,12 +1891,17 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
         }
       }
 #pragma unroll
-      for (int v = 0; v < 5; ++v) fe[sd][v] = fma(cd, Fo[v], (sg * lh) * F[v]);
+      for (int v = 0; v < 5; ++v) fe[x][v] = fma(cd, Fo[v], (sg * lh) * F[v]);
     }
+  };
+  // the sums of the nodes M0 <= m < M1 (all, or the near or the far half of the line): each node meets its partners
+  // in the same order whoever sums it, so the bits do not depend on the split
+  auto pairs = [&](const LineSlots<n> &slot, auto m0, auto m1) {
+    constexpr int M0 = decltype(m0)::value, M1 = decltype(m1)::value;
 #pragma unroll
     for (int m = 0; m < n; ++m)
 #pragma unroll
-      for (int v = 0; v < 5; ++v) acc[m][v] = m == 0 ? fe[0][v] : (m == N ? fe[1][v] : 0.0);
+      for (int v = 0; v < 5; ++v) acc[m][v] = m == 0 ? fe[0][v] : (m == N ? fe[M0 > 0 ? 0 : NF - 1][v] : 0.0);
     // EC: where every pair of every line of this wave lies in the series' range (the largest ratio of a
     // line is that of its largest and smallest value) the unrolled loop below needs no logarithm
     bool series = true;
@@ -1907,14 +1936,19 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
           if (j == i + 1) An = B;
           if (j + 1 < n) Bn = node(j + 1);
           else if (i + 2 < n) Bn = node(i + 2);
+          const bool si = i >= M0 && i < M1, sj = j >= M0 && j < M1;  // whose sums are taken here
+          if (!si && !sj) {
+            B = Bn;
+            continue;
+          }
           const double nS[3] = {A.nv[0] + B.nv[0], A.nv[1] + B.nv[1], A.nv[2] + B.nv[2]};
           double F[5];
           pair2<VF, true>(A.s, B.s, nS, kg, F);
           const double Dij = D[i * n + j], Dji = D[j * n + i];
 #pragma unroll
           for (int v = 0; v < 5; ++v) {
-            acc[i][v] = fma(Dij, F[v], acc[i][v]);
-            acc[j][v] = fma(Dji, F[v], acc[j][v]);
+            if (si) acc[i][v] = fma(Dij, F[v], acc[i][v]);
+            if (sj) acc[j][v] = fma(Dji, F[v], acc[j][v]);
           }
           B = Bn;
           // at most two pairs in flight: more spill (n <= 6 fits as scheduled)
@@ -1956,6 +1990,38 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
         }
       }
     }
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, n / 2> IH;
+  typedef std::integral_constant<int, n> IN;
+  if constexpr (!ENDS) {
+    if (act) {
+      const LineSlots<n> slot(dir, a, b);
+      faces(slot);
+      pairs(slot, I0(), IN());
+    }
+  } else if constexpr (WU) {
+    if (act) {
+      const LineSlots<n> slot(dir, a, b);
+      faces(slot);
+      if (end) pairs(slot, IH(), IN());
+      else pairs(slot, I0(), IH());
+    }
+  } else {
+    // the far end's flux to the line's own lane
+    double *sF = sm + SplitLds<N>::template nodes<AFF, ENDS>();
+    const LineSlots<n> slot(act ? dir : 0, act ? a : 0, act ? b : 0);
+    if (act) faces(slot);
+    if (act && end) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sF[v * NL + line] = fe[0][v];
+    }
+    __syncthreads();
+    if (act && !end) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) fe[1][v] = sF[v * NL + line];
+      pairs(slot, I0(), IN());
+    }
   }
   // the epilogue's loads are issued before the directions' sums meet
   double Rq[IT][5], gd[IT][4], sjq[IT];
@@ -1976,16 +2042,19 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       }
     }
   }
-  // the three directions' sums, in order
+  // the three directions' sums, in order (SEP: put down at once, added below in that order)
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
+  for (int d = 0; d < (SEP ? 1 : 3); ++d) {
     __syncthreads();
-    if (act && dir == d) {
+    if (act && !(ENDS && !WU && end) && (SEP || dir == d)) {
+      const LineSlots<n> slot(dir, a, b);
+      double *sD = sAcc + (SEP ? dir * 5 * n3 : 0);
 #pragma unroll
       for (int m = 0; m < n; ++m) {
-        const int q = d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m));
+        if (ENDS && WU && (m >= n / 2) != (end != 0)) continue;
+        const int q = SEP ? slot(m) : (d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m)));
 #pragma unroll
-        for (int v = 0; v < 5; ++v) sAcc[v * n3 + q] = d == 0 ? acc[m][v] : sAcc[v * n3 + q] + acc[m][v];
+        for (int v = 0; v < 5; ++v) sD[v * n3 + q] = SEP || d == 0 ? acc[m][v] : sD[v * n3 + q] + acc[m][v];
       }
     }
   }
@@ -1997,7 +2066,10 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
     const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
     double r[5];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) r[v] = sAcc[v * n3 + q];
+    for (int v = 0; v < 5; ++v) {
+      r[v] = sAcc[v * n3 + q];
+      if (SEP) r[v] = (r[v] + sAcc[(5 + v) * n3 + q]) + sAcc[(10 + v) * n3 + q];
+    }
     if (NS) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) r[1 + c] -= gd[it][c];
@@ -2019,15 +2091,15 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
   }
 }
 
-template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
-__global__ void __launch_bounds__(SplitSz<N>::NT, split_minb(N, VF, AFF)) k_split(Geo g, Phys ph, const double *__restrict__ U,
+template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF, bool ENDS>
+__global__ void __launch_bounds__((line_lanes<N, ENDS>()), (split_minb(N, VF, AFF))) k_split(Geo g, Phys ph, const double *__restrict__ U,
                                                      double *__restrict__ out, double *__restrict__ R, double ca,
                                                      double cb, double dt, int mode) {
-  __shared__ double sm[AFF ? SplitLds<N>::AFFINE : SplitLds<N>::A];
+  __shared__ double sm[SplitLds<N>::template size<VF, AFF, ENDS>()];
   const int e = xcd_element(blockIdx.x, g.K);
   if (e >= g.K) return;
   if (FVM && g.fvflag[e]) return;  // a finite-volume element
-  split_body<N, NS, VF, GEN, FVM, AFF>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
+  split_body<N, NS, VF, GEN, FVM, AFF, ENDS>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
 }
 
 // ----------------------------------------------------------------------------- weak/strong form, by lines
@@ -2048,17 +2120,23 @@ template <int N> constexpr int line_minb() { return N >= 8 ? 2 : 3; }
 // each of two rounds of face points, and the register at the end).  Here every load of an element is issued
 // before the first barrier.  A step of 48^3 elements (Euler, LG, N = 3) 2408 -> 2026 us; of 16^3 (Navier-Stokes,
 // weak form, LG, N = 7: half the LDS accesses) 1433 -> 1247 us; strong form, LGL, N = 4, curved 467 -> 456 us.
-// AFF, FVM, mode as for the split operator.  TP: two-point surface flux (riemann 2, 3): its logarithmic means
+// AFF, FVM, mode as for the split operator.  ENDS too, each lane taking one half of the line's nodes' fluxes (Euler
+// on LG nodes, 64 elements, curved: N = 5 54.8 -> 44.7 us a step, N = 7 76.2 -> 67.8).  TP: two-point surface flux (riemann 2, 3): its logarithmic means
 // cost 60 registers more, so LLF and Roe take the instance without them.
-template <int N, bool LGL, bool NS, int FORM, int GEN, bool FVM, bool AFF, bool TP>
-__global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
+template <int N, bool LGL, bool NS, int FORM, int GEN, bool FVM, bool AFF, bool TP, bool ENDS>
+__global__ void __launch_bounds__((line_lanes<N, ENDS>()), (line_minb<N>()))
     k_line(Geo g, Phys ph, const double *__restrict__ U, double *__restrict__ out, double *__restrict__ R, double ca,
            double cb, double dt, int mode) {
   using S = Sz<N>;
-  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = SplitSz<N>::NT, IT = (n3 + NT - 1) / NT;
+  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = line_lanes<N, ENDS>(), IT = (n3 + NT - 1) / NT;
+  constexpr int NL = 3 * n2, NE = ENDS ? 1 : 2;
+  constexpr bool WU = EndsSz<N>::HALF % 64 == 0;  // an end's lanes fill whole waves
+  constexpr bool SEP = line_apart<N, ENDS>();  // the directions' sums in LDS of their own
+  static_assert(SEP == (ENDS && WU));
   constexpr bool PFM = NS && !(FORM == 2 && LGL);  // face viscous fluxes along each side's own normal
-  // state, metric terms (none on affine elements); the result takes the metric terms' place
-  __shared__ double sm[(AFF ? 10 : 14) * n3];
+  // state, metric terms (none on affine elements); the result takes the metric terms' place; ENDS with both
+  // halves in one wave: the far ends' fluxes
+  __shared__ double sm[SEP ? 20 * n3 : (AFF ? 10 : 14) * n3 + (ENDS ? 5 * NL : 0)];
   double *sU = sm, *sJ = sm + 5 * n3, *sAcc = sJ;
   const int e = xcd_element(blockIdx.x, g.K), lane = threadIdx.x;
   if (e >= g.K) return;
@@ -2071,17 +2149,19 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
   typedef const __attribute__((address_space(4))) double *Scal;
   const Scal M = (Scal)(FORM == 0 ? tab->Dh : (LGL ? tab->D : tab->Ds));
   const Scal lm = (Scal)tab->lm, lp = (Scal)tab->lp, lhm = (Scal)tab->lhm, lhp = (Scal)tab->lhp;
-  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(lane / n2) : lane / n2;
-  const int ab = lane - dir * n2, a = ab % n, b = ab / n;
-  const bool act = lane < 3 * n2;
+  const int end = line_end<N, ENDS>(lane), line = lane - end * EndsSz<N>::HALF;
+  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(line / n2) : line / n2;
+  const int ab = line - dir * n2, a = ab % n, b = ab / n;
+  const bool act = line < NL && end < 2;
   // the neighbours' indices first (loads return in order), then everything else the element reads
-  int nb2[2] = {0, 0};
-  NbFace f2[2];
+  int nb2[NE] = {};
+  NbFace f2[NE];
 #pragma unroll
-  for (int sd = 0; sd < 2; ++sd)
+  for (int x = 0; x < NE; ++x)
     if (act) {
-      nb2[sd] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
-      f2[sd] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
+      const int sd = ENDS ? end : x;
+      nb2[x] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
+      f2[x] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
     }
   double Uq[IT][5], Rq[IT][5];
 #pragma unroll
@@ -2105,49 +2185,49 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
     }
   }
   constexpr bool LINES = !LGL && !NS;     // the neighbours' traces are interpolated here from their lines
-  constexpr int CH = n <= 4 ? n : 2;      // nodes of both neighbours' lines in flight
-  double Ux[2][5], Vo[2][4], Vn[2][4], nt2[2][3];
-  int kind[2];  // -1 inner face, else the boundary kind; -2 a face whose outward flux is given (Ux)
+  constexpr int CH = n <= 4 || ENDS ? n : 2;  // nodes of the neighbours' lines in flight
+  double Ux[NE][5], Vo[NE][4], Vn[NE][4], nt2[NE][3];
+  int kind[NE];  // -1 inner face, else the boundary kind; -2 a face whose outward flux is given (Ux)
 #pragma unroll
-  for (int sd = 0; sd < 2; ++sd) {
-    kind[sd] = -1;
+  for (int x = 0; x < NE; ++x) {
+    kind[x] = -1;
     if (!act) continue;
-    const int s = 2 * dir + sd;
-    const int nb = nb2[sd];
-    const NbFace f = f2[sd];
+    const int sd = ENDS ? end : x, s = 2 * dir + sd;
+    const int nb = nb2[x];
+    const NbFace f = f2[x];
     const bool bnd = GEN && f.bnd;
     const double *fnp = AFF ? g.Jc + (size_t)e * AFFINE_DOUBLES + 10 + 3 * s : g.fn + ((size_t)e * 6 + s) * 3 * n2 + ab;
     const int fst = AFF ? 1 : n2;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) nt2[sd][d] = fnp[d * fst];
+    for (int d = 0; d < 3; ++d) nt2[x][d] = fnp[d * fst];
     const double *gx = nullptr;
     if (GEN == 2 && bnd && f.kind == FACE_MORTAR) gx = g.mflux + (size_t)g.mslot[(size_t)e * 6 + s] * 5 * n2 + ab;
     if (FVM && !bnd && g.fvflag[nb]) gx = g.fvFx + ((size_t)e * 6 + s) * 5 * n2 + ab;
     if ((GEN == 2 || FVM) && gx) {
       // the outward flux from the mortar face array, or of a face shared with a finite-volume element
-      kind[sd] = -2;
+      kind[x] = -2;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Ux[sd][v] = gx[v * n2];
+      for (int v = 0; v < 5; ++v) Ux[x][v] = gx[v * n2];
       continue;
     }
-    if (bnd) kind[sd] = f.kind;
+    if (bnd) kind[x] = f.kind;
     if (!bnd && !LINES) {
       if (LGL) {
         const double *Un = U + (size_t)nb * 5 * n3;
         const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dir, a, b, sd ? 0 : N);
 #pragma unroll
-        for (int v = 0; v < 5; ++v) Ux[sd][v] = Un[v * n3 + qn];
+        for (int v = 0; v < 5; ++v) Ux[x][v] = Un[v * n3 + qn];
       } else {
         const double *ut = g.Utr + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 5 * n2 + f.a + n * f.b;
 #pragma unroll
-        for (int v = 0; v < 5; ++v) Ux[sd][v] = ut[v * n2];
+        for (int v = 0; v < 5; ++v) Ux[x][v] = ut[v * n2];
       }
     }
     if (NS) {
       const double *fo = g.Gf + ((size_t)e * 6 + s) * 4 * n2 + ab;
       const double *fnb = bnd ? fo : g.Gf + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) { Vo[sd][c] = fo[c * n2]; Vn[sd][c] = fnb[c * n2]; }
+      for (int c = 0; c < 4; ++c) { Vo[x][c] = fo[c * n2]; Vn[x][c] = fnb[c * n2]; }
     }
   }
   // the epilogue's loads: the register here where they are few, the rest below
@@ -2175,36 +2255,36 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
   if constexpr (LINES) {
     if (act) {
 #pragma unroll
-      for (int sd = 0; sd < 2; ++sd)
+      for (int x = 0; x < NE; ++x)
 #pragma unroll
         for (int v = 0; v < 5; ++v)
-          if (kind[sd] != -2) Ux[sd][v] = 0.0;
-#pragma unroll(n <= 4 ? n : 1)
+          if (kind[x] != -2) Ux[x][v] = 0.0;
+#pragma unroll(CH == n ? n : 1)
       for (int c = 0; c < n; c += CH) {
-        double x[2][CH][5];
+        double y[NE][CH][5];
 #pragma unroll
-        for (int sd = 0; sd < 2; ++sd) {
-          if (kind[sd] != -1) continue;
-          const NbFace f = f2[sd];
-          const double *Un = U + (size_t)nb2[sd] * 5 * n3;
+        for (int x = 0; x < NE; ++x) {
+          if (kind[x] != -1) continue;
+          const NbFace f = f2[x];
+          const double *Un = U + (size_t)nb2[x] * 5 * n3;
 #pragma unroll
           for (int m = 0; m < CH; ++m)
             if (c + m < n) {
               const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, c + m) : line_node<n>(dir, a, b, c + m);
 #pragma unroll
-              for (int v = 0; v < 5; ++v) x[sd][m][v] = Un[v * n3 + qn];
+              for (int v = 0; v < 5; ++v) y[x][m][v] = Un[v * n3 + qn];
             }
         }
 #pragma unroll
-        for (int sd = 0; sd < 2; ++sd) {
-          if (kind[sd] != -1) continue;
-          const bool np = GEN ? f2[sd].plus : !sd;
+        for (int x = 0; x < NE; ++x) {
+          if (kind[x] != -1) continue;
+          const bool np = GEN ? f2[x].plus : !(ENDS ? end : x);
 #pragma unroll
           for (int m = 0; m < CH; ++m)
             if (c + m < n) {
               const double l = np ? lp[c + m] : lm[c + m];
 #pragma unroll
-              for (int v = 0; v < 5; ++v) Ux[sd][v] = fma(l, x[sd][m][v], Ux[sd][v]);
+              for (int v = 0; v < 5; ++v) Ux[x][v] = fma(l, y[x][m][v], Ux[x][v]);
             }
         }
       }
@@ -2223,16 +2303,15 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
   }
   __syncthreads();
   double acc[n][5];
-  if (act) {
-    const LineSlots<n> slot(dir, a, b);
-    // numerical fluxes at the line's ends, outward
-    double F2[2][5];
+  constexpr int NF = ENDS && WU ? 1 : 2;
+  double F2[NF][5];  // numerical fluxes at the line's ends, outward
+  auto faces = [&](const LineSlots<n> &slot) {
 #pragma unroll
-    for (int sd = 0; sd < 2; ++sd) {
-      const bool plus = sd;
-      if ((GEN == 2 || FVM) && kind[sd] == -2) {
+    for (int x = 0; x < NE; ++x) {
+      const bool plus = ENDS ? end : x;
+      if ((GEN == 2 || FVM) && kind[x] == -2) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) F2[sd][v] = Ux[sd][v];
+        for (int v = 0; v < 5; ++v) F2[x][v] = Ux[x][v];
         continue;
       }
       double Uw[5];
@@ -2253,52 +2332,54 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
       }
       // the master's normal and state go first (the stored normal is outward, the master's negated on
       // the slave side)
-      const bool mst = GEN ? f2[sd].master : plus;
+      const bool mst = GEN ? f2[x].master : plus;
       const double sg = mst ? 1.0 : -1.0;
-      const double nt[3] = {sg * nt2[sd][0], sg * nt2[sd][1], sg * nt2[sd][2]};
+      const double nt[3] = {sg * nt2[x][0], sg * nt2[x][1], sg * nt2[x][2]};
       const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
       const double ish = 1.0 / sh;
       const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
-      const bool bnd = GEN && kind[sd] >= 0;
-      const bool outflow = bnd && kind[sd] == DG_BC_OUTFLOW;
-      const bool given = bnd && (kind[sd] == DG_BC_STATE || outflow);
-      const bool iso = bnd && kind[sd] == DG_BC_WALL_ISOTHERMAL;
-      const bool wall = bnd && (kind[sd] == DG_BC_WALL || iso);
+      const bool bnd = GEN && kind[x] >= 0;
+      const bool outflow = bnd && kind[x] == DG_BC_OUTFLOW;
+      const bool given = bnd && (kind[x] == DG_BC_STATE || outflow);
+      const bool iso = bnd && kind[x] == DG_BC_WALL_ISOTHERMAL;
+      const bool wall = bnd && (kind[x] == DG_BC_WALL || iso);
       if (bnd) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) Ux[sd][v] = Uw[v];
+        for (int v = 0; v < 5; ++v) Ux[x][v] = Uw[v];
         if (outflow) {
           // pressure outflow: the own trace's density and velocity with p_out
-          Ux[sd][4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
+          Ux[x][4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
         } else if (given) {
 #pragma unroll
-          for (int v = 0; v < 5; ++v) Ux[sd][v] = ph.ub[v];  // given outer state
+          for (int v = 0; v < 5; ++v) Ux[x][v] = ph.ub[v];  // given outer state
         } else if (wall) {
-          Ux[sd][1] = -Uw[1]; Ux[sd][2] = -Uw[2]; Ux[sd][3] = -Uw[3];  // no-slip wall: velocity reversed
+          Ux[x][1] = -Uw[1]; Ux[x][2] = -Uw[2]; Ux[x][3] = -Uw[3];  // no-slip wall: velocity reversed
         } else {
-          mirror3(Ux[sd] + 1, nh);  // symmetry plane: mirror image of the inner state
+          mirror3(Ux[x] + 1, nh);  // symmetry plane: mirror image of the inner state
         }
       }
-      const double *UM = mst ? Uw : Ux[sd], *US = mst ? Ux[sd] : Uw;
+      double UM[5], US[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) { UM[v] = mst ? Uw[v] : Ux[x][v]; US[v] = mst ? Ux[x][v] : Uw[v]; }
       double F[5];
       if constexpr (TP) riemann(ph, UM, US, nh, F);
       else if (ph.rs == DG_RS_LLF) riemann_t<DG_RS_LLF>(ph, UM, US, nh, F);
       else riemann_t<DG_RS_ROE>(ph, UM, US, nh, F);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) F2[sd][v] = (sg * sh) * F[v];
+      for (int v = 0; v < 5; ++v) F2[x][v] = (sg * sh) * F[v];
       if (PFM) {
         // minus the outward BR1 mean of the viscous flux: each side's flux carries its own outward normal
         // (the two normals of a face are negatives of each other), a boundary side's is the mean itself
 #pragma unroll
-        for (int c = 0; c < 4; ++c) F2[sd][1 + c] -= bnd ? Vo[sd][c] : 0.5 * (Vo[sd][c] - Vn[sd][c]);
+        for (int c = 0; c < 4; ++c) F2[x][1 + c] -= bnd ? Vo[x][c] : 0.5 * (Vo[x][c] - Vn[x][c]);
       } else if (NS) {
         // minus the BR1 mean of the viscous flux along this side's +xi direction (the split form's reading
         // of the traces and boundary kinds), applied outward
         const double sp = plus ? 1.0 : -1.0;
-        const double sn = (GEN && f2[sd].plus == plus) ? -1.0 : 1.0;
+        const double sn = (GEN && f2[x].plus == plus) ? -1.0 : 1.0;
         double V[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[sd][c] : 0.5 * (Vo[sd][c] + sn * Vn[sd][c]);
+        for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[x][c] : 0.5 * (Vo[x][c] + sn * Vn[x][c]);
         if (wall) {
           // the momentum part of the inner flux; at an isothermal wall the inner heat flux (the energy flux
           // minus the work of the stress)
@@ -2310,17 +2391,23 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
           V[3] = 0.0;
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) F2[sd][1 + c] -= sp * V[c];
+        for (int c = 0; c < 4; ++c) F2[x][1 + c] -= sp * V[c];
       }
-      __builtin_amdgcn_sched_barrier(0);  // one end at a time: both in flight spill
+      if (!ENDS) __builtin_amdgcn_sched_barrier(0);  // one end at a time: both in flight spill
     }
+  };
+  // the sums over the nodes M0 <= m < M1 and over the line's ends that lie among them
+  auto contract = [&](const LineSlots<n> &slot, auto m0, auto m1) {
+    constexpr int M0 = decltype(m0)::value, M1 = decltype(m1)::value;
     // surface integral (on LGL nodes lhat is non-zero at the ends only)
 #pragma unroll
     for (int m = 0; m < n; ++m)
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        if (LGL) acc[m][v] = m == 0 ? lhm[0] * F2[0][v] : (m == N ? lhp[N] * F2[1][v] : 0.0);
-        else acc[m][v] = fma(lhm[m], F2[0][v], lhp[m] * F2[1][v]);
+        if (LGL) acc[m][v] = m == 0 && M0 == 0 ? lhm[0] * F2[0][v] : (m == N && M1 == n ? lhp[N] * F2[M0 > 0 ? 0 : NF - 1][v] : 0.0);
+        else if (M0 > 0) acc[m][v] = lhp[m] * F2[0][v];
+        else if (M1 < n) acc[m][v] = lhm[m] * F2[0][v];
+        else acc[m][v] = fma(lhm[m], F2[0][v], lhp[m] * F2[NF - 1][v]);
       }
     double jl[3] = {0.0, 0.0, 0.0};
     if constexpr (AFF) {
@@ -2330,7 +2417,7 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
     const double *sJd = sJ + 3 * dir * n3;
     // volume integral: node by node, its flux times the matrix's column into the line's sums
 #pragma unroll
-    for (int m = 0; m < n; ++m) {
+    for (int m = M0; m < M1; ++m) {
       const int q = slot(m);
       double Uo[5], Fc[5], nv[3];
 #pragma unroll
@@ -2350,18 +2437,52 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);  // one node's flux at a time: more in flight spill
     }
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, (n + 1) / 2> IH;
+  typedef std::integral_constant<int, n> IN;
+  if constexpr (!ENDS) {
+    if (act) {
+      const LineSlots<n> slot(dir, a, b);
+      faces(slot);
+      contract(slot, I0(), IN());
+    }
+  } else if constexpr (WU) {
+    if (act) {
+      const LineSlots<n> slot(dir, a, b);
+      faces(slot);
+      if (end) contract(slot, IH(), IN());
+      else contract(slot, I0(), IH());
+    }
+  } else {
+    // both halves in one wave: the far end's flux to the line's own lane
+    double *sF = sm + (AFF ? 10 : 14) * n3;
+    const LineSlots<n> slot(act ? dir : 0, act ? a : 0, act ? b : 0);
+    if (act) faces(slot);
+    if (act && end) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sF[v * NL + line] = F2[0][v];
+    }
+    __syncthreads();
+    if (act && !end) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) F2[1][v] = sF[v * NL + line];
+      contract(slot, I0(), IN());
+    }
   }
   if constexpr (!PRE) load_epilogue();
-  // the three directions' sums, in order
+  // the three directions' sums, in order (SEP: apart, first the near ends' halves, then the far ends' on top)
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
+  for (int d = 0; d < (SEP ? 2 : 3); ++d) {
     __syncthreads();
-    if (act && dir == d) {
+    if (act && (SEP ? end == d : !(ENDS && end) && dir == d)) {
+      const LineSlots<n> slot(dir, a, b);
+      double *sD = sAcc + (SEP ? dir * 5 * n3 : 0);
 #pragma unroll
       for (int m = 0; m < n; ++m) {
-        const int q = d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m));
+        const int q = SEP ? slot(m) : (d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m)));
 #pragma unroll
-        for (int v = 0; v < 5; ++v) sAcc[v * n3 + q] = d == 0 ? acc[m][v] : sAcc[v * n3 + q] + acc[m][v];
+        for (int v = 0; v < 5; ++v) sD[v * n3 + q] = d == 0 ? acc[m][v] : sD[v * n3 + q] + acc[m][v];
       }
     }
   }
@@ -2376,6 +2497,7 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       double r = sAcc[v * n3 + q];
+      if (SEP) r = (r + sAcc[(5 + v) * n3 + q]) + sAcc[(10 + v) * n3 + q];
       if (NS && v > 0) r -= gd[it][v - 1];  // the viscous volume term, formed by the lifting kernel
       const double ut = -r * sjq[it];
       if (mode == 0) {
@@ -2392,7 +2514,7 @@ __global__ void __launch_bounds__(SplitSz<N>::NT, (line_minb<N>()))
 
 // ----------------------------------------------------------------------------- ensemble batch
 // Workgroups of the batched kernels walk the concatenated element list of all members of one
-// degree; EPB elements share a workgroup (one slot of Sz<N>::NT threads each, SplitSz<N>::NT in
+// degree; EPB elements share a workgroup (one slot of Sz<N>::NT threads each, line_lanes in
 // the split-form kernel, wave aligned).
 // Each slot finds its member by bisection of the element prefix sums.
 // AFF: no, every or some member's elements are affine.  AFF_MIXED takes each member's own path, so that a member's
@@ -2440,8 +2562,9 @@ __global__ void __launch_bounds__((lift_b_lanes<N, AFF>()) * EPB, (lift_b_minb<N
 }
 
 template <int N, bool NS, int VF, int EPB, bool GEN, int AFF>
-__global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N, VF, AFF == AFF_ALL)) k_split_b(BatchView bv) {
-  constexpr int NT = SplitSz<N>::NT, L = AFF == AFF_ALL ? SplitLds<N>::AFFINE : SplitLds<N>::A;
+__global__ void __launch_bounds__((line_lanes<N, ends_always(N)>()) * EPB, (split_minb(N, VF, AFF == AFF_ALL))) k_split_b(BatchView bv) {
+  constexpr bool ENDS = ends_always(N);
+  constexpr int NT = line_lanes<N, ENDS>(), L = SplitLds<N>::template size<VF, AFF == AFF_ALL, ENDS>();
   __shared__ double sm[EPB * L];
   const BatchBlock B = batch_block(bv, EPB, blockIdx.x);
   if (B.item >= B.end) return;
@@ -2453,9 +2576,9 @@ __global__ void __launch_bounds__(SplitSz<N>::NT * EPB, split_minb(N, VF, AFF ==
   const Member &M = bv.m[mi];
   const int e = valid ? item - bv.first[mi] : 0;
   if (AFF == AFF_ALL || (AFF == AFF_MIXED && B.affine))
-    split_body<N, NS, VF, GEN, false, true>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
+    split_body<N, NS, VF, GEN, false, true, ENDS>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
   else
-    split_body<N, NS, VF, GEN, false, false>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
+    split_body<N, NS, VF, GEN, false, false, ENDS>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
 }
 
 // ----------------------------------------------------------------------------- reductions
@@ -3300,6 +3423,13 @@ __global__ void __launch_bounds__(Sz<N>::NT) k_fv_switch(Geo g, Phys ph, FvGeo f
 
 // The kernels that take an element's metric terms as constants (AFF) run on meshes whose every element is
 // affine (Geo::Jc is set up by dg_init exactly there); any other mesh reads them per node.
+// Whether a mesh takes the kernels with a lane per end of every line: where its workgroups run in one round (one per CU
+// from N = 6 on, two below), so that the chain of one lane's steps is the time.  A step of 343 and 512 elements takes
+// 0.81 to 0.97 of the other kernels' time at N = 4, 5 and 1.03 to 1.22 at N = 6, 7; of 216 elements 0.82 to 0.97 at
+// N = 4 to 8; of 1000 elements 0.93 to 1.13 at N = 4, 5.  Against one node per lane, 64 elements, curved: split EC N = 7
+// 122.0 -> 118.3 us a step, weak form on LG nodes N = 5 120.0 -> 111.4 (without this rule 126.5 and 124.2).
+static bool small_mesh(int N, int K) { return K <= (N >= 6 ? 256 : 512); }
+
 template <int N, bool LGL, bool NS, int FORM>
 static int launch_main_t(const Geo &g, const Phys &ph, const double *U, const double *G, double *out, double *R,
                          double a, double b, double dt, int mode, hipStream_t st) {
@@ -3315,25 +3445,35 @@ static int launch_main_t(const Geo &g, const Phys &ph, const double *U, const do
       return DG_OK;
     }
   }
-  const dim3 block(SplitSz<N>::NT);
   const bool tp = ph.rs >= DG_RS_VOLFLUX;
-#define DG_KMT(G_, F_, A_, T_) \
-  hipLaunchKernelGGL((k_line<N, LGL, NS, FORM, G_, F_, A_, T_>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode)
-#define DG_KM(G_, F_) \
+#define DG_KM(G_, F_, A_, T_, E_) \
+  hipLaunchKernelGGL((k_line<N, LGL, NS, FORM, G_, F_, A_, T_, E_>), grid, dim3(line_lanes<N, E_>()), 0, st, g, ph, U, out, R, a, b, dt, mode)
+#define DG_KMT(G_, F_) \
   do { \
-    if (g.Jc) { if (tp) DG_KMT(G_, F_, true, true); else DG_KMT(G_, F_, true, false); } \
-    else { if (tp) DG_KMT(G_, F_, false, true); else DG_KMT(G_, F_, false, false); } \
+    constexpr bool E = ends_always(N); \
+    if (g.Jc) { if (tp) DG_KM(G_, F_, true, true, E); else DG_KM(G_, F_, true, false, E); } \
+    else { if (tp) DG_KM(G_, F_, false, true, E); else DG_KM(G_, F_, false, false, E); } \
   } while (0)
-  if constexpr (!NS) {
-    if (g.fvflag) DG_KM(1, true);
-    else if (lev == 2) DG_KM(2, false);
-    else if (lev == 1) DG_KM(1, false);
-    else DG_KM(0, false);
+#define DG_KMS(G_, F_) \
+  do { if (g.Jc) DG_KM(G_, F_, true, true, true); else DG_KM(G_, F_, false, true, true); } while (0)
+  if (!ends_always(N) && small_mesh(N, g.K)) {
+    // one instance for every mesh and surface flux
+    if constexpr (!NS) {
+      if (g.fvflag) DG_KMS(1, true); else DG_KMS(2, false);
+    } else {
+      DG_KMS(2, false);
+    }
+  } else if constexpr (!NS) {
+    if (g.fvflag) DG_KMT(1, true);
+    else if (lev == 2) DG_KMT(2, false);
+    else if (lev == 1) DG_KMT(1, false);
+    else DG_KMT(0, false);
   } else {
-    if (lev == 1) DG_KM(1, false); else DG_KM(0, false);
+    if (lev == 1) DG_KMT(1, false); else DG_KMT(0, false);
   }
-#undef DG_KM
+#undef DG_KMS
 #undef DG_KMT
+#undef DG_KM
   DG_CHECK_LAUNCH();
   return DG_OK;
 }
@@ -3341,23 +3481,28 @@ static int launch_main_t(const Geo &g, const Phys &ph, const double *U, const do
 template <int N, bool NS, int VF>
 static int launch_split_t(const Geo &g, const Phys &ph, const double *U, double *out, double *R, double a, double b,
                           double dt, int mode, hipStream_t st) {
-  dim3 grid(xcd_grid(g.K)), block(SplitSz<N>::NT);
-#define DG_KS(G_, F_) \
-  do { \
-    if (g.Jc) hipLaunchKernelGGL((k_split<N, NS, VF, G_, F_, true>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode); \
-    else hipLaunchKernelGGL((k_split<N, NS, VF, G_, F_, false>), grid, block, 0, st, g, ph, U, out, R, a, b, dt, mode); \
-  } while (0)
+  const dim3 grid(xcd_grid(g.K));
+#define DG_KSE(G_, F_, A_, E_) \
+  hipLaunchKernelGGL((k_split<N, NS, VF, G_, F_, A_, E_>), grid, dim3(line_lanes<N, E_>()), 0, st, g, ph, U, out, R, a, b, dt, mode)
+#define DG_KS(G_, F_, E_) \
+  do { if (g.Jc) DG_KSE(G_, F_, true, E_); else DG_KSE(G_, F_, false, E_); } while (0)
+  // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
+  const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
+  constexpr bool E = ends_always(N);
+  const bool small = !E && small_mesh(N, g.K);  // one instance for every mesh
   if constexpr (!NS) {
     if (g.fvflag) {
-      DG_KS(1, true);
+      if (small) DG_KS(1, true, true); else DG_KS(1, true, E);
       DG_CHECK_LAUNCH();
       return DG_OK;
     }
   }
-  // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
-  const int lev = g.fc == nullptr ? 0 : (g.mslot ? 2 : 1);
-  if (lev == 0) DG_KS(0, false); else if (lev == 1) DG_KS(1, false); else DG_KS(2, false);
+  if (small) DG_KS(2, false, true);
+  else if (lev == 0) DG_KS(0, false, E);
+  else if (lev == 1) DG_KS(1, false, E);
+  else DG_KS(2, false, E);
 #undef DG_KS
+#undef DG_KSE
   DG_CHECK_LAUNCH();
   return DG_OK;
 }
@@ -3462,7 +3607,7 @@ template <int N, int EPB> static int launch_batch_lift_a(const BatchView &bv, hi
 
 template <int N, bool NS, int VF, int EPB, int AFF>
 static int launch_batch_split_t(const BatchView &bv, hipStream_t st) {
-  const dim3 grid(batch_grid(bv, EPB)), block(SplitSz<N>::NT * EPB);
+  const dim3 grid(batch_grid(bv, EPB)), block(line_lanes<N, ends_always(N)>() * EPB);
   if (bv.general) hipLaunchKernelGGL((k_split_b<N, NS, VF, EPB, true, AFF>), grid, block, 0, st, bv);
   else hipLaunchKernelGGL((k_split_b<N, NS, VF, EPB, false, AFF>), grid, block, 0, st, bv);
   DG_CHECK_LAUNCH();
@@ -3659,8 +3804,9 @@ int launch_axpby(double *y, const double *x, double alpha, double beta, size_t n
 // last slot run the per-element code as invalid slots (no memory access, every barrier).
 constexpr int FUSED_SPLIT_LDS = 2 * SplitLds<7>::A;  // 152 KB: one workgroup per CU
 template <int N> constexpr int fused_epb_split() {
-  constexpr int by_lanes = 512 / SplitSz<N>::NT;
-  constexpr int by_lds = FUSED_SPLIT_LDS / SplitLds<N>::A;
+  constexpr bool ENDS = ends_always(N);
+  constexpr int by_lanes = 512 / line_lanes<N, ENDS>();
+  constexpr int by_lds = FUSED_SPLIT_LDS / SplitLds<N>::template size<0, false, ENDS>();
   return by_lanes < by_lds ? by_lanes : by_lds;
 }
 template <int N> constexpr int fused_epb_lift() {
@@ -3685,7 +3831,8 @@ __device__ __forceinline__ BatchBlock fused_block(const BatchView &bv, int epb, 
 
 template <int N, bool NS, int VF>
 __device__ __forceinline__ void fused_split_group(const BatchView &bv, int blk, double *smem) {
-  constexpr int NT = SplitSz<N>::NT, EPB = fused_epb_split<N>(), L = SplitLds<N>::A;
+  constexpr bool ENDS = ends_always(N);
+  constexpr int NT = line_lanes<N, ENDS>(), EPB = fused_epb_split<N>(), L = SplitLds<N>::template size<VF, false, ENDS>();
   const BatchBlock B = fused_block(bv, EPB, blk);
   const int raw = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int slot = raw < EPB ? raw : EPB - 1;
@@ -3697,9 +3844,9 @@ __device__ __forceinline__ void fused_split_group(const BatchView &bv, int blk, 
   const int e = valid ? item - bv.first[mi] : 0;
   double *sm = smem + slot * L;
   if (B.affine)
-    split_body<N, NS, VF, 0, false, true>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
+    split_body<N, NS, VF, 0, false, true, ENDS>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
   else
-    split_body<N, NS, VF, 0, false, false>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
+    split_body<N, NS, VF, 0, false, false, ENDS>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
 }
 
 template <bool NS, int VF>

@@ -55,6 +55,24 @@ template <int N> struct SplitSz {
   static constexpr int NT = (NL + 63) / 64 * 64;
 };
 
+// With a lane per end of every line (ENDS): the first HALF lanes take the lines and the fluxes at their near ends,
+// the next HALF the fluxes at the far ends; wave aligned where the two halves do not fit one wave.
+template <int N> struct EndsSz {
+  static constexpr int NL = SplitSz<N>::NL, HALF = 2 * NL <= 64 ? NL : (NL + 63) / 64 * 64;
+  static constexpr int NT = (2 * HALF + 63) / 64 * 64;
+};
+template <int N, bool ENDS> constexpr int line_lanes() { return ENDS ? EndsSz<N>::NT : SplitSz<N>::NT; }
+template <int N, bool ENDS> __device__ __forceinline__ int line_end(int lane) {
+  if constexpr (!ENDS) return 0;
+  else if constexpr (EndsSz<N>::HALF % 64 == 0) return __builtin_amdgcn_readfirstlane(lane / EndsSz<N>::HALF);
+  else return lane / EndsSz<N>::HALF;
+}
+// one wave holds both ends of every line of degrees 1 and 2: a second lane costs nothing there
+constexpr bool ends_always(int N) { return N <= 2; }
+// the kernels of small meshes: one workgroup per CU, so the three directions' sums may lie in LDS side by side, put
+// down after one barrier instead of one after the other
+template <int N, bool ENDS> constexpr bool line_apart() { return ENDS && !ends_always(N); }
+
 // The 1D tables through the scalar cache.
 typedef const __attribute__((address_space(4))) double *Scalar;
 struct Scalars {
