@@ -3540,38 +3540,20 @@ int launch_lift(const Geo &g, const Phys &ph, bool lgl, int out, const double *U
     else hipLaunchKernelGGL((k_lift<N, L_, O_, G_>), grid, block, 0, st, g, ph, U, G, Fv); \
   } while (0)
 #define DG_KL(L_, O_) \
-  do { \
-    if (lev == 0) DG_KLG(L_, O_, 0); \
-    else if (lev == 1) DG_KLG(L_, O_, 1); \
-    else DG_KLG(L_, O_, 2); \
-  } while (0)
-  if (out == LIFT_SV) {
-    // the strong-form operator of conforming meshes on LG nodes
-    if (lev == 2 || lgl) return DG_ERR_UNSUPPORTED;
-    if (lev == 0) DG_KLG(false, LIFT_SV, 0); else DG_KLG(false, LIFT_SV, 1);
-  } else if (out == LIFT_WV) {
-    // the weak-form operator of conforming meshes
-    if (lev == 2) return DG_ERR_UNSUPPORTED;
-    if (lgl) {
-      if (lev == 0) DG_KLG(true, LIFT_WV, 0); else DG_KLG(true, LIFT_WV, 1);
-    } else {
-      if (lev == 0) DG_KLG(false, LIFT_WV, 0); else DG_KLG(false, LIFT_WV, 1);
-    }
-  } else if (!lgl) {
-    if (out == LIFT_G) DG_KL(false, LIFT_G);
-    else if (out == LIFT_GT) DG_KL(false, LIFT_GT);
-    else return DG_ERR_UNSUPPORTED;
-  } else if (out == LIFT_G) {
-    DG_KL(true, LIFT_G);
-  } else if (out == LIFT_FV) {
-    DG_KL(true, LIFT_FV);
-  } else if (out == LIFT_DIV) {
-    DG_KL(true, LIFT_DIV);
-  } else if (out == LIFT_DIVK) {
-    DG_KL(true, LIFT_DIVK);
-  } else {
-    return DG_ERR_UNSUPPORTED;
-  }
+  do { if (lev == 0) DG_KLG(L_, O_, 0); else DG_KLG(L_, O_, 1); } while (0)
+  // only what rhs_dispatch and the reverse ask for: gradients on meshes with non-conforming faces (weak and strong
+  // form), the fluxes for the reverse and the weak and strong forms' viscous terms on conforming ones
+  if (out == LIFT_G && lgl && lev == 2) DG_KLG(true, LIFT_G, 2);
+  else if (out == LIFT_GT && !lgl && lev == 2) DG_KLG(false, LIFT_GT, 2);
+  else if (out == LIFT_SV && !lgl && lev < 2) DG_KL(false, LIFT_SV);
+  else if (out == LIFT_WV && lgl && lev < 2) DG_KL(true, LIFT_WV);
+  else if (out == LIFT_WV && !lgl && lev < 2) DG_KL(false, LIFT_WV);
+  else if (out == LIFT_FV && lgl && lev < 2) DG_KL(true, LIFT_FV);
+  else if (out == LIFT_DIV && lgl && lev < 2) DG_KL(true, LIFT_DIV);
+  else if (out == LIFT_DIV && lgl) DG_KLG(true, LIFT_DIV, 2);
+  else if (out == LIFT_DIVK && lgl && lev < 2) DG_KL(true, LIFT_DIVK);
+  else if (out == LIFT_DIVK && lgl) DG_KLG(true, LIFT_DIVK, 2);
+  else return DG_ERR_UNSUPPORTED;
 #undef DG_KLG
 #undef DG_KL
   DG_CHECK_LAUNCH();
