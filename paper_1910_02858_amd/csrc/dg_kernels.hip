@@ -1676,47 +1676,40 @@ struct LineNode {  // a node of a line: its two-point state and the line directi
 // AFF: every element is affine, its metric terms and 1/J are the element's constants (Geo::Jc): 10 of the
 // 43 doubles per node are not read, and of the 41 KB of LDS at N = 7 instead of 78 four workgroups fit a CU; by
 // registers two do with the EC and central fluxes, four with the KEP flux (split_minb).
-// ENDS: a lane per end of every line (see EndsSz): the fluxes at the two ends are evaluated at once, and with the
-// short pair fluxes each lane sums one half of the line's nodes.  For degrees 1 and 2, where both ends' lanes fit the
-// one wave (1 M nodes, curved, KEP: N = 1 2570 -> 1797 us a step, N = 2 913 -> 756), and for small meshes (small_mesh).
 // mode 0 writes U_t, 1 the fused RK stage.  FVM: the sides that meet a finite-volume element take their
 // flux from Geo::fvFx.
-template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF, bool ENDS>
+template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
 __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const Tab *tab, int e, bool valid, int lane,
                                            const double *__restrict__ U, double *__restrict__ out,
                                            double *__restrict__ R, double ca, double cb, double dt, int mode,
                                            double *sm) {
   using S = Sz<N>;
-  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = line_lanes<N, ENDS>(), NL = 3 * n2, NE = ENDS ? 1 : 2;
-  constexpr bool WU = split_halves<N, VF>();
-  constexpr bool SEP = line_apart<N, ENDS>();  // the directions' sums in LDS of their own
+  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = SplitSz<N>::NT;
   constexpr int IT = (n3 + NT - 1) / NT;  // nodes per lane in the node loops
   const double gm1 = ph.gamma - 1.0, kg = 1.0 / gm1, gg = gm1 / ph.gamma;
   const double *Ue = U + (size_t)e * 5 * n3;
   const double *Jae = g.Ja + (size_t)e * 9 * n3;
   double *sU = sm, *sS = sm + 5 * n3, *sJ = sm + 10 * n3;  // node slots: div_slot
-  double *sAcc = AFF || line_apart<N, ENDS>() ? sS : sJ;
+  double *sAcc = AFF ? sS : sJ;
   AffineConst jc = nullptr;
   if constexpr (AFF) jc = affine_const(g, e);
   // the 1D tables through the scalar cache
   const __attribute__((address_space(4))) double *D = (const __attribute__((address_space(4))) double *)tab->D;
   const double lh0 = tab->lhm[0], lhN = tab->lhp[N];
   // this lane's line: direction, and its position (a, b) among the direction's lines, which is also the
-  // face point of its two ends; ENDS: and the end whose flux it evaluates
-  const int end = line_end<N, ENDS>(lane), line = lane - end * EndsSz<N>::HALF;
-  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(line / n2) : line / n2;
-  const int ab = line - dir * n2, a = ab % n, b = ab / n;
-  const bool act = valid && line < NL && end < 2;
+  // face point of its two ends
+  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(lane / n2) : lane / n2;
+  const int ab = lane - dir * n2, a = ab % n, b = ab / n;
+  const bool act = valid && lane < 3 * n2;
   // the two end faces' neighbours first (loads return in order: behind the others, the neighbours' traces
   // would wait for all of them), then the state and metric terms for LDS and the faces' other sides
-  int nb2[NE] = {};
-  NbFace f2[NE];
+  int nb2[2] = {0, 0};
+  NbFace f2[2];
 #pragma unroll
-  for (int x = 0; x < NE; ++x)
+  for (int sd = 0; sd < 2; ++sd)
     if (act) {
-      const int sd = ENDS ? end : x;
-      nb2[x] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
-      f2[x] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
+      nb2[sd] = g.nbr[(size_t)e * 6 + 2 * dir + sd];
+      f2[sd] = nbr_face<n, (GEN > 0)>(g, e, 2 * dir + sd, a, b);
     }
   double Uq[IT][5];
 #pragma unroll
@@ -1736,39 +1729,39 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       for (int c = 0; c < 9; ++c) Jq[it][c] = Jae[c * n3 + t];
     }
   }
-  double Ux[NE][5], Vo[NE][4], Vn[NE][4];  // the end faces: the other side's state, both sides' viscous fluxes
-  int kind[NE];                // -1 inner face, else the boundary kind; -2 a face whose flux is given (Ux)
+  double Ux[2][5], Vo[2][4], Vn[2][4];  // the end faces: the other side's state, both sides' viscous fluxes
+  int kind[2];                // -1 inner face, else the boundary kind; -2 a face whose flux is given (Ux)
 #pragma unroll
-  for (int x = 0; x < NE; ++x) {
-    kind[x] = -1;
+  for (int sd = 0; sd < 2; ++sd) {
+    kind[sd] = -1;
     if (!act) continue;
-    const int sd = ENDS ? end : x, s = 2 * dir + sd;
+    const int s = 2 * dir + sd;
     const bool plus = sd;
-    const int nb = nb2[x];
-    const NbFace f = f2[x];
+    const int nb = nb2[sd];
+    const NbFace f = f2[sd];
     const bool bnd = GEN && f.bnd;
     if (GEN == 2 && bnd && f.kind == FACE_MORTAR) {
       // non-conforming face: the outward flux from the mortar face array
       const double *mf = g.mflux + (size_t)g.mslot[(size_t)e * 6 + s] * 5 * n2 + ab;
-      kind[x] = -2;
+      kind[sd] = -2;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Ux[x][v] = mf[v * n2];
+      for (int v = 0; v < 5; ++v) Ux[sd][v] = mf[v * n2];
       continue;
     }
     if (FVM && g.fvflag[nb]) {
       // face shared with a finite-volume element: the outward flux at the face nodes
       const double *fx = g.fvFx + ((size_t)e * 6 + s) * 5 * n2 + ab;
-      kind[x] = -2;
+      kind[sd] = -2;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Ux[x][v] = fx[v * n2];
+      for (int v = 0; v < 5; ++v) Ux[sd][v] = fx[v * n2];
       continue;
     }
-    if (bnd) kind[x] = f.kind;
+    if (bnd) kind[sd] = f.kind;
     if (!bnd) {
       const double *Un = U + (size_t)nb * 5 * n3;
       const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dir, a, b, plus ? 0 : N);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Ux[x][v] = Un[v * n3 + qn];
+      for (int v = 0; v < 5; ++v) Ux[sd][v] = Un[v * n3 + qn];
     }
     if (NS) {
       // both sides' contravariant viscous flux of the face's direction from the lifting (a boundary side:
@@ -1776,7 +1769,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       const double *fo = g.Gf + ((size_t)e * 6 + s) * 4 * n2 + ab;
       const double *fnb = bnd ? fo : g.Gf + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) { Vo[x][c] = fo[c * n2]; Vn[x][c] = fnb[c * n2]; }
+      for (int c = 0; c < 4; ++c) { Vo[sd][c] = fo[c * n2]; Vn[sd][c] = fnb[c * n2]; }
     }
   }
 #pragma unroll
@@ -1796,25 +1789,25 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
   }
   __syncthreads();
   double acc[n][5];
-  constexpr int NF = ENDS && WU ? 1 : 2;
-  double fe[NF][5];
-  // the line direction's metric terms at a node
-  const double *sJd = sJ + 3 * dir * n3;
-  double jl[3] = {0.0, 0.0, 0.0};
-  auto metric = [&](int d, int q) -> double {
-    if constexpr (AFF) return jl[d];
-    else return sJd[d * n3 + q];
-  };
-  auto faces = [&](const LineSlots<n> &slot) {
+  if (act) {
+    const LineSlots<n> slot(dir, a, b);
+    // the line direction's metric terms at a node
+    const double *sJd = sJ + 3 * dir * n3;
+    double jl[3] = {0.0, 0.0, 0.0};
     if constexpr (AFF) {
 #pragma unroll
       for (int d = 0; d < 3; ++d) jl[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
     }
+    auto metric = [&](int d, int q) -> double {
+      if constexpr (AFF) return jl[d];
+      else return sJd[d * n3 + q];
+    };
     // numerical surface fluxes at the line's ends, lifted (outward times lhat), and the interior
     // convective part: 2 D_ii F(U_i) (D_ii is non-zero only at the ends of LGL lines) -+ lhat F_int
+    double fe[2][5];
 #pragma unroll
-    for (int x = 0; x < NE; ++x) {
-      const bool plus = ENDS ? end : x;
+    for (int sd = 0; sd < 2; ++sd) {
+      const bool plus = sd;
       const int qo = slot(plus ? N : 0);
       const double sg = plus ? 1.0 : -1.0, lh = plus ? lhN : lh0;
       double Uw[5], Fo[5];
@@ -1826,39 +1819,36 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
       const Pr5 Pw = {Uw[0], sS[n3 + qo], sS[2 * n3 + qo], sS[3 * n3 + qo],
                       gm1 * (Uw[4] - 0.5 * (Uw[1] * sS[n3 + qo] + Uw[2] * sS[2 * n3 + qo] + Uw[3] * sS[3 * n3 + qo]))};
       flux_c(Uw, Pw, nt, Fo);
-      const double cd = 2.0 * (plus ? D[N * n + N] : D[0]) - sg * lh;
+      const double cd = 2.0 * D[plus ? N * n + N : 0] - sg * lh;
       double F[5];
-      if ((GEN == 2 || FVM) && kind[x] == -2) {
+      if ((GEN == 2 || FVM) && kind[sd] == -2) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) F[v] = sg * Ux[x][v];
+        for (int v = 0; v < 5; ++v) F[v] = sg * Ux[sd][v];
       } else {
         const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
         const double ish = 1.0 / sh;
         const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
-        const bool bnd = GEN && kind[x] >= 0;
-        const bool outflow = bnd && kind[x] == DG_BC_OUTFLOW;
-        const bool given = bnd && (kind[x] == DG_BC_STATE || outflow);
-        const bool iso = bnd && kind[x] == DG_BC_WALL_ISOTHERMAL;
-        const bool wall = bnd && (kind[x] == DG_BC_WALL || iso);
+        const bool bnd = GEN && kind[sd] >= 0;
+        const bool outflow = bnd && kind[sd] == DG_BC_OUTFLOW;
+        const bool given = bnd && (kind[sd] == DG_BC_STATE || outflow);
+        const bool iso = bnd && kind[sd] == DG_BC_WALL_ISOTHERMAL;
+        const bool wall = bnd && (kind[sd] == DG_BC_WALL || iso);
         if (bnd) {
 #pragma unroll
-          for (int v = 0; v < 5; ++v) Ux[x][v] = Uw[v];
+          for (int v = 0; v < 5; ++v) Ux[sd][v] = Uw[v];
           if (outflow) {
             // pressure outflow: the own trace's density and velocity with p_out
-            Ux[x][4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
+            Ux[sd][4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
           } else if (given) {
 #pragma unroll
-            for (int v = 0; v < 5; ++v) Ux[x][v] = ph.ub[v];  // given outer state
+            for (int v = 0; v < 5; ++v) Ux[sd][v] = ph.ub[v];  // given outer state
           } else if (wall) {
-            Ux[x][1] = -Uw[1]; Ux[x][2] = -Uw[2]; Ux[x][3] = -Uw[3];  // no-slip wall: velocity reversed
+            Ux[sd][1] = -Uw[1]; Ux[sd][2] = -Uw[2]; Ux[sd][3] = -Uw[3];  // no-slip wall: velocity reversed
           } else {
-            mirror3(Ux[x] + 1, nh);  // symmetry plane: mirror image of the inner state
+            mirror3(Ux[sd] + 1, nh);  // symmetry plane: mirror image of the inner state
           }
         }
-        double UM[5], US[5];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) { UM[v] = plus ? Uw[v] : Ux[x][v]; US[v] = plus ? Ux[x][v] : Uw[v]; }
-        riemann_vf<VF>(ph, UM, US, nh, F);
+        riemann_vf<VF>(ph, plus ? Uw : Ux[sd], plus ? Ux[sd] : Uw, nh, F);
 #pragma unroll
         for (int v = 0; v < 5; ++v) F[v] *= sh;
         if (NS) {
@@ -1866,9 +1856,9 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
           // conforming face is continuous: the neighbour's Ja of its face direction is +-Ja^dir, + where
           // one side is a +xi side and the other a -xi side)
           double V[4];
-          const double sn = (GEN && f2[x].plus == plus) ? -1.0 : 1.0;
+          const double sn = (GEN && f2[sd].plus == plus) ? -1.0 : 1.0;
 #pragma unroll
-          for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[x][c] : 0.5 * (Vo[x][c] + sn * Vn[x][c]);
+          for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[sd][c] : 0.5 * (Vo[sd][c] + sn * Vn[sd][c]);
           if (!bnd || given) {
             // given outer state: the outer viscous flux equals the inner one
 #pragma unroll
@@ -1891,8 +1881,368 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
         }
       }
 #pragma unroll
-      for (int v = 0; v < 5; ++v) fe[x][v] = fma(cd, Fo[v], (sg * lh) * F[v]);
+      for (int v = 0; v < 5; ++v) fe[sd][v] = fma(cd, Fo[v], (sg * lh) * F[v]);
     }
+#pragma unroll
+    for (int m = 0; m < n; ++m)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) acc[m][v] = m == 0 ? fe[0][v] : (m == N ? fe[1][v] : 0.0);
+    // EC: where every pair of every line of this wave lies in the series' range (the largest ratio of a
+    // line is that of its largest and smallest value) the unrolled loop below needs no logarithm
+    bool series = true;
+    if constexpr (VF == 1) {
+      double r0 = sS[slot(0)], r1 = r0, b0 = sS[4 * n3 + slot(0)], b1 = b0;
+#pragma unroll
+      for (int m = 1; m < n; ++m) {
+        const double r = sS[slot(m)], bt = sS[4 * n3 + slot(m)];
+        r0 = fmin(r0, r); r1 = fmax(r1, r);
+        b0 = fmin(b0, bt); b1 = fmax(b1, bt);
+      }
+      const double dr = r1 - r0, sr = r1 + r0, db = b1 - b0, sb = b1 + b0;
+      series = dr * dr < 0.99e-4 * (sr * sr) && db * db < 0.99e-4 * (sb * sb);
+      series = __all(series);
+    }
+    if (VF != 1 || series) {
+      // node i in registers, its partners read from LDS one pair ahead of their use (a whole line in
+      // registers spills 500 bytes at n = 8); the first partner is the next row's node
+      auto node = [&](int m) -> LineNode {
+        LineNode x;
+        const int q = slot(m);
+        x.s = load_ps<VF>(sS, n3, q, gg);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) x.nv[d] = metric(d, q);
+        return x;
+      };
+      LineNode A = node(0), B = node(1), An = B, Bn = B;
+#pragma unroll
+      for (int i = 0; i + 1 < n; ++i) {
+#pragma unroll
+        for (int j = i + 1; j < n; ++j) {
+          if (j == i + 1) An = B;
+          if (j + 1 < n) Bn = node(j + 1);
+          else if (i + 2 < n) Bn = node(i + 2);
+          const double nS[3] = {A.nv[0] + B.nv[0], A.nv[1] + B.nv[1], A.nv[2] + B.nv[2]};
+          double F[5];
+          pair2<VF, true>(A.s, B.s, nS, kg, F);
+          const double Dij = D[i * n + j], Dji = D[j * n + i];
+#pragma unroll
+          for (int v = 0; v < 5; ++v) {
+            acc[i][v] = fma(Dij, F[v], acc[i][v]);
+            acc[j][v] = fma(Dji, F[v], acc[j][v]);
+          }
+          B = Bn;
+          // at most two pairs in flight: more spill (n <= 6 fits as scheduled)
+          if (n > 6 && (j - i) % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+        }
+        A = An;
+        asm volatile("" ::: "memory");  // the next row's partners are read again, not kept
+      }
+    } else {
+      // the same pairs (i, i + s mod n) with logarithms, the states read from LDS as they are met; a
+      // rolled loop over i whose sums move down one place per turn, so that node i's is always the first
+#pragma unroll 1
+      for (int i = 0; i < n; ++i) {
+        const int qi = slot(i);
+        const PS A = load_ps<VF>(sS, n3, qi, gg);
+        const double na[3] = {metric(0, qi), metric(1, qi), metric(2, qi)};
+#pragma unroll
+        for (int sft = 1; sft <= n / 2; ++sft) {
+          if (2 * sft == n && 2 * i >= n) continue;  // met from the other end
+          const int j = i + sft < n ? i + sft : i + sft - n;
+          const int qj = slot(j);
+          const PS B = load_ps<VF>(sS, n3, qj, gg);
+          const double nS[3] = {na[0] + metric(0, qj), na[1] + metric(1, qj), na[2] + metric(2, qj)};
+          double F[5];
+          pair2<VF>(A, B, nS, kg, F);
+          const double Dij = D[i * n + j], Dji = D[j * n + i];
+#pragma unroll
+          for (int v = 0; v < 5; ++v) {
+            acc[0][v] = fma(Dij, F[v], acc[0][v]);
+            acc[sft][v] = fma(Dji, F[v], acc[sft][v]);
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          const double x = acc[0][v];
+#pragma unroll
+          for (int m = 0; m + 1 < n; ++m) acc[m][v] = acc[m + 1][v];
+          acc[N][v] = x;
+        }
+      }
+    }
+  }
+  // the epilogue's loads are issued before the directions' sums meet
+  double Rq[IT][5], gd[IT][4], sjq[IT];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+      sjq[it] = AFF ? jc[9] : g.sJ[(size_t)e * n3 + t];
+      if (NS) {
+        // viscous part in strong form, formed by the lifting kernel
+#pragma unroll
+        for (int c = 0; c < 4; ++c) gd[it][c] = g.Gd[((size_t)e * 4 + c) * n3 + t];
+      }
+      if (mode == 1 && ca != 0.0) {
+        const double *Re = R + (size_t)e * 5 * n3;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Rq[it][v] = Re[v * n3 + t];
+      }
+    }
+  }
+  // the three directions' sums, in order
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    __syncthreads();
+    if (act && dir == d) {
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        const int q = d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m));
+#pragma unroll
+        for (int v = 0; v < 5; ++v) sAcc[v * n3 + q] = d == 0 ? acc[m][v] : sAcc[v * n3 + q] + acc[m][v];
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (!(valid && t < n3)) continue;
+    const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+    double r[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) r[v] = sAcc[v * n3 + q];
+    if (NS) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) r[1 + c] -= gd[it][c];
+    }
+    double *Oe = out + (size_t)e * 5 * n3;
+    if (mode == 0) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Oe[v * n3 + t] = -r[v] * sjq[it];
+    } else {
+      double *Re = R + (size_t)e * 5 * n3;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        // a = 0 (first stage) does not read R, so R may hold anything on entry
+        const double x = (ca != 0.0 ? ca * Rq[it][v] : 0.0) + dt * (-r[v] * sjq[it]);
+        Re[v * n3 + t] = x;
+        Oe[v * n3 + t] = sU[v * n3 + q] + cb * x;
+      }
+    }
+  }
+}
+
+template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
+__global__ void __launch_bounds__(SplitSz<N>::NT, split_minb(N, VF, AFF)) k_split(Geo g, Phys ph, const double *__restrict__ U,
+                                                     double *__restrict__ out, double *__restrict__ R, double ca,
+                                                     double cb, double dt, int mode) {
+  __shared__ double sm[AFF ? SplitLds<N>::AFFINE : SplitLds<N>::A];
+  const int e = xcd_element(blockIdx.x, g.K);
+  if (e >= g.K) return;
+  if (FVM && g.fvflag[e]) return;  // a finite-volume element
+  split_body<N, NS, VF, GEN, FVM, AFF>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
+}
+
+// The same with a lane per end of every line (see EndsSz): the fluxes at the two ends are evaluated at once, and with
+// the short pair fluxes each lane sums one half of the line's nodes.  For degrees 1 and 2, where both ends' lanes fit
+// the one wave (1 M nodes, curved, KEP: N = 1 2570 -> 1797 us a step, N = 2 913 -> 756), and for small meshes (small_mesh).
+// The bits are those of split_body.  (One body for both took 64 us instead of 62 at N = 5, curved, 16^3, from another
+// schedule alone.)
+template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
+__device__ __forceinline__ void split_ends(const Geo &g, const Phys &ph, const Tab *tab, int e, bool valid, int lane,
+                                           const double *__restrict__ U, double *__restrict__ out,
+                                           double *__restrict__ R, double ca, double cb, double dt, int mode,
+                                           double *sm) {
+  using S = Sz<N>;
+  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, NT = EndsSz<N>::NT, NL = 3 * n2;
+  constexpr bool WU = split_halves<N, VF>();
+  constexpr bool SEP = !ends_always(N);  // the directions' sums in LDS of their own
+  constexpr int IT = (n3 + NT - 1) / NT;  // nodes per lane in the node loops
+  const double gm1 = ph.gamma - 1.0, kg = 1.0 / gm1, gg = gm1 / ph.gamma;
+  const double *Ue = U + (size_t)e * 5 * n3;
+  const double *Jae = g.Ja + (size_t)e * 9 * n3;
+  double *sU = sm, *sS = sm + 5 * n3, *sJ = sm + 10 * n3;  // node slots: div_slot
+  double *sAcc = AFF || !ends_always(N) ? sS : sJ;
+  AffineConst jc = nullptr;
+  if constexpr (AFF) jc = affine_const(g, e);
+  // the 1D tables through the scalar cache
+  const __attribute__((address_space(4))) double *D = (const __attribute__((address_space(4))) double *)tab->D;
+  const double lh0 = tab->lhm[0], lhN = tab->lhp[N];
+  // this lane's line: direction, and its position (a, b) among the direction's lines, which is also the
+  // face point of its two ends, and the end whose flux it evaluates
+  const int end = line_end<N, true>(lane), line = lane - end * EndsSz<N>::HALF;
+  const int dir = n2 % 64 == 0 ? __builtin_amdgcn_readfirstlane(line / n2) : line / n2;
+  const int ab = line - dir * n2, a = ab % n, b = ab / n;
+  const bool act = valid && line < NL && end < 2;
+  // the two end faces' neighbours first (loads return in order: behind the others, the neighbours' traces
+  // would wait for all of them), then the state and metric terms for LDS and the faces' other sides
+  const int s = 2 * dir + end;
+  const bool plus = end;
+  int nb = 0;
+  NbFace f;
+  if (act) {
+    nb = g.nbr[(size_t)e * 6 + s];
+    f = nbr_face<n, (GEN > 0)>(g, e, s, a, b);
+  }
+  double Uq[IT][5];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Uq[it][v] = Ue[v * n3 + t];
+    }
+  }
+  double Jq[IT][9];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (!AFF && valid && t < n3) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) Jq[it][c] = Jae[c * n3 + t];
+    }
+  }
+  double Ux[5], Vo[4], Vn[4];  // the end face: the other side's state, both sides' viscous fluxes
+  int kind = -1;               // -1 inner face, else the boundary kind; -2 a face whose flux is given (Ux)
+  if (act) {
+    const bool bnd = GEN && f.bnd;
+    // the outward flux of a non-conforming face, or of one shared with a finite-volume element
+    const double *gx = nullptr;
+    if (GEN == 2 && bnd && f.kind == FACE_MORTAR) gx = g.mflux + (size_t)g.mslot[(size_t)e * 6 + s] * 5 * n2 + ab;
+    if (FVM && g.fvflag[nb]) gx = g.fvFx + ((size_t)e * 6 + s) * 5 * n2 + ab;
+    if ((GEN == 2 || FVM) && gx) {
+      kind = -2;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Ux[v] = gx[v * n2];
+    } else {
+      if (bnd) kind = f.kind;
+      if (!bnd) {
+        const double *Un = U + (size_t)nb * 5 * n3;
+        const int qn = GEN ? line_node<n>(f.dn, f.a, f.b, f.plus ? N : 0) : line_node<n>(dir, a, b, plus ? 0 : N);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Ux[v] = Un[v * n3 + qn];
+      }
+      if (NS) {
+        // both sides' contravariant viscous flux of the face's direction from the lifting (a boundary side:
+        // the own trace)
+        const double *fo = g.Gf + ((size_t)e * 6 + s) * 4 * n2 + ab;
+        const double *fnb = bnd ? fo : g.Gf + ((size_t)nb * 6 + 2 * f.dn + (f.plus ? 1 : 0)) * 4 * n2 + f.a + n * f.b;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) { Vo[c] = fo[c * n2]; Vn[c] = fnb[c * n2]; }
+      }
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = lane + it * NT;
+    if (valid && t < n3) {
+      const int q = div_slot<n>(t % n, (t / n) % n, t / n2);
+      const Pr5 P = to_prim(Uq[it], gm1);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sU[v * n3 + q] = Uq[it][v];
+      sS[q] = P.rho; sS[n3 + q] = P.u; sS[2 * n3 + q] = P.v; sS[3 * n3 + q] = P.w;
+      // beta = rho / (2 p) for EC, the total enthalpy otherwise
+      sS[4 * n3 + q] = (VF == 1) ? 0.5 * P.rho / P.p : (Uq[it][4] + P.p) / P.rho;
+#pragma unroll
+      for (int c = 0; c < 9 && !AFF; ++c) sJ[c * n3 + q] = Jq[it][c];
+    }
+  }
+  __syncthreads();
+  double acc[n][5];
+  constexpr int NF = WU ? 1 : 2;
+  double fe[NF][5];  // this lane's end (without split sums: then the line's two ends)
+  // the line direction's metric terms at a node
+  const double *sJd = sJ + 3 * dir * n3;
+  double jl[3] = {0.0, 0.0, 0.0};
+  auto metric = [&](int d, int q) -> double {
+    if constexpr (AFF) return jl[d];
+    else return sJd[d * n3 + q];
+  };
+  auto faces = [&](const LineSlots<n> &slot) {
+    if constexpr (AFF) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) jl[d] = dir == 0 ? jc[d] : (dir == 1 ? jc[3 + d] : jc[6 + d]);
+    }
+    // numerical surface fluxes at the line's ends, lifted (outward times lhat), and the interior
+    // convective part: 2 D_ii F(U_i) (D_ii is non-zero only at the ends of LGL lines) -+ lhat F_int
+    const int qo = slot(plus ? N : 0);
+    const double sg = plus ? 1.0 : -1.0, lh = plus ? lhN : lh0;
+    double Uw[5], Fo[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) Uw[v] = sU[v * n3 + qo];
+    // normal along +xi scaled by s-hat: Ja^dir at the face node, the master's on the master side and
+    // (up to rounding, the metric terms being continuous across the face) on the slave
+    const double nt[3] = {metric(0, qo), metric(1, qo), metric(2, qo)};
+    const Pr5 Pw = {Uw[0], sS[n3 + qo], sS[2 * n3 + qo], sS[3 * n3 + qo],
+                    gm1 * (Uw[4] - 0.5 * (Uw[1] * sS[n3 + qo] + Uw[2] * sS[2 * n3 + qo] + Uw[3] * sS[3 * n3 + qo]))};
+    flux_c(Uw, Pw, nt, Fo);
+    const double cd = 2.0 * (plus ? D[N * n + N] : D[0]) - sg * lh;
+    double F[5];
+    if ((GEN == 2 || FVM) && kind == -2) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) F[v] = sg * Ux[v];
+    } else {
+      const double sh = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
+      const double ish = 1.0 / sh;
+      const double nh[3] = {nt[0] * ish, nt[1] * ish, nt[2] * ish};
+      const bool bnd = GEN && kind >= 0;
+      const bool outflow = bnd && kind == DG_BC_OUTFLOW;
+      const bool given = bnd && (kind == DG_BC_STATE || outflow);
+      const bool iso = bnd && kind == DG_BC_WALL_ISOTHERMAL;
+      const bool wall = bnd && (kind == DG_BC_WALL || iso);
+      if (bnd) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Ux[v] = Uw[v];
+        if (outflow) {
+          // pressure outflow: the own trace's density and velocity with p_out
+          Ux[4] = ph.pout / gm1 + 0.5 * (Uw[1] * Uw[1] + Uw[2] * Uw[2] + Uw[3] * Uw[3]) / Uw[0];
+        } else if (given) {
+#pragma unroll
+          for (int v = 0; v < 5; ++v) Ux[v] = ph.ub[v];  // given outer state
+        } else if (wall) {
+          Ux[1] = -Uw[1]; Ux[2] = -Uw[2]; Ux[3] = -Uw[3];  // no-slip wall: velocity reversed
+        } else {
+          mirror3(Ux + 1, nh);  // symmetry plane: mirror image of the inner state
+        }
+      }
+      double UM[5], US[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) { UM[v] = plus ? Uw[v] : Ux[v]; US[v] = plus ? Ux[v] : Uw[v]; }
+      riemann_vf<VF>(ph, UM, US, nh, F);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) F[v] *= sh;
+      if (NS) {
+        // BR1 mean of the viscous fluxes along this side's +xi normal Ja^dir (the normal metric of a
+        // conforming face is continuous: the neighbour's Ja of its face direction is +-Ja^dir, + where
+        // one side is a +xi side and the other a -xi side)
+        double V[4];
+        const double sn = (GEN && f.plus == plus) ? -1.0 : 1.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) V[c] = bnd ? Vo[c] : 0.5 * (Vo[c] + sn * Vn[c]);
+        if (!bnd || given) {
+          // given outer state: the outer viscous flux equals the inner one
+#pragma unroll
+          for (int c = 0; c < 4; ++c) F[1 + c] -= V[c];
+        } else if (wall) {
+          // no-slip wall: the outer momentum flux equals the inner one, the outer energy flux is its
+          // negative (reversed velocity, mirrored heat flux), so the mean keeps the momentum; at an
+          // isothermal wall the outer gradient is the inner one, so the mean energy flux is the inner
+          // heat flux: the inner energy flux minus the work (tau Ja^dir) . u
+#pragma unroll
+          for (int c = 0; c < 3; ++c) F[1 + c] -= V[c];
+          if (iso) F[4] -= V[3] - (V[0] * Uw[1] + V[1] * Uw[2] + V[2] * Uw[3]) * (1.0 / Uw[0]);
+        } else {
+          // symmetry plane: the mirrored outer flux cancels the inner shear and heat flux, the mean
+          // keeps the normal part of the momentum flux
+          const double gm = V[0] * nh[0] + V[1] * nh[1] + V[2] * nh[2];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) F[1 + c] -= gm * nh[c];
+        }
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) fe[0][v] = fma(cd, Fo[v], (sg * lh) * F[v]);
   };
   // the sums of the nodes M0 <= m < M1 (all, or the near or the far half of the line): each node meets its partners
   // in the same order whoever sums it, so the bits do not depend on the split
@@ -1994,13 +2344,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, n / 2> IH;
   typedef std::integral_constant<int, n> IN;
-  if constexpr (!ENDS) {
-    if (act) {
-      const LineSlots<n> slot(dir, a, b);
-      faces(slot);
-      pairs(slot, I0(), IN());
-    }
-  } else if constexpr (WU) {
+  if constexpr (WU) {
     if (act) {
       const LineSlots<n> slot(dir, a, b);
       faces(slot);
@@ -2009,7 +2353,7 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
     }
   } else {
     // the far end's flux to the line's own lane
-    double *sF = sm + SplitLds<N>::template nodes<AFF, ENDS>();
+    double *sF = sm + SplitLds<N>::template nodes<AFF, true>();
     const LineSlots<n> slot(act ? dir : 0, act ? a : 0, act ? b : 0);
     if (act) faces(slot);
     if (act && end) {
@@ -2046,12 +2390,12 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
 #pragma unroll
   for (int d = 0; d < (SEP ? 1 : 3); ++d) {
     __syncthreads();
-    if (act && !(ENDS && !WU && end) && (SEP || dir == d)) {
+    if (act && (WU || !end) && (SEP || dir == d)) {
       const LineSlots<n> slot(dir, a, b);
       double *sD = sAcc + (SEP ? dir * 5 * n3 : 0);
 #pragma unroll
       for (int m = 0; m < n; ++m) {
-        if (ENDS && WU && (m >= n / 2) != (end != 0)) continue;
+        if (WU && (m >= n / 2) != (end != 0)) continue;
         const int q = SEP ? slot(m) : (d == 0 ? div_slot<n>(m, a, b) : (d == 1 ? div_slot<n>(a, m, b) : div_slot<n>(a, b, m)));
 #pragma unroll
         for (int v = 0; v < 5; ++v) sD[v * n3 + q] = SEP || d == 0 ? acc[m][v] : sD[v * n3 + q] + acc[m][v];
@@ -2091,15 +2435,15 @@ __device__ __forceinline__ void split_body(const Geo &g, const Phys &ph, const T
   }
 }
 
-template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF, bool ENDS>
-__global__ void __launch_bounds__((line_lanes<N, ENDS>()), (split_minb(N, VF, AFF))) k_split(Geo g, Phys ph, const double *__restrict__ U,
+template <int N, bool NS, int VF, int GEN, bool FVM, bool AFF>
+__global__ void __launch_bounds__(EndsSz<N>::NT, (split_minb(N, VF, AFF))) k_split_ends(Geo g, Phys ph, const double *__restrict__ U,
                                                      double *__restrict__ out, double *__restrict__ R, double ca,
                                                      double cb, double dt, int mode) {
-  __shared__ double sm[SplitLds<N>::template size<VF, AFF, ENDS>()];
+  __shared__ double sm[SplitLds<N>::template size<VF, AFF, true>()];
   const int e = xcd_element(blockIdx.x, g.K);
   if (e >= g.K) return;
   if (FVM && g.fvflag[e]) return;  // a finite-volume element
-  split_body<N, NS, VF, GEN, FVM, AFF, ENDS>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
+  split_ends<N, NS, VF, GEN, FVM, AFF>(g, ph, g.tab, e, true, threadIdx.x, U, out, R, ca, cb, dt, mode, sm);
 }
 
 // ----------------------------------------------------------------------------- weak/strong form, by lines
@@ -2561,6 +2905,13 @@ __global__ void __launch_bounds__((lift_b_lanes<N, AFF>()) * EPB, (lift_b_minb<N
   }
 }
 
+// one element of a member, one RK stage
+template <int N, bool NS, int VF, int GEN, bool AFF>
+__device__ __forceinline__ void split_member(const Member &M, const Tab *tab, int e, bool valid, int t, double *sm) {
+  if constexpr (ends_always(N)) split_ends<N, NS, VF, GEN, false, AFF>(M.g, M.ph, tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
+  else split_body<N, NS, VF, GEN, false, AFF>(M.g, M.ph, tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
+}
+
 template <int N, bool NS, int VF, int EPB, bool GEN, int AFF>
 __global__ void __launch_bounds__((line_lanes<N, ends_always(N)>()) * EPB, (split_minb(N, VF, AFF == AFF_ALL))) k_split_b(BatchView bv) {
   constexpr bool ENDS = ends_always(N);
@@ -2576,9 +2927,9 @@ __global__ void __launch_bounds__((line_lanes<N, ends_always(N)>()) * EPB, (spli
   const Member &M = bv.m[mi];
   const int e = valid ? item - bv.first[mi] : 0;
   if (AFF == AFF_ALL || (AFF == AFF_MIXED && B.affine))
-    split_body<N, NS, VF, GEN, false, true, ENDS>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
+    split_member<N, NS, VF, GEN, true>(M, bv.tab, e, valid, t, sm + slot * L);
   else
-    split_body<N, NS, VF, GEN, false, false, ENDS>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm + slot * L);
+    split_member<N, NS, VF, GEN, false>(M, bv.tab, e, valid, t, sm + slot * L);
 }
 
 // ----------------------------------------------------------------------------- reductions
@@ -3483,7 +3834,10 @@ static int launch_split_t(const Geo &g, const Phys &ph, const double *U, double 
                           double dt, int mode, hipStream_t st) {
   const dim3 grid(xcd_grid(g.K));
 #define DG_KSE(G_, F_, A_, E_) \
-  hipLaunchKernelGGL((k_split<N, NS, VF, G_, F_, A_, E_>), grid, dim3(line_lanes<N, E_>()), 0, st, g, ph, U, out, R, a, b, dt, mode)
+  do { \
+    if constexpr (E_) hipLaunchKernelGGL((k_split_ends<N, NS, VF, G_, F_, A_>), grid, dim3(EndsSz<N>::NT), 0, st, g, ph, U, out, R, a, b, dt, mode); \
+    else hipLaunchKernelGGL((k_split<N, NS, VF, G_, F_, A_>), grid, dim3(SplitSz<N>::NT), 0, st, g, ph, U, out, R, a, b, dt, mode); \
+  } while (0)
 #define DG_KS(G_, F_, E_) \
   do { if (g.Jc) DG_KSE(G_, F_, true, E_); else DG_KSE(G_, F_, false, E_); } while (0)
   // GEN: 0 structured, 1 face codes, 2 face codes and non-conforming faces
@@ -3826,9 +4180,9 @@ __device__ __forceinline__ void fused_split_group(const BatchView &bv, int blk, 
   const int e = valid ? item - bv.first[mi] : 0;
   double *sm = smem + slot * L;
   if (B.affine)
-    split_body<N, NS, VF, 0, false, true, ENDS>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
+    split_member<N, NS, VF, 0, true>(M, bv.tab, e, valid, t, sm);
   else
-    split_body<N, NS, VF, 0, false, false, ENDS>(M.g, M.ph, bv.tab, e, valid, t, M.U, M.out, M.R, M.a, M.b, M.dt, 1, sm);
+    split_member<N, NS, VF, 0, false>(M, bv.tab, e, valid, t, sm);
 }
 
 template <bool NS, int VF>
