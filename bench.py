@@ -30,17 +30,23 @@ if ROOT not in sys.path:
 METRIC = "DOF-updates/s (PID s/DOF/stage) at N=7 TGV; adjoint/forward cost ratio"
 HBM_PEAK_GBS = 8000.0
 # split-form operator at N = 7 on affine elements: U 5 + viscous divergence 4 + own face traces of the viscous
-# fluxes 3 (24 n^2 values per element, n = 8) + R 5 read, U_new 5 + R 5 written (curved elements: Ja 9 + 1/J 1 more)
+# fluxes 3 (24 n^2 values per element, n = 8) + R 5 read, U_new 5 + R 5 written (curved elements: BYTES_METRIC more)
 BYTES_MAIN = 27 * 8
-# lifting for the split form: U 5 read, viscous divergence 4 + face traces 3 written (curved: Ja 9 + 1/J 1 more)
+# lifting for the split form: U 5 read, viscous divergence 4 + face traces 3 written (curved: BYTES_METRIC more)
 BYTES_LIFT = 12 * 8
 # weak-form operator at N = 7 (Navier-Stokes) on affine elements: U 5 + viscous volume term 4 + own face viscous
 # fluxes 3 (24 n^2 per element) + R 5 read, U_new 5 + R 5 written
 BYTES_WEAK_MAIN = 27 * 8
+# per-node metric terms, read by the operator and by the lifting kernel where the mesh is not affine
+BYTES_METRIC = 10 * 8
 # reverse stage on curved elements: k_vjp_line reads U 5, the kept viscous fluxes' momentum part 9, Ja 9, 1/J 1,
 # Ubar_t 5, Ubar 5 and writes Ubar 5; k_vjp_face reads Ubar 5, Rbar 5 and writes Rbar 5
 BYTES_VJP_MAIN = 39 * 8
 BYTES_VJP_FACE = 15 * 8
+
+
+def metric_terms(S) -> str:
+    return "per element" if S.affine else "per node"
 
 
 def bytes_fv(n: int) -> float:
@@ -51,7 +57,7 @@ def bytes_fv(n: int) -> float:
 
 # HBM traffic of the split kernel from committed counter summaries: FETCH_SIZE and WRITE_SIZE
 # (KiB per dispatch) of one rocprofv3 --pmc pass each, scaled by the factors a 1 GiB
-# device-to-device copy gives on the same box; valid only while the kernel sources still hash
+# device-to-device copy gives on the same card; valid only while the kernel sources still hash
 # to the value recorded with the counters.
 COUNTERS = os.path.join(ROOT, "profiles", "k_split_ns_ec_n7_k48_counters.txt")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1910_02858_amd", "csrc", f) for f in ("dg_kernels.hip", "dg_internal.h", "dg_lines.h")]
@@ -195,7 +201,7 @@ def adjoint_ratio(dgsem, inputs, torch, repeats: int = 2, general: bool = False,
 def ensemble_bench(dgsem, inputs, torch, steps: int = 10, n_members: int = 256):
     """Seeded ensemble of uneven members (K1 ~ U{4..12}, N ~ U{3..7}, amplitude and Mach drawn per
     member; split KEP + Roe + BR1, TGV): DOF updates per second of whole RK steps for
-    (a) the batched step replayed as one HIP graph, with one lifting and one operator launch per
+    (a) the batched step replayed as HIP graphs (one per degree, or one for all), with one lifting and one operator launch per
     stage for all degrees (fused) and with one pair per degree, (b) the batched stages launched
     eagerly and (c) every member advanced with its own one-mesh launches, all on the same GPU;
     ``batched_graph`` is the launch mode the tuner chose."""
@@ -305,8 +311,8 @@ def weak_form_bench(dgsem, inputs, torch, stages: int = 10):
     elements, the Navier-Stokes TGV (central volume flux, Roe, BR1) in weak and strong form at N=7
     on 48^3 on LG and on LGL nodes (strong form on LGL nodes: the split form's reads), all
     56.6 M nodes; per-kernel times (the lifting's includes the LG prolongation), the operator
-    kernel priced at 216 B per node (affine elements) or at its Euler reads and writes (U 5, R 5
-    read, U_new 5, R 5 written: 160 B)."""
+    kernel priced at 216 B per node or at its Euler reads and writes (U 5, R 5 read, U_new 5,
+    R 5 written: 160 B), and at the per-node metric terms where the library reads them."""
     out = {}
     for name, wl, nbytes in (("euler_dwave_lg3_k96_weak", inputs.workload(1, K1=96), 20 * 8),
                              ("ns_tgv_central_roe_lg7_k48_weak",
@@ -337,8 +343,9 @@ def weak_form_bench(dgsem, inputs, torch, stages: int = 10):
         dof = S.K * S.n3
         main_ms = prof["main_ms"] / max(prof["main_launches"], 1)
         lift_ms = prof["lift_ms"] / max(prof["lift_launches"], 1) if prof["lift_launches"] else 0.0
+        nbytes += 0 if S.affine else BYTES_METRIC
         gbs = nbytes * dof / (main_ms * 1e-3) / 1e9
-        out[name] = {"dof": dof, "kernels_ms": {"main": main_ms, "lift": lift_ms},
+        out[name] = {"dof": dof, "metric_terms": metric_terms(S), "kernels_ms": {"main": main_ms, "lift": lift_ms},
                      "value": dof / ((main_ms + lift_ms) * 1e-3),
                      "roofline": {"bound": "hbm", "kernel": "k_line (" + name.rsplit("_", 1)[1] + " form)", "achieved": gbs,
                                   "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
@@ -678,8 +685,11 @@ def main():
     S.profile(False)
     main_ms = prof["main_ms"] / max(prof["main_launches"], 1)
     lift_ms = prof["lift_ms"] / max(prof["lift_launches"], 1)
-    main_gbs = BYTES_MAIN * dof / (main_ms * 1e-3) / 1e9
-    lift_gbs = BYTES_LIFT * dof / (lift_ms * 1e-3) / 1e9
+    metric = 0 if S.affine else BYTES_METRIC
+    path = metric_terms(S)
+    main_bytes, lift_bytes = BYTES_MAIN + metric, BYTES_LIFT + metric
+    main_gbs = main_bytes * dof / (main_ms * 1e-3) / 1e9
+    lift_gbs = lift_bytes * dof / (lift_ms * 1e-3) / 1e9
 
     ec_branch = None
     if not args.no_ec_branch and wl.volflux == "ec":
@@ -739,12 +749,12 @@ def main():
         "roofline": {"bound": "hbm", "kernel": "k_split (face fluxes + split volume integral + surface integral + RK update)", "achieved": main_gbs,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": main_gbs / HBM_PEAK_GBS, "traffic": traffic_gbs,
                      "traffic_bytes_per_launch": tbytes if traffic_gbs is not None else None,
-                     "algorithmic_bytes_per_dof": BYTES_MAIN},
+                     "algorithmic_bytes_per_dof": main_bytes, "metric_terms": path},
         "roofline_lift": {"achieved": lift_gbs, "frac": lift_gbs / HBM_PEAK_GBS,
-                          "algorithmic_bytes_per_dof": BYTES_LIFT},
-        "stage_hbm_frac": (BYTES_MAIN + BYTES_LIFT) * dof * stages / wall / 1e9 / HBM_PEAK_GBS,
+                          "algorithmic_bytes_per_dof": lift_bytes},
+        "stage_hbm_frac": (main_bytes + lift_bytes) * dof * stages / wall / 1e9 / HBM_PEAK_GBS,
         "copy_gbs": copy_gbs,
-        "stage_frac_of_copy": ((BYTES_MAIN + BYTES_LIFT) * dof * stages / wall / 1e9 / copy_gbs
+        "stage_frac_of_copy": ((main_bytes + lift_bytes) * dof * stages / wall / 1e9 / copy_gbs
                                if copy_gbs else None),
         "adjoint_forward_ratio": None,
     }

@@ -301,6 +301,12 @@ int dg_node_coords(dg_handle *h, double *x_host);
 /* Sizes: out[0] = K, out[1] = N, out[2] = n^3, out[3] = node type. */
 int dg_info(const dg_handle *h, int64_t out[4]);
 
+/* Which metric terms the operator and lifting kernels read: 1 if every element of the mesh is
+ * affine within the rounding of its coordinates (one set of constants per element, 10 doubles
+ * per node less to read in each of the two kernels), 0 if they read Ja and 1/J at every node.
+ * A null handle gives DG_ERR_ARG. */
+int dg_affine(const dg_handle *h);
+
 /* Per-kernel timing for performance reports.  With enable != 0 every later dg_rhs /
  * dg_rk_stage records HIP events around the lifting and the main kernel on the handle's
  * stream and waits for them (so calls become synchronous); dg_profile also clears the

@@ -1115,6 +1115,8 @@ int dg_info(const dg_handle *h, int64_t out[4]) {
   return DG_OK;
 }
 
+int dg_affine(const dg_handle *h) { return h ? h->d_Jc != nullptr : (int)DG_ERR_ARG; }
+
 int dg_rhs(dg_handle *h, const double *U, double *Ut) {
   if (!h) return DG_ERR_ARG;
   int rc = check_solution_ptr(h, U, "U");

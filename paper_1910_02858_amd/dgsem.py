@@ -33,6 +33,7 @@ EXPORTS = [
     "dg_batch_info", "dg_batch_last_error", "dg_rk_stage_keep", "dg_rk_step_vjp", "dg_rk_steps_vjp",
     "dg_integrals_noalloc", "dg_profile_read_ex", "dg_mesh_file_write", "dg_mesh_file_info", "dg_mesh_file_read",
     "dg_mesh_connect_nodes", "dg_fv_enable", "dg_fv_set_types", "dg_fv_types", "dg_fv_indicator", "dg_fv_switch",
+    "dg_affine",
 ]
 
 
@@ -101,6 +102,7 @@ def lib():
         L.dg_node_coords.argtypes = [_VP, _D]
         L.dg_mass_weights.argtypes = [_VP, _VP]
         L.dg_info.argtypes = [_VP, ctypes.POINTER(ctypes.c_int64)]
+        L.dg_affine.argtypes = [_VP]
         L.dg_destroy.argtypes = [_VP]
         L.dg_destroy.restype = None
         L.dg_status_string.restype = ctypes.c_char_p
@@ -448,6 +450,11 @@ class DGSolver:
         self._sync_stream()
         self._check(lib().dg_fv_switch(self.h, _VP(_dptr(U))), "dg_fv_switch")
 
+    @property
+    def affine(self) -> bool:
+        """Whether the kernels use one set of metric terms per element (dg_affine)."""
+        return lib().dg_affine(self.h) == 1
+
     def check_finite(self, U) -> bool:
         self._sync_stream()
         rc = lib().dg_check_finite(self.h, _VP(_dptr(U)))
@@ -500,7 +507,7 @@ class DGSolver:
 
 class Batch:
     """Several solvers advanced together (``dg_batch``): one lifting and one operator launch per
-    degree present and stage, optionally one HIP graph per RK step.  All solvers must use the
+    degree present and stage, optionally as HIP graphs, one RK step a replay.  All solvers must use the
     split form on LGL nodes with the same equations, volume flux and Riemann solver."""
 
     def __init__(self, solvers):

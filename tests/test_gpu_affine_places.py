@@ -148,3 +148,17 @@ def test_refined_lattice_freestream_and_conservation(dg, orc, form, vf, nodes, e
     print("conservation", np.abs(tot / scale).max(), flush=True)
     assert np.abs(Ut).max() < 1e-12 * fscale
     assert np.all(np.abs(tot) < 1e-13 * scale), (tot, scale)
+
+
+@pytest.mark.parametrize("N", [3, 7])
+def test_which_metric_terms_are_read(dg, orc, N):
+    """dg_affine: a lattice, shifted or turned, reads one set per element; a curved mesh and a lattice with one node
+    moved by more than rounding read them at every node."""
+    k = (12, 3, 2)
+    wl = inputs.workload(2, N=N)
+    nbr, side, _ = inputs.periodic_lattice(*k)
+    X = _lattice(orc.basis(N, "lgl")["x"], k, "turned")
+    moved = X.copy()
+    moved[1, 0, 0] += 1e-9
+    curved = X + 0.02 * np.sin(X[:, [1, 2, 0]])
+    assert [gpu_solver(dg, wl, np.ascontiguousarray(x), nbr, side).affine for x in (X, moved, curved)] == [True, False, False]
