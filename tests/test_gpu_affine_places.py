@@ -158,7 +158,7 @@ def test_which_metric_terms_are_read(dg, orc, N):
     wl = inputs.workload(2, N=N)
     nbr, side, _ = inputs.periodic_lattice(*k)
     X = _lattice(orc.basis(N, "lgl")["x"], k, "turned")
-    moved = X.copy()
-    moved[1, 0, 0] += 1e-9
-    curved = X + 0.02 * np.sin(X[:, [1, 2, 0]])
+    moved, P = X.copy(), inputs.lattice_points(orc.basis(N, "lgl")["x"], *k)
+    moved[1, 0, 1 + (N + 1) * (N + 2)] += 1e-9  # an inner node
+    curved = P + 0.02 * np.sin(P[:, [1, 2, 0]])  # periodic like the lattice
     assert [gpu_solver(dg, wl, np.ascontiguousarray(x), nbr, side).affine for x in (X, moved, curved)] == [True, False, False]
