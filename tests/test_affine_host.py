@@ -157,3 +157,38 @@ def test_mortar_sides_are_not_tied(orc, affine):
     assert C is not None
     area = np.abs(C[:, 0])
     assert np.isclose(area.max() / area.min(), 4.0)
+
+
+@pytest.mark.parametrize("N", [2, 3, 7])
+def test_every_node_decides_near_the_limit(orc, affine, N):
+    """Single sheared elements far enough from the origin that the rounding of their coordinates is about the share
+    of the element that counts as rounding: accepted exactly where every node's own deviation is within it, also
+    where the largest deviations of the three coordinates, taken together, are not."""
+    x = orc.basis(N, "lgl")["x"]
+    n, rng = N + 1, np.random.default_rng(N)
+    nbr, side = np.full((1, 6), -1, np.int32), np.zeros((1, 6), np.int8)
+    xl = x.astype(np.longdouble)
+    ref = np.stack((np.tile(xl, n * n), np.tile(np.repeat(xl, n), n), np.repeat(xl, n * n)))
+    accepted = rejected = together_only = 0
+    for _ in range(400):
+        A0 = np.eye(3) + 0.4 * rng.standard_normal((3, 3))
+        if np.linalg.det(A0) < 0.2:
+            continue
+        X = (A0.T @ ref.astype(float) + rng.uniform(200, 3200, (3, 1)) / n)[None]
+        Y = X[0].astype(np.longdouble).reshape(3, n, n, n)
+        Y = Y - Y[:, :1, :1, :1]
+        cs = Y[:, ::N, ::N, ::N]
+        c = cs.mean((1, 2, 3))
+        A = np.stack([(np.take(cs, 1, a) - np.take(cs, 0, a)).mean((1, 2)) / 2 for a in (3, 2, 1)])
+        v = Y.reshape(3, -1) - c[:, None] - A.T @ ref
+        Ja = np.stack([np.cross(A[(i + 1) % 3], A[(i + 2) % 3]) for i in range(3)])
+        J, limit = A[0] @ Ja[0], 2 * np.longdouble(1.6e-13) / n
+        moved, together = np.abs(Ja @ v).max() / J, (np.abs(Ja) @ np.abs(v).max(1)).max() / J
+        if abs(moved / limit - 1) < 1e-6:  # the two sums' own rounding
+            continue
+        ok = bool(moved <= limit)
+        assert np.abs(v).max() <= 4 * 2.0 ** -52 * np.abs(X).max()
+        assert (affine(x, X, nbr, side) is not None) == ok, (moved, limit)
+        accepted, rejected, together_only = accepted + ok, rejected + (not ok), together_only + (ok and together > limit)
+    print(accepted, rejected, together_only)
+    assert min(accepted, rejected, together_only) >= 10
